@@ -20,8 +20,8 @@
 #include "../../include/firesim.h"
 #include "rl.hpp"
 #include "internal.hpp"
+#include "plane.hpp"
 #include "relaxed.hpp"
-#include "resident.hpp"
 
 using namespace firesim;
 
@@ -63,7 +63,7 @@ struct PlanGroup {
     int64_t n_cells = 0;             // cells of its envs
     int32_t max_h = 0, max_w = 0;    // largest H and W among them
     bool aligned = true;             // every env W % 4 == 0 with a 4-aligned offset
-    ResidentShape res;               // the resident kernel's LDS layout over its envs
+    ResidentShape res;               // whether its envs may take the resident plan
     sim_plan plan{4, 64, 1, 1, 1, 0, 0};
     float tuned_ms = 0.0f;           // the autotuner's time per step (0: not timed)
     bool from_cache = false;
@@ -74,10 +74,34 @@ struct PlanGroup {
     int32_t n_tiles = 0;
     int32_t tiles_rt = 0;            // tile_rows the tile list was built for
     int32_t tiles_tw = 0;            // tile_width the tile list was built for
+    // the bit-plane kernel's tiles: launches of whole envs, and the tiles of
+    // the envs that do not fit LDS whole, with their run marks
+    std::vector<PlaneLaunch> plane_whole;
+    PlaneLaunch plane_parts{};       // n_tiles == 0: every env is whole
+    int32_t plane_threads = -1;      // the plan's resident value they were built for (-1: not built)
+    PlaneTile* d_ptiles = nullptr;
+    int32_t* d_ptile_nbr = nullptr;  // [parts][8] neighbouring tiles (-1 off the env)
+    int32_t* d_part_work = nullptr;  // their marks [2][parts], list counts [4], lists [2][parts]
+    int32_t* d_part_envs = nullptr;  // envs cut into parts
+    int32_t n_part_envs = 0;
 };
+
+void free_planes(PlanGroup& g)
+{
+    for (void** p : {(void**)&g.d_ptiles, (void**)&g.d_ptile_nbr, (void**)&g.d_part_work,
+                     (void**)&g.d_part_envs}) {
+        if (*p) (void)hipFree(*p);
+        *p = nullptr;
+    }
+    g.plane_whole.clear();
+    g.plane_parts = PlaneLaunch{};
+    g.plane_threads = -1;
+    g.n_part_envs = 0;
+}
 
 void free_group(PlanGroup& g)
 {
+    free_planes(g);
     for (void* p : {(void*)g.d_list, (void*)g.d_tiles, (void*)g.d_tile_nbr, (void*)g.d_tile_burn,
                     (void*)g.d_tile_eq})
         if (p) (void)hipFree(p);
@@ -114,6 +138,7 @@ struct sim_handle {
     // tiles with no fire in reach skipped (the dense plan, which streams every
     // cell's 10 bytes each step, is {4, 256, 1, 0, 0, 0})
     sim_plan plan{4, 64, 1, 1, 1, 0, 0};
+    size_t plane_lds = 0;  // the largest dynamic LDS of the bit-plane kernel
     // the whole batch under `plan`, or (when non-empty) its size classes under their own plans
     PlanGroup all;
     std::vector<PlanGroup> classes;
@@ -144,6 +169,7 @@ struct sim_handle {
     uint8_t* d_cls = nullptr;
     float* d_den = nullptr;
     float* d_wind = nullptr;
+    float* d_phi = nullptr;            // [n_cells][8] ignition rate of every edge (nullptr: worked out in the step)
     uint8_t* d_init_states = nullptr;  // initial fire state (for the relaxed initial state)
     uint8_t* d_tmp = nullptr;          // ping-pong state buffer
     uint32_t* d_t = nullptr;           // step counter base read by the step kernels
@@ -202,7 +228,7 @@ private:
 
 void free_all(sim_handle* h)
 {
-    void* ptrs[] = {h->d_envs, h->d_chunk_env, h->d_loss_scratch, h->d_g, h->d_E, h->d_cls, h->d_den, h->d_wind, h->d_init_states,
+    void* ptrs[] = {h->d_envs, h->d_chunk_env, h->d_loss_scratch, h->d_g, h->d_E, h->d_cls, h->d_den, h->d_wind, h->d_phi, h->d_init_states,
                     h->d_tmp, h->d_t, h->d_rl_drop, h->d_rl_counts};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -303,9 +329,159 @@ std::vector<PlanGroup*> active_groups(sim_handle* h)
     return out;
 }
 
-// Rebuild a group's tile list if its plan changed the geometry.
+// The bit-plane kernel's dynamic-LDS limit is an attribute of the kernel
+// functions, shared by every handle in the process: it is raised once per
+// device to everything the device allows beside the kernel's static LDS, so
+// that no batch lowers it under another's.  Returns whether that worked.
+bool plane_lds_allowed(int device, int max_lds)
+{
+    static std::mutex mu;
+    static int state[kMaxDevices] = {};  // 0 not tried, 1 set, 2 refused
+    if (device < 0 || device >= kMaxDevices) return false;
+    std::lock_guard<std::mutex> lock(mu);
+    if (state[device] == 0) {
+        const bool ok = plane_set_lds_limit(max_lds - (int)kPlaneStaticLds) == hipSuccess;
+        if (!ok) (void)hipGetLastError();  // not sticky: the batches just take the tiled kernels
+        state[device] = ok ? 1 : 2;
+    }
+    return state[device] == 1;
+}
+
+// The largest dynamic LDS the bit-plane kernel may take, 0 if it cannot run.
+size_t plane_lds_limit(int device)
+{
+    int max_lds = 0;
+    if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess ||
+        max_lds <= (int)kPlaneStaticLds || !plane_lds_allowed(device, max_lds))
+        return 0;
+    return (size_t)max_lds - kPlaneStaticLds;
+}
+
+// Do the group's steps run on the bit-plane kernel?  The plans that read fuel
+// and elevation at fronts only and skip what has no fire in reach: the
+// sparse front-skipping plan and the resident plan.
+bool wants_planes(const sim_plan& p) { return p.resident != 0 || (p.skip_static && p.sparse && p.temporal <= 1); }
+
+// Lanes of the workgroup that takes an env of `cells` cells.  Measured, 200
+// steps: 256 envs of 128 x 128 take 0.84 ms with 512 lanes, 1.10 ms with 256;
+// 192 envs of up to 331 x 331 1.31 ms with 1024 for the large ones, 1.56 ms
+// with 512; 1024 envs of 256 x 256 2.55 ms with 512, 4.4 ms with 1024.
+int plane_threads_for(int64_t cells)
+{
+    return cells >= 96 * 1024 ? 1024 : (cells >= 1536 ? 512 : 64);
+}
+
+// The tiles and launches of group g's bit-plane steps.  An env is taken whole
+// where its planes fit LDS, else in parts of kPartRows x kPartCols.  Whole
+// envs are launched together when the chip holds one workgroup of each at
+// once; else by workgroup size, so that small envs share a compute unit.
+constexpr int kPartRows = 64, kPartCols = 128, kPartSteps = 16;
+int build_planes(sim_handle* h, PlanGroup& g)
+{
+    free_planes(g);
+    const size_t limit = h->plane_lds = plane_lds_limit(h->device);
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) cus = 1;
+    g.plane_threads = g.plan.resident;
+    if (limit == 0) return SIM_OK;
+    struct Whole {
+        int32_t env, threads;
+        int64_t cells;
+    };
+    std::vector<Whole> whole;
+    std::vector<PlaneTile> tiles, parts;
+    std::vector<int32_t> nbr, part_envs;
+    const int32_t n_members = g.envs.empty() ? h->n_env : (int32_t)g.envs.size();
+    for (int32_t q = 0; q < n_members; ++q) {
+        const int32_t e = g.envs.empty() ? q : g.envs[q];
+        const int H = h->envs[e].H, W = h->envs[e].W;
+        const int64_t cells = (int64_t)H * W;
+        // room for four planes and the largest workgroup's lists: whether an
+        // env is whole does not depend on the call
+        if (plane_indexable(H, W) &&
+            plane_lds_bytes(plane_frame_words(H, W), 4, 512, plane_list_cap(H, W)) <= limit) {
+            whole.push_back({e, g.plan.resident ? g.plan.resident : plane_threads_for(cells), cells});
+            continue;
+        }
+        part_envs.push_back(e);
+        const int nr = (H + kPartRows - 1) / kPartRows, nc = (W + kPartCols - 1) / kPartCols;
+        const int32_t first = (int32_t)parts.size();
+        for (int i = 0; i < nr; ++i)
+            for (int j = 0; j < nc; ++j) {
+                parts.push_back(PlaneTile{e, i * kPartRows, j * kPartCols, std::min(kPartRows, H - i * kPartRows),
+                                          std::min(kPartCols, W - j * kPartCols)});
+                for (int di = -1; di <= 1; ++di)
+                    for (int dj = -1; dj <= 1; ++dj) {
+                        if (di == 0 && dj == 0) continue;
+                        const int a = i + di, b = j + dj;
+                        nbr.push_back(a >= 0 && a < nr && b >= 0 && b < nc ? first + a * nc + b : -1);
+                    }
+            }
+    }
+    std::stable_sort(whole.begin(), whole.end(), [](const Whole& a, const Whole& b) { return a.cells > b.cells; });
+    if (!whole.empty() && whole.size() <= (size_t)cus)
+        for (Whole& w : whole) w.threads = whole[0].threads;
+    for (const Whole& w : whole) {
+        const int H = h->envs[w.env].H, W = h->envs[w.env].W;
+        if (g.plane_whole.empty() || g.plane_whole.back().threads != w.threads) {
+            PlaneLaunch L{};
+            L.threads = w.threads;
+            g.plane_whole.push_back(L);
+        }
+        PlaneLaunch& L = g.plane_whole.back();
+        L.n_tiles += 1;
+        L.frame_words = std::max(L.frame_words, (int32_t)plane_frame_words(H, W));
+        L.list_cap = std::max(L.list_cap, plane_list_cap(H, W));
+        tiles.push_back(PlaneTile{w.env, 0, 0, H, W});
+    }
+    const size_t n_whole = tiles.size(), n_parts = parts.size();
+    tiles.insert(tiles.end(), parts.begin(), parts.end());
+    auto upload = [&](auto** p, const auto* from, size_t n) {
+        return hipMalloc(p, n * sizeof(**p)) == hipSuccess &&
+               hipMemcpy(*p, from, n * sizeof(**p), hipMemcpyHostToDevice) == hipSuccess;
+    };
+    bool ok = upload(&g.d_ptiles, tiles.data(), tiles.size());
+    if (n_parts)
+        ok = ok && upload(&g.d_ptile_nbr, nbr.data(), nbr.size()) &&
+             upload(&g.d_part_envs, part_envs.data(), part_envs.size()) &&
+             hipMalloc(&g.d_part_work, (4 * n_parts + 4) * sizeof(int32_t)) == hipSuccess;
+    if (!ok) {
+        free_planes(g);
+        return fail(h, SIM_ENOMEM, "tile list allocation failed");
+    }
+    size_t at = 0;
+    for (PlaneLaunch& L : g.plane_whole) {
+        L.tiles = g.d_ptiles + at;
+        at += (size_t)L.n_tiles;
+    }
+    if (n_parts) {
+        PlaneLaunch& L = g.plane_parts;
+        L.tiles = g.d_ptiles + n_whole;
+        L.n_tiles = (int32_t)n_parts;
+        L.halo = kPartSteps;
+        L.threads = kPlaneHaloThreads;
+        const int rows = kPartRows + 2 * kPartSteps, cols = kPartCols + 2 * kPlaneHaloCols;
+        L.frame_words = (int32_t)plane_frame_words(rows, cols);
+        L.list_cap = plane_list_cap(rows, cols);
+        g.n_part_envs = (int32_t)part_envs.size();
+    }
+    return SIM_OK;
+}
+
+bool has_planes(const PlanGroup& g) { return !g.plane_whole.empty() || g.plane_parts.n_tiles > 0; }
+
+// Rebuild a group's tile lists if its plan changed the geometry.  A group
+// whose envs all run whole on the bit-plane kernel needs no other tiles.
 int ensure_group_tiles(sim_handle* h, PlanGroup& g)
 {
+    if (wants_planes(g.plan)) {
+        if (g.plane_threads != g.plan.resident) {
+            h->graph.valid = false;
+            const int rc = build_planes(h, g);
+            if (rc != SIM_OK) return rc;
+        }
+        if (has_planes(g) && g.plane_parts.n_tiles == 0) return SIM_OK;
+    }
     if (g.tiles_rt == tiles_key(g.plan) && g.tiles_tw == g.plan.tile_width) return SIM_OK;
     h->graph.valid = false;
     return build_tiles(h, g, tiles_key(g.plan), g.plan.tile_width);
@@ -318,25 +494,6 @@ int ensure_tiles(sim_handle* h)
         if (rc != SIM_OK) return rc;
     }
     return SIM_OK;
-}
-
-// The resident kernel's dynamic-LDS limit is an attribute of the kernel
-// functions, shared by every handle in the process: it is raised once per
-// device to everything the device allows beside the kernel's static LDS, so
-// that no batch lowers it under another's.  Returns whether that worked.
-constexpr size_t kResidentStaticLds = 2560;
-bool resident_lds_allowed(int device, int max_lds)
-{
-    static std::mutex mu;
-    static int state[kMaxDevices] = {};  // 0 not tried, 1 set, 2 refused
-    if (device < 0 || device >= kMaxDevices) return false;
-    std::lock_guard<std::mutex> lock(mu);
-    if (state[device] == 0) {
-        const bool ok = resident_set_lds_limit(max_lds - (int)kResidentStaticLds) == hipSuccess;
-        if (!ok) (void)hipGetLastError();  // not sticky: the batches just do not take the plan
-        state[device] = ok ? 1 : 2;
-    }
-    return state[device] == 1;
 }
 
 // The resident workgroup size a new handle starts with, 0 for the tiled
@@ -393,10 +550,8 @@ void describe_group(sim_handle* h, PlanGroup& g)
         max_frame <= max_lds) {
         g.res.frame_cap = (int32_t)((max_frame + 3) & ~3);
         g.res.cell_cap = (int32_t)max_cells;
-        // the kernel's own static LDS (under 2.5 KiB) comes on top of the dynamic part
         const size_t need = resident_lds_bytes(g.res);
-        g.res.fits = need + kResidentStaticLds <= (size_t)max_lds && resident_lds_allowed(h->device, max_lds);
-
+        g.res.fits = need + kResidentStaticLds <= (size_t)max_lds && plane_lds_allowed(h->device, max_lds);
     }
 }
 
@@ -429,6 +584,69 @@ hipError_t copy_group(sim_handle* h, hipStream_t s, const PlanGroup& g, uint8_t*
     return launch_copy_envs(s, h->d_envs, g.d_list, (int32_t)g.envs.size(), dst, src);
 }
 
+// The T steps of group g on the bit-plane kernel: one launch per workgroup
+// size for the whole envs, in place, and launches of up to kPartSteps steps
+// between the two state buffers for the envs in parts (an even number of
+// them where T allows, so that the result ends in `states`).
+hipError_t enqueue_planes(sim_handle* h, PlanGroup& g, hipStream_t s, const StepLaunch& L, uint8_t* states,
+                          const int32_t* actions, int32_t T, int32_t* counts, uint8_t* history)
+{
+    hipError_t e;
+    auto with_inputs = [&](PlaneLaunch P) {
+        P.envs = h->d_envs;
+        P.n_env = h->n_env;
+        P.fields = L.fields;
+        P.args = L.args;
+        P.aligned = g.aligned;
+        P.phi = h->series_cell || h->series_env ? nullptr : h->d_phi;
+        return P;
+    };
+    // a fourth plane (retardant drops) may leave less room for the wave lists
+    const int planes = actions && L.args.drop_mode == SIM_DROP_SUPPRESS ? 4 : 3;
+    auto fitted = [&](PlaneLaunch P) {
+        while (P.threads > 512 && plane_lds_bytes(P.frame_words, planes, P.threads, P.list_cap) > h->plane_lds)
+            P.threads /= 2;
+        return P;
+    };
+    for (const PlaneLaunch& P : g.plane_whole)
+        if ((e = launch_stoch_plane(s, with_inputs(fitted(P)), states, states, h->d_t, 0u, T, actions, counts, history,
+                                    PlaneParts{})) != hipSuccess)
+            return e;
+    if (g.plane_parts.n_tiles == 0) return hipSuccess;
+    const PlaneLaunch P = with_inputs(g.plane_parts);
+    int32_t* const mark = g.d_part_work;
+    int32_t* const n_list = mark + 2 * (int64_t)P.n_tiles;
+    int32_t* const list = n_list + 4;
+    if ((e = launch_fill_i32(s, mark, 2 * (int64_t)P.n_tiles + 4, 0)) != hipSuccess) return e;
+    int32_t n = (T + kPartSteps - 1) / kPartSteps;
+    if (n % 2 && T > 1) ++n;
+    uint8_t *cur = states, *nxt = h->d_tmp;
+    for (int32_t i = 0, k = 0; i < n; ++i) {
+        const int32_t steps = (T - k + (n - i) - 1) / (n - i);
+        const int32_t here = i & 1, there = here ^ 1;
+        PlaneParts parts{};
+        parts.mark = mark + here * (int64_t)P.n_tiles;
+        parts.mark_next = mark + there * (int64_t)P.n_tiles;
+        parts.nbr = g.d_ptile_nbr;
+        parts.first = i == 0;
+        if (!actions) {  // a drop may touch a part that is on no list
+            parts.list = i == 0 ? nullptr : list + here * (int64_t)P.n_tiles;
+            parts.n_list = n_list + i % 3;
+            parts.list_next = list + there * (int64_t)P.n_tiles;
+            parts.n_next = n_list + (i + 1) % 3;
+            parts.n_clear = n_list + (i + 2) % 3;
+        }
+        e = launch_stoch_plane(s, P, cur, nxt, h->d_t, (uint32_t)k, steps,
+                               actions ? actions + (int64_t)k * h->n_env : nullptr,
+                               counts ? counts + (int64_t)k * h->n_env : nullptr, nullptr, parts);
+        if (e != hipSuccess) return e;
+        k += steps;
+        std::swap(cur, nxt);
+    }
+    if (cur != states) return launch_copy_envs(s, h->d_envs, g.d_part_envs, g.n_part_envs, states, cur);
+    return hipSuccess;
+}
+
 // Enqueue the launches of T steps of group g's envs (if T is odd the result
 // is copied back from the ping-pong buffer).  With a history buffer, step k
 // reads row k-1 (states for k = 0) and writes row k, and the last row is
@@ -443,25 +661,11 @@ hipError_t enqueue_group(sim_handle* h, PlanGroup& g, hipStream_t s, uint8_t* st
         L.args.drop_radius = drop[1];
     }
     const sim_plan& plan = g.plan;
-    const int32_t n_members = g.envs.empty() ? h->n_env : (int32_t)g.envs.size();
     uint8_t* cur = states;
     uint8_t* nxt = history ? history : h->d_tmp;
-    if (plan.resident) {
-        // all T steps in one launch, in place (one launch per step with a history)
-        if (!history)
-            return launch_stoch_resident(s, h->d_envs, h->n_env, g.d_list, n_members, L.fields, L.args, g.res,
-                                         plan.resident, states, states, h->d_t, 0u, T, actions, counts);
-        for (int32_t k = 0; k < T; ++k) {
-            e = launch_stoch_resident(s, h->d_envs, h->n_env, g.d_list, n_members, L.fields, L.args, g.res,
-                                      plan.resident, cur, nxt, h->d_t, (uint32_t)k, 1,
-                                      actions ? actions + (int64_t)k * h->n_env : nullptr,
-                                      counts ? counts + (int64_t)k * h->n_env : nullptr);
-            if (e != hipSuccess) return e;
-            cur = nxt;
-            nxt = history + (int64_t)(k + 1) * h->n_cells;
-        }
-        return copy_group(h, s, g, states, cur);
-    }
+    // (a history of envs in parts needs each state in memory between the steps)
+    if (wants_planes(plan) && has_planes(g) && !(history && g.plane_parts.n_tiles))
+        return enqueue_planes(h, g, s, L, states, actions, T, counts, history);
     const bool sparse = plan.sparse != 0;
     if (sparse) {  // nothing is known yet about how the two buffers compare
         e = launch_fill_i32(s, g.d_tile_eq, g.n_tiles, 0);
@@ -726,13 +930,26 @@ int sim_init(sim_handle** out, const sim_params* p, int32_t n_env, const sim_env
                                      h->d_den, h->d_wind, states_out);
     if (e == hipSuccess) e = launch_ignite(s, d_ign, n_ign, h->d_envs, states_out);
     if (e == hipSuccess) e = launch_copy_u8(s, h->d_init_states, states_out, n_cells);
+    // the table of edge rates, where it takes at most a quarter of the free
+    // memory (without it the steps work the rates out)
+    {
+        size_t mem_free = 0, mem_total = 0;
+        if (hipMemGetInfo(&mem_free, &mem_total) == hipSuccess && 32 * n <= mem_free / 4 &&
+            hipMalloc(&h->d_phi, 32 * n) != hipSuccess)
+            h->d_phi = nullptr;
+        (void)hipGetLastError();  // a refused allocation is not an error of this call
+    }
+    if (e == hipSuccess && h->d_phi) {
+        const StaticFields F{h->d_g, h->d_E, h->wind_cell ? h->d_wind : nullptr, n_cells, 0, nullptr, n_env};
+        e = launch_phi_table(s, h->d_envs, h->d_chunk_env, h->n_chunks, F, step_args(h), h->d_phi);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (d_ign) (void)hipFree(d_ign);
     if (e != hipSuccess) {
         fail(h, SIM_EHIP, "initialisation kernels failed: %s", hipGetErrorString(e));
         return bail(SIM_EHIP);
     }
-    if ((rc = build_tiles(h, h->all, tiles_key(h->all.plan), h->all.plan.tile_width)) != SIM_OK) return bail(rc);
+    if ((rc = ensure_group_tiles(h, h->all)) != SIM_OK) return bail(rc);
     if (hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess) {
         fail(h, SIM_EHIP, "stream creation failed");
         return bail(SIM_EHIP);

@@ -54,11 +54,11 @@ __device__ __forceinline__ float exp_c(float x)
     constexpr float kT2 = 0.5f, kT3 = (float)(1.0 / 6.0), kT4 = (float)(1.0 / 24.0);
     constexpr float kT5 = (float)(1.0 / 120.0), kT6 = (float)(1.0 / 720.0);
     constexpr float kT7 = (float)(1.0 / 5040.0);
-    if (x != x) return x;
-    if (x < -87.0f) return 0.0f;
-    if (x > 88.0f) x = 88.0f;
-    const float n = __builtin_rintf(x * kInvLn2);
-    const float r = (x - n * kLn2Head) - n * kLn2Tail;
+    // the special cases are selected at the end: no branch, so a lane's
+    // exponentials overlap with whatever else it has to do
+    const float xc = x > 88.0f ? 88.0f : x;
+    const float n = __builtin_rintf(xc * kInvLn2);
+    const float r = (xc - n * kLn2Head) - n * kLn2Tail;
     float poly = kT7;
     poly = poly * r + kT6;
     poly = poly * r + kT5;
@@ -68,7 +68,9 @@ __device__ __forceinline__ float exp_c(float x)
     poly = poly * r + 1.0f;
     poly = poly * r + 1.0f;
     const float two_n = __int_as_float(((int)n + 127) << 23);
-    return poly * two_n;
+    float y = poly * two_n;
+    y = x < -87.0f ? 0.0f : y;
+    return x != x ? x : y;
 }
 
 // arctan in fp32 for the slope-angle variant: odd; pi/2 - atan(1/x) above

@@ -38,6 +38,16 @@ __device__ __forceinline__ uint32_t compu(const uint4& v, int c)
     return c == 0 ? v.x : (c == 1 ? v.y : (c == 2 ? v.z : v.w));
 }
 
+// phi of one edge (Eq. 3): p_base g(u) exp(wind exponent + alpha_s slope) of
+// the source u in direction k of a target at elevation E_v.
+__device__ __forceinline__ float edge_rate(int k, float wexp, float g_u, float E_v, float E_u, const StepArgs& A)
+{
+    float slope = (E_v - E_u) * ((k & 1) ? A.inv_run_diag : A.inv_run_orth);
+    if (A.slope_mode) slope = atan_c(slope);  // the slope angle in radians
+    const float x = wexp + A.alpha_s * slope;
+    return (A.p_base * g_u) * exp_c(x);
+}
+
 // p_ignite of a target cell from its burning-neighbour mask (bit k: the
 // source v - D_k burns), its own fuel term and elevation, and its sources'
 // fuel, elevation and (per-cell) wind: lambda is summed in ascending
@@ -57,10 +67,7 @@ __device__ __forceinline__ float ignite_prob_of(uint32_t nbk, float g_v, float E
             wexp = wind_exponent(k, A.alpha_w1, A.alpha_w2, V_u[k], Vx_u[k], Vy_u[k]);
         else
             wexp = ew[k];
-        float slope = (E_v - E_u[k]) * ((k & 1) ? A.inv_run_diag : A.inv_run_orth);
-        if (A.slope_mode) slope = atan_c(slope);  // the slope angle in radians
-        const float x = wexp + A.alpha_s * slope;
-        lambda = lambda + (A.p_base * g_u[k]) * exp_c(x);
+        lambda = lambda + edge_rate(k, wexp, g_u[k], E_v, E_u[k], A);
     }
     if (!(lambda > 0.0f)) return 0.0f;
     const float gamma = A.alpha_gamma * g_v;
