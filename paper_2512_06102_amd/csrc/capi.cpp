@@ -138,7 +138,6 @@ struct sim_handle {
     // tiles with no fire in reach skipped (the dense plan, which streams every
     // cell's 10 bytes each step, is {4, 256, 1, 0, 0, 0})
     sim_plan plan{4, 64, 1, 1, 1, 0, 0};
-    size_t plane_lds = 0;  // the largest dynamic LDS of the bit-plane kernel
     // the whole batch under `plan`, or (when non-empty) its size classes under their own plans
     PlanGroup all;
     std::vector<PlanGroup> classes;
@@ -362,31 +361,34 @@ size_t plane_lds_limit(int device)
 // sparse front-skipping plan and the resident plan.
 bool wants_planes(const sim_plan& p) { return p.resident != 0 || (p.skip_static && p.sparse && p.temporal <= 1); }
 
-// Lanes of the workgroup that takes an env of `cells` cells.  Measured, 200
-// steps: 256 envs of 128 x 128 take 0.84 ms with 512 lanes, 1.10 ms with 256;
-// 192 envs of up to 331 x 331 1.31 ms with 1024 for the large ones, 1.56 ms
-// with 512; 1024 envs of 256 x 256 2.55 ms with 512, 4.4 ms with 1024.
-int plane_threads_for(int64_t cells)
+// Lanes of the workgroup that takes an env of `cells` cells, in a batch of
+// `per_cu` envs per compute unit.  More lanes shorten a step while workgroups
+// are few, fewer lanes waste less once they share the units.  Measured, 200
+// steps of 256 x 256: 64 envs 1.04 ms with 512 lanes, 1.33 ms with 256; 1024
+// envs 2.33 ms and 2.21 ms (4.2 ms with 1024 lanes); 256 envs of 128 x 128
+// 0.76 ms with 512 and 1.00 ms with 256; 192 envs of up to 331 x 331 1.26 ms
+// with 1024 lanes for the large ones and 1.35 ms with 512.
+int plane_threads_for(int64_t cells, int64_t per_cu)
 {
-    return cells >= 96 * 1024 ? 1024 : (cells >= 1536 ? 512 : 64);
+    if (cells >= 96 * 1024) return 1024;
+    return cells < 1536 ? 64 : (per_cu > 3 ? 256 : 512);
 }
 
 // The tiles and launches of group g's bit-plane steps.  An env is taken whole
-// where its planes fit LDS, else in parts of kPartRows x kPartCols.  Whole
-// envs are launched together when the chip holds one workgroup of each at
-// once; else by workgroup size, so that small envs share a compute unit.
-constexpr int kPartRows = 64, kPartCols = 128, kPartSteps = 16;
+// where its planes fit LDS, else in parts of kPartRows x kPartCols.
+constexpr int kPartRows = 64, kPartCols = 128, kPartSteps = 24;
 int build_planes(sim_handle* h, PlanGroup& g)
 {
     free_planes(g);
-    const size_t limit = h->plane_lds = plane_lds_limit(h->device);
+    const size_t limit = plane_lds_limit(h->device);
     int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) cus = 1;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus < 1)
+        cus = 1;
     g.plane_threads = g.plan.resident;
     if (limit == 0) return SIM_OK;
     struct Whole {
         int32_t env, threads;
-        int64_t cells;
+        size_t lds;
     };
     std::vector<Whole> whole;
     std::vector<PlaneTile> tiles, parts;
@@ -396,11 +398,11 @@ int build_planes(sim_handle* h, PlanGroup& g)
         const int32_t e = g.envs.empty() ? q : g.envs[q];
         const int H = h->envs[e].H, W = h->envs[e].W;
         const int64_t cells = (int64_t)H * W;
-        // room for four planes and the largest workgroup's lists: whether an
-        // env is whole does not depend on the call
-        if (plane_indexable(H, W) &&
-            plane_lds_bytes(plane_frame_words(H, W), 4, 512, plane_list_cap(H, W)) <= limit) {
-            whole.push_back({e, g.plan.resident ? g.plan.resident : plane_threads_for(cells), cells});
+        const int threads = g.plan.resident ? g.plan.resident : plane_threads_for(cells, n_members / cus);
+        const size_t lds =
+            plane_lds_bytes(plane_frame_words(H, W), 3, threads, plane_list_cap(H, W));
+        if (plane_indexable(H, W) && lds <= limit) {
+            whole.push_back({e, threads, lds});
             continue;
         }
         part_envs.push_back(e);
@@ -418,15 +420,22 @@ int build_planes(sim_handle* h, PlanGroup& g)
                     }
             }
     }
-    std::stable_sort(whole.begin(), whole.end(), [](const Whole& a, const Whole& b) { return a.cells > b.cells; });
-    if (!whole.empty() && whole.size() <= (size_t)cus)
-        for (Whole& w : whole) w.threads = whole[0].threads;
+    // whole envs, the largest first, into launches: one is full when the chip
+    // holds no more of its workgroups at once, and then ends before the first
+    // env of a smaller kind (less LDS, fewer lanes)
+    std::stable_sort(whole.begin(), whole.end(), [](const Whole& a, const Whole& b) { return a.lds > b.lds; });
+    int64_t room = 0;
+    size_t first_lds = 0;
     for (const Whole& w : whole) {
         const int H = h->envs[w.env].H, W = h->envs[w.env].W;
-        if (g.plane_whole.empty() || g.plane_whole.back().threads != w.threads) {
+        const bool fits_on = !g.plane_whole.empty() && (g.plane_whole.back().n_tiles < room ||
+                                                        w.lds * 4 > 3 * first_lds);
+        if (!fits_on) {
             PlaneLaunch L{};
             L.threads = w.threads;
             g.plane_whole.push_back(L);
+            first_lds = w.lds;
+            room = (int64_t)cus * std::max<int64_t>(1, std::min<int64_t>((int64_t)(limit / w.lds), 2048 / w.threads));
         }
         PlaneLaunch& L = g.plane_whole.back();
         L.n_tiles += 1;
@@ -601,15 +610,8 @@ hipError_t enqueue_planes(sim_handle* h, PlanGroup& g, hipStream_t s, const Step
         P.phi = h->series_cell || h->series_env ? nullptr : h->d_phi;
         return P;
     };
-    // a fourth plane (retardant drops) may leave less room for the wave lists
-    const int planes = actions && L.args.drop_mode == SIM_DROP_SUPPRESS ? 4 : 3;
-    auto fitted = [&](PlaneLaunch P) {
-        while (P.threads > 512 && plane_lds_bytes(P.frame_words, planes, P.threads, P.list_cap) > h->plane_lds)
-            P.threads /= 2;
-        return P;
-    };
     for (const PlaneLaunch& P : g.plane_whole)
-        if ((e = launch_stoch_plane(s, with_inputs(fitted(P)), states, states, h->d_t, 0u, T, actions, counts, history,
+        if ((e = launch_stoch_plane(s, with_inputs(P), states, states, h->d_t, 0u, T, actions, counts, history,
                                     PlaneParts{})) != hipSuccess)
             return e;
     if (g.plane_parts.n_tiles == 0) return hipSuccess;

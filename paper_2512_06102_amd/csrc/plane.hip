@@ -14,24 +14,28 @@
 //     (B of the 3 x 3 neighbourhood), need = front or B.  The 4-cell groups
 //     with a needed cell are listed in LDS by the whole workgroup; B of the
 //     next step is cleared.
-//  2. The lanes share the list: one Philox block per group, the burning
-//     cells' survival straight into the next B, and the front cells packed
-//     into the wave's own short list, 64 of which are evaluated at a time.
-//     A front cell's rates come from the table phi[cell][8] (32 bytes, the
-//     same for every step under static wind), so its probability costs two
-//     16-byte loads, eight masked adds and one exponential.
+//  2. The lanes share the list, one group each: a Philox block, the burning
+//     cells' survival and the front cells' ignitions, and the group's bits of
+//     the next B.  A front cell's rates come from the table phi[cell][8] (32
+//     bytes, the same for every step under static wind), so its probability
+//     costs two 16-byte loads (on their way during the Philox block), eight
+//     masked adds and one exponential.  Under a wind series, or without the
+//     table, the front cells go to the wave's own short list, 64 of which are
+//     evaluated at a time.
 // Two barriers per step (three with a drop).  No state goes to memory between
 // the steps of a launch.
 //
 // What bounds it: the chain of a step (LDS round trips, one Philox block, one
-// table load, one exponential, the barriers; 4000 to 10000 cycles), not
+// table load, one exponential, the barriers; 4000 to 10000 cycles at one
+// workgroup per compute unit) and the instructions of the lanes that have
+// little to do (VALU issue about half of the chip's rate at 1024 envs), not
 // memory.  Measured against one launch per step over 64-lane tiles (the other
-// step kernel): 1024 envs of 256 x 256, 200 steps, 11.5 -> 3.03 ms; 1024 envs
-// of 64 to 512 squared with a drop per step, 300 steps, 18.1 -> 8.7 ms; 8 envs
-// of 2048 x 2048 with per-cell wind, 1000 steps, 26.9 -> 6.8 ms (parts of 64 x
-// 128 with 16 steps of halo; 8.3 ms with 128 x 128, 8.6 ms with 8 steps).
+// step kernel): 1024 envs of 256 x 256, 200 steps, 11.5 -> 2.3 ms; 1024 envs
+// of 64 to 512 squared with a drop per step, 300 steps, 18.1 -> 6.6 ms; 8 envs
+// of 2048 x 2048 with per-cell wind, 1000 steps, 26.9 -> 6.6 ms (parts of 64 x
+// 128 with 24 steps of halo; 7.2 ms with 12 steps, 8.3 ms with 128 x 128).
 // Against one workgroup per env with byte states and the exponentials worked
-// out per step: 64 envs of 64 x 64, 200 steps, 491 -> 304 us.
+// out per step: 64 envs of 64 x 64, 200 steps, 491 -> 255 us.
 //
 // With a halo the region is the tile and `steps` rows and 32 columns around
 // it; a step works out the cells that the tile's last step still depends on.
@@ -64,10 +68,13 @@ __device__ __forceinline__ void wave_sync()
 
 // Workgroup barrier that orders LDS only: stores to memory stay in flight
 // (__syncthreads waits for them, about 1000 cycles with a count stored in the
-// step before).
+// step before).  The wait for the wave's own LDS operations is explicit: a
+// fence on local memory alone emits none, and an add without a result was
+// still on its way when another wave read the sum behind the barrier.
 __device__ __forceinline__ void lds_barrier()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
@@ -77,19 +84,15 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Inclusive prefix sum over the wave (every lane active).
-__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x)
+// Adds x to a word of LDS that every lane names alike, and returns what was
+// there.  The address is hidden from the compiler, which would otherwise
+// gather the lanes' values in a scalar loop (2500 cycles for 64 lanes, about
+// 200 for the conflict in LDS).
+__device__ __forceinline__ uint32_t lds_add(uint32_t* p, uint32_t x)
 {
-    auto add = [&](auto ctrl, auto rows) {
-        x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
-    };
-    add(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});  // row_shr:1
-    add(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});  // row_shr:2
-    add(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});  // row_shr:4
-    add(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});  // row_shr:8
-    add(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});  // row_bcast:15
-    add(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});  // row_bcast:31
-    return x;
+    uint32_t i = 0;
+    asm volatile("" : "+v"(i));
+    return atomicAdd(p + i, x);
 }
 
 // Bits of a 32-cell word at column 32 w that lie in columns [lo, hi).
@@ -144,8 +147,13 @@ struct PlaneArgs {
     uint32_t keep_below;  // a BURNING cell stays when its 24-bit draw is below this
 };
 
+// Waves per SIMD the kernel is compiled for: with the table 80 VGPRs fit
+// without a spill (64 spill, and 1024 envs of 256 x 256 run 4% slower).
+constexpr int plane_waves_per_eu(int rates) { return rates == kRatesTable ? 6 : 4; }
+
 template <int NT, bool ALIGNED, int RATES, bool HALO>
-__global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_per_eu(RATES)))) void stoch_plane_kernel(
+    PlaneArgs K)
 {
     constexpr int NW = NT / 64;
     extern __shared__ uint4 lds_dyn[];
@@ -216,15 +224,17 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
         }
     }
 
-    uint2* const wl = reinterpret_cast<uint2*>(lds_dyn) + wv * kPlaneWaveList;  // this wave's front cells
-    uint32_t* const pF = reinterpret_cast<uint32_t*>(reinterpret_cast<uint2*>(lds_dyn) + NW * kPlaneWaveList);
+    // the wave's front cells (without the table), then the planes
+    uint2* const wl = reinterpret_cast<uint2*>(lds_dyn) + wv * kPlaneWaveList;
+    uint32_t* const pF = reinterpret_cast<uint32_t*>(reinterpret_cast<uint2*>(lds_dyn) +
+                                                     (RATES == kRatesTable ? 0 : NW * kPlaneWaveList));
     uint32_t* cur = pF + K.frame_words;
     uint32_t* nxt = cur + K.frame_words;
     uint32_t* const pU = nxt + K.frame_words;
-    uint16_t* const list = reinterpret_cast<uint16_t*>(pF + (3 + K.has_u) * K.frame_words);
+    uint16_t* const list = reinterpret_cast<uint16_t*>(pF + (3 + (HALO ? K.has_u : 0)) * K.frame_words);
 
     // -- planes cleared (frames included), then filled from the source bytes
-    for (int i = tid; i < (3 + K.has_u) * K.frame_words; i += NT) pF[i] = 0u;
+    for (int i = tid; i < (3 + (HALO ? K.has_u : 0)) * K.frame_words; i += NT) pF[i] = 0u;
     if (tid < 2) {
         s_n[tid] = 0u;
         s_all[tid] = 0u;
@@ -255,7 +265,7 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
                     const int at = (r + 1) * S + 1 + (g >> 3), sh = 4 * (g & 7);
                     if (f) atomicOr(&pF[at], f << sh);
                     if (bu) atomicOr(&cur[at], bu << sh);
-                    if (K.has_u) {
+                    if (HALO && K.has_u) {
                         uint32_t u = ~pack4((w | (w >> 1)) & 0x01010101u) & 0xFu;
                         if (!ALIGNED && col + 3 >= W) u &= (1u << (W - col)) - 1u;
                         if (u) atomicOr(&pU[at], u << sh);
@@ -270,7 +280,7 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
         const int at = (r + 1) * S + 1 + (g >> 3), sh = 4 * (g & 7);
         const uint32_t f = pF[at] >> sh, bu = cur[at] >> sh;
         uint32_t z = spread4(~(f | bu));
-        if (K.has_u) {
+        if (HALO && K.has_u) {
             z &= ~spread4(pU[at] >> sh);
         } else if (z) {
             const int col = p0 + 4 * g;
@@ -374,13 +384,24 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
                         const int w = wa + q % nw, at = (ra + q / nw + 1) * S + 1 + w;
                         const uint32_t m = column_mask(w, ca, cb + 1);
                         if (K.A.drop_mode == 0) {
-                            pU[at] |= (pF[at] | cur[at]) & m;
+                            uint32_t gone = (pF[at] | cur[at]) & m;
+                            if (HALO) {
+                                pU[at] |= gone;
+                            } else {
+                                // a whole env is stepped in place: its bytes say
+                                // which cells are UNBURNABLE
+                                uint8_t* o = K.dst + base + (uint32_t)((q0 + ra + q / nw) * W + p0 + 32 * w);
+                                for (; gone; gone &= gone - 1) o[__ffs(gone) - 1] = kUnburnable;
+                            }
                             pF[at] &= ~m;
                         }
                         cur[at] &= ~m;
                     }
                 }
-                lds_barrier();
+                if (K.history)
+                    __syncthreads();  // the next history row reads the dropped bytes
+                else
+                    lds_barrier();
             }
         }
         if (quiet) continue;
@@ -388,71 +409,54 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
         // -- 1. scan: the cells that this step has to work out
         const int left = K.steps - 1 - s;
         const int lo = HALO ? max(tr0 - left, 0) : 0, hi = HALO ? min(tr1 + left, RH) : RH;
-        // the wave's needed words: needed groups in bits 4 b, the lane in bits
-        // 1-3 and 5-7, its row in bits 9-10
-        uint32_t* const ww = reinterpret_cast<uint32_t*>(wl);
-        const uint32_t lane_bits = ((lane & 7) << 1) | ((lane >> 3) << 5);
         // strips of one row have a scan of their own: it reads 3 rows, not 6
         auto scan = [&](auto rows_at_once) {
             constexpr int ROWS = decltype(rows_at_once)::value;
             for (int w0 = 0; w0 < WW; w0 += w_step)
                 for (int j = 0; j < per; j += ROWS) {
-                    // a lane's word column and rows [ra, rb); lanes beyond the last
-                    // strip or column take part with no rows
-                    const int cw = w0 + my_w, cwc = min(cw, WW - 1);
-                    const int ra = lo + my_strip * per + j;
-                    const int rb = my_strip < n_strips && cw < WW ? min(lo + (my_strip + 1) * per, hi) : 0;
-                    if (!__any(ra < rb)) continue;
-                    uint32_t m[ROWS + 2], h[ROWS + 2], f[ROWS];
-                    // (the frame has kScanRows - 1 rows to spare below)
-                    const int at0 = min(ra, RH) * S + 1 + cwc;  // row ra - 1
-#pragma unroll
-                    for (int q = 0; q < ROWS + 2; ++q) {
-                        const uint32_t* p = cur + at0 + q * S;
+                    // a lane's word column and rows ra, ra + n_strips, ...: a
+                    // fire's rows fall to different lanes and waves (with
+                    // neighbouring rows to a lane, one wave lists most of the
+                    // groups while the others wait, 2900 of 11500 cycles)
+                    const int cw = w0 + my_w, ra = lo + my_strip + j * n_strips;
+                    if (my_strip >= n_strips || cw >= WW || ra >= hi) continue;
+                    uint32_t m[ROWS], h[ROWS], f[ROWS];
+                    int at[ROWS];
+                    auto reach = [&](const uint32_t* p, uint32_t& mid) {
                         const uint32_t l = p[-1], r = p[1];
-                        m[q] = p[0];
+                        mid = p[0];
                         // the row's burning cells and their left and right neighbours
-                        h[q] = m[q] | __builtin_amdgcn_alignbit(m[q], l, 31) | __builtin_amdgcn_alignbit(r, m[q], 1);
-                        if (q >= 1 && q <= ROWS) f[q - 1] = pF[at0 + q * S];
-                    }
-                    const uint32_t mask = HALO ? column_mask(cw, tc0 - left, tc1 + left) : ~0u;
-                    const uint32_t id0 = ((uint32_t)ra << gshift) | (uint32_t)(8 * cw);
-                    uint32_t cnt = 0;
-                    int n_words = 0;  // wave-uniform
+                        return mid | __builtin_amdgcn_alignbit(mid, l, 31) | __builtin_amdgcn_alignbit(r, mid, 1);
+                    };
 #pragma unroll
                     for (int q = 0; q < ROWS; ++q) {
-                        const bool in = ra + q < rb;
-                        uint32_t need = (f[q] & (h[q] | h[q + 1] | h[q + 2])) | m[q + 1];
+                        at[q] = (min(ra + q * n_strips, RH - 1) + 1) * S + 1 + cw;
+                        const uint32_t* p = cur + at[q];
+                        uint32_t above, below;
+                        h[q] = reach(p - S, above) | reach(p, m[q]) | reach(p + S, below);
+                        f[q] = pF[at[q]];
+                    }
+                    const uint32_t mask = HALO ? column_mask(cw, tc0 - left, tc1 + left) : ~0u;
+                    uint32_t todo = 0;  // bit 4 b + q: group b of row q has a needed cell
+#pragma unroll
+                    for (int q = 0; q < ROWS; ++q) {
+                        const bool in = ra + q * n_strips < hi;
+                        uint32_t need = (f[q] & h[q]) | m[q];
                         if (HALO) need &= mask;
-                        need = in ? need : 0u;
-                        if (in) nxt[at0 + (q + 1) * S] = 0u;
-                        const uint64_t any = __ballot(need != 0u);
-                        uint32_t nz = need | (need >> 1);  // bit 4 b: group b has a needed cell
+                        if (in) nxt[at[q]] = 0u;
+                        uint32_t nz = need | (need >> 1);
                         nz = (nz | (nz >> 2)) & 0x11111111u;
-                        cnt += (uint32_t)__popc(nz);
-                        if (need) ww[n_words + lanes_below(any)] = nz | lane_bits | ((uint32_t)q << 9);
-                        n_words += __popcll(any);
+                        todo |= (in ? nz : 0u) << q;
                     }
-                    if (n_words == 0) continue;
-                    const uint32_t upto = wave_inclusive_sum(cnt);
-                    uint32_t first = 0;
-                    if (lane == 63) first = atomicAdd(&s_n[s & 1], upto);
-                    wave_sync();
-                    uint32_t slot = (uint32_t)__builtin_amdgcn_readlane((int)first, 63);
-                    // eight words at a time: lane 8 i + b takes group b of word i
-                    for (int e0 = 0; e0 < n_words; e0 += 8) {
-                        const int i = e0 + (lane >> 3);
-                        const uint32_t e = ww[min(i, n_words - 1)];
-                        const bool is = i < n_words && ((e >> (4 * (lane & 7))) & 1u);
-                        const uint32_t from = ((e >> 1) & 7u) | ((e >> 2) & 0x38u);
-                        const uint32_t id = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(from << 2), (int)id0) +
-                                            (((e >> 9) & 3u) << gshift);
-                        const uint64_t any = __ballot(is);
-                        const uint32_t at_slot = slot + lanes_below(any);
-                        if (is && at_slot < (uint32_t)K.list_cap) list[at_slot] = (uint16_t)(id | (lane & 7));
-                        slot += (uint32_t)__popcll(any);
+                    if (todo == 0u) continue;
+                    uint32_t slot = lds_add(&s_n[s & 1], (uint32_t)__popc(todo));
+                    const uint32_t id0 = ((uint32_t)ra << gshift) | (uint32_t)(8 * cw);
+                    const uint32_t id_row = (uint32_t)n_strips << gshift;
+                    for (; todo; todo &= todo - 1) {
+                        const uint32_t bit = (uint32_t)__ffs(todo) - 1u;
+                        if (slot < (uint32_t)K.list_cap) list[slot] = (uint16_t)(id0 + (bit & 3u) * id_row + (bit >> 2));
+                        ++slot;
                     }
-                    wave_sync();
                 }
         };
         if (!small) {
@@ -476,7 +480,7 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
         uint32_t n_all = 0, n_tile = 0;  // this lane's BURNING cells
         int wn = 0;                      // cells in the wave's list (wave-uniform)
         auto inside = [&](int r, int c) { return r >= tr0 && r < tr1 && c >= tc0 && c < tc1; };
-        // evaluate the last n (<= 64) cells of the wave's list
+        // without the table: evaluate the last n (<= 64) cells of the wave's list
         auto eval = [&](int n) {
             wave_sync();
             if (lane < n) {
@@ -484,18 +488,8 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
                 const int r = e.x & 0x7FFF, c = (e.x >> 15) & 0x7FFF;
                 const uint32_t win = (e.x >> 30) | ((e.y >> 24) << 2);
                 const int64_t v = base + (uint32_t)((q0 + r) * W + p0 + c);
-                float p;
-                if constexpr (RATES == kRatesTable) {
-                    const float4 pa = K.phi[2 * v], pb = K.phi[2 * v + 1];
-                    float gv = K.F.g[v];
-                    asm volatile("" : "+v"(gv));  // loaded with the rates, not behind a branch on their sum
-                    const float lambda = rate_sum(pa, pb, win);
-                    const float q = 1.0f - exp_c(-((K.A.alpha_gamma * gv) * lambda));
-                    p = lambda > 0.0f ? q : 0.0f;
-                } else {
-                    const uint32_t nbk = direction_mask(win & 7u, (win >> 3) & 7u, (win >> 6) & 7u, 0);
-                    p = ignite_prob<RATES == kRatesCellWind>(nbk, v, W, F, K.A, ew);
-                }
+                const uint32_t nbk = direction_mask(win & 7u, (win >> 3) & 7u, (win >> 6) & 7u, 0);
+                const float p = ignite_prob<RATES == kRatesCellWind>(nbk, v, W, F, K.A, ew);
                 if (word_to_uniform(e.y << 8) < p) {
                     const int at = (r + 1) * S + 1 + (c >> 5);
                     atomicOr(&nxt[at], 1u << (c & 31));
@@ -508,9 +502,9 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
             wave_sync();
         };
         int rd = lo + dense_r, gd = dense_g;
+        // a list is dealt out entry by entry: a short one keeps every wave busy
         const int n_rounds = (n_work + NT - 1) / NT;
         for (int k = 0; k < n_rounds; ++k) {
-            // a list is dealt out entry by entry: a short one keeps every wave busy
             bool on;
             int r, g;
             if (dense) {
@@ -524,7 +518,7 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
                     ++rd;
                 }
             } else {
-                const int i = k * NT + wv + NW * lane;
+                const int i = NW * (64 * k + lane) + wv;
                 on = i < n_work;
                 const uint32_t id = on ? list[i] : 0u;
                 r = (int)(id >> gshift);
@@ -545,51 +539,88 @@ __global__ __launch_bounds__(NT) void stoch_plane_kernel(PlaneArgs K)
             const uint32_t front = on ? flam & (ud | (ud >> 1) | (ud >> 2) | md6 | (md6 >> 2)) & 0xFu : 0u;
             const uint32_t burn = on ? (md6 >> 1) & 0xFu : 0u;
             const bool last = k == n_rounds - 1;
-            const bool any = __any((burn | front) != 0u);
-            if (!any && !(last && wn > 0)) continue;
             uint4 w = make_uint4(0u, 0u, 0u, 0u);
             if (burn | front) {
-                w = group_words<ALIGNED>((int64_t)((q0 + r) * W + p0 + col), t, ed.env_id, key);
-                const uint32_t keep = burn & ((w.x >> 8 < K.keep_below ? 1u : 0u) | (w.y >> 8 < K.keep_below ? 2u : 0u) |
-                                              (w.z >> 8 < K.keep_below ? 4u : 0u) | (w.w >> 8 < K.keep_below ? 8u : 0u));
-                if (keep) atomicOr(&nxt[at], keep << sh);
-                n_all += (uint32_t)__popc(keep);
-                if (HALO && inside(r, col)) n_tile += (uint32_t)__popc(keep);  // tile edges are on group edges
+                const int n0 = (q0 + r) * W + p0 + col;  // the group's first cell
+                uint32_t next = 0;                       // its cells that burn after the step
+                float4 ra[4], rb[4];
+                float gv[4];
+                if constexpr (RATES == kRatesTable) {
+                    // the front cells' rates are on their way while the draws are
+                    // worked out (those of the other cells are left: at 1024 envs
+                    // of 256 x 256 whole 128-byte groups take 3.3 ms for 2.5)
+                    const float4* ph = K.phi + 2 * (base + n0);
+                    const float* pg = K.F.g + base + n0;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        ra[c] = rb[c] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                        gv[c] = 0.0f;
+                        if ((front >> c) & 1u) {
+                            ra[c] = ph[2 * c];
+                            rb[c] = ph[2 * c + 1];
+                            gv[c] = pg[c];
+                        }
+                    }
+                }
+                w = group_words<ALIGNED>((int64_t)n0, t, ed.env_id, key);
+                next = burn & ((w.x >> 8 < K.keep_below ? 1u : 0u) | (w.y >> 8 < K.keep_below ? 2u : 0u) |
+                               (w.z >> 8 < K.keep_below ? 4u : 0u) | (w.w >> 8 < K.keep_below ? 8u : 0u));
+                if constexpr (RATES == kRatesTable) {
+                    uint32_t ign = 0;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t win = ((up6 >> c) & 7u) | (((md6 >> c) & 7u) << 3) | (((dn6 >> c) & 7u) << 6);
+                        const float lambda = rate_sum(ra[c], rb[c], win);
+                        const float q = 1.0f - exp_c(-((K.A.alpha_gamma * gv[c]) * lambda));
+                        const float pr = lambda > 0.0f ? q : 0.0f;
+                        ign |= word_to_uniform(compu(w, c)) < pr ? 1u << c : 0u;
+                    }
+                    ign &= front;
+                    next |= ign;
+                    if (ign) atomicAnd(&pF[at], ~(ign << sh));
+                }
+                if (next) atomicOr(&nxt[at], next << sh);
+                n_all += (uint32_t)__popc(next);
+                if (HALO && inside(r, col)) n_tile += (uint32_t)__popc(next);  // tile edges are on group edges
             }
-            // the front cells into the wave's list, two of the group at a time
-            const uint32_t rc = (uint32_t)r | ((uint32_t)col << 15);
+            if constexpr (RATES != kRatesTable) {
+                // the front cells into the wave's list, two of the group at a time
+                if (!__any(front != 0u) && !(last && wn > 0)) continue;
+                const uint32_t rc = (uint32_t)r | ((uint32_t)col << 15);
 #pragma unroll 1
-            for (int h = 0; h < 2; ++h) {
-                const uint32_t fr = front >> (2 * h);
-                const uint64_t m0 = __ballot((fr & 1u) != 0u), m1 = __ballot((fr & 2u) != 0u);
-                const int n0 = __popcll(m0);
-                const uint32_t w9 = ((up6 >> (2 * h)) & 15u) | (((md6 >> (2 * h)) & 15u) << 8) | (((dn6 >> (2 * h)) & 15u) << 16);
-                auto entry = [&](int c, uint32_t word) {
-                    const uint32_t x = w9 >> c;
-                    const uint32_t win = (x & 7u) | ((x >> 5) & 0x38u) | ((x >> 10) & 0x1C0u);
-                    return make_uint2((rc + ((uint32_t)(2 * h + c) << 15)) | (win << 30), (word >> 8) | ((win >> 2) << 24));
-                };
-                if (fr & 1u) wl[wn + lanes_below(m0)] = entry(0, h ? w.z : w.x);
-                if (fr & 2u) wl[wn + n0 + lanes_below(m1)] = entry(1, h ? w.w : w.y);
-                wn += n0 + __popcll(m1);
-                const int full = last && h ? 1 : 64;
-                while (wn >= full) eval(min(wn, 64));
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t fr = front >> (2 * h);
+                    const uint64_t m0 = __ballot((fr & 1u) != 0u), m1 = __ballot((fr & 2u) != 0u);
+                    const int n0 = __popcll(m0);
+                    const uint32_t w9 = ((up6 >> (2 * h)) & 15u) | (((md6 >> (2 * h)) & 15u) << 8) |
+                                        (((dn6 >> (2 * h)) & 15u) << 16);
+                    auto entry = [&](int c, uint32_t word) {
+                        const uint32_t x = w9 >> c;
+                        const uint32_t win = (x & 7u) | ((x >> 5) & 0x38u) | ((x >> 10) & 0x1C0u);
+                        return make_uint2((rc + ((uint32_t)(2 * h + c) << 15)) | (win << 30),
+                                          (word >> 8) | ((win >> 2) << 24));
+                    };
+                    if (fr & 1u) wl[wn + lanes_below(m0)] = entry(0, h ? w.z : w.x);
+                    if (fr & 2u) wl[wn + n0 + lanes_below(m1)] = entry(1, h ? w.w : w.y);
+                    wn += n0 + __popcll(m1);
+                    const int full = last && h ? 1 : 64;
+                    while (wn >= full) eval(min(wn, 64));
+                }
             }
         }
-        if (__any(n_all != 0u)) {
-            n_all = wave_inclusive_sum(n_all);
-            if (HALO) n_tile = wave_inclusive_sum(n_tile);
-            if (lane == 63) {
-                atomicAdd(&s_all[s & 1], n_all);
-                atomicAdd(&s_tile[kc], HALO ? n_tile : n_all);
-            }
+        if (n_all) {
+            lds_add(&s_all[s & 1], n_all);
+            if (!HALO || n_tile) lds_add(&s_tile[kc], HALO ? n_tile : n_all);
         }
         uint32_t* tmp = cur;
         cur = nxt;
         nxt = tmp;
     }
 
-    lds_barrier();
+    if (!HALO && K.actions)
+        __syncthreads();  // the dropped bytes are in memory
+    else
+        lds_barrier();
     if (!stopped && K.history) store_tile(K.history + (int64_t)(K.steps - 1) * K.F.n_cells);
     if (HALO && tid < 9) {
         // the next launch runs this part and its neighbours if it still burns,
@@ -723,7 +754,7 @@ hipError_t launch_stoch_plane(hipStream_t s, const PlaneLaunch& L, const uint8_t
     K.n_tiles = L.n_tiles;
     K.frame_words = L.frame_words;
     K.list_cap = L.list_cap;
-    K.has_u = actions && L.args.drop_mode == 0 ? 1 : 0;
+    K.has_u = L.halo && actions && L.args.drop_mode == 0 ? 1 : 0;
     K.envs = L.envs;
     K.n_env = L.n_env;
     K.F = L.fields;
@@ -739,7 +770,7 @@ hipError_t launch_stoch_plane(hipStream_t s, const PlaneLaunch& L, const uint8_t
     K.history = history;
     K.parts = parts;
     K.keep_below = keep_threshold(L.args.p_continue);
-    const size_t lds = plane_lds_bytes(L.frame_words, 3 + K.has_u, L.threads, L.list_cap);
+    const size_t lds = plane_lds_bytes(L.frame_words, 3 + K.has_u, K.phi ? 0 : L.threads, L.list_cap);
     const int rates = K.phi ? kRatesTable : (K.F.wind ? kRatesCellWind : kRatesEnvWind);
     return with_kernel(L.threads, L.halo != 0, L.aligned, rates, [&](auto* kernel) {
         hipLaunchKernelGGL(kernel, dim3(K.n_tiles), dim3(L.threads), lds, s, K);

@@ -50,6 +50,7 @@ inline int32_t plane_list_cap(int64_t rows, int64_t cols)
     const int64_t groups = rows * ((cols + 3) / 4);
     return (int32_t)std::min<int64_t>(4096, std::max<int64_t>(256, ((groups / 8 + 63) / 64) * 64));
 }
+// threads: 0 for the launches that read the table (they keep no wave lists)
 inline size_t plane_lds_bytes(int64_t frame_words, int planes, int threads, int32_t list_cap)
 {
     return 8 * (size_t)kPlaneWaveList * (size_t)(threads / 64) + 4 * (size_t)planes * (size_t)frame_words +

@@ -54,9 +54,9 @@ def test_word_edges(sizes, mode):
 @pytest.mark.parametrize("mode,splits", [(None, ()), (None, (1, 16)), (0, (17,)), (1, ())])
 @pytest.mark.parametrize("size", [(700, 640), (130, 4100), (601, 603)])
 def test_parts_with_halo(size, mode, splits):
-    """Envs too large for one workgroup: parts step 16 at a time with a halo."""
+    """Envs too large for one workgroup: parts step 24 at a time with a halo."""
     batch = firegen.landscape_batch(82, [size, (65, 129)], ign_range=(40, 40))
-    _run(batch, firegen.Params(p_base=1.0, p_continue=0.7, veg=_veg(82)), 37, mode, splits=splits)
+    _run(batch, firegen.Params(p_base=1.0, p_continue=0.7, veg=_veg(82)), 60, mode, splits=splits)
 
 
 @pytest.mark.parametrize("sizes", [[(128, 128)], [(90, 61), (61, 90)], [(700, 660)]])
