@@ -862,8 +862,9 @@ int sim_init(sim_handle** out, const sim_params* p, int32_t n_env, const sim_env
         if (v.W % 4 != 0 || v.offset % 4 != 0) h->aligned = false;
     if (h->wind_cell && n_cells % 4 != 0) h->aligned = false;
     if (h->aligned) {
-        int64_t max_cells = 0, max_frame = 0;
+        int64_t max_cells = 0, max_frame = 0, max_plane = 0;
         for (const sim_env& v : h->envs) {
+            max_plane = std::max<int64_t>(max_plane, ((int64_t)v.H + 2) * ((v.W + 31) / 32 + 1) + 1);
             max_cells = std::max<int64_t>(max_cells, (int64_t)v.H * v.W);
             max_frame = std::max<int64_t>(max_frame, ((int64_t)v.H + 2) * (v.W / 4 + 2));
         }
@@ -871,6 +872,7 @@ int sim_init(sim_handle** out, const sim_params* p, int32_t n_env, const sim_env
         if (max_cells <= 65536 && max_frame <= (int64_t)kRlFusedMaxLds) {
             rs.frame_cap = (int32_t)((max_frame + 3) & ~3);
             rs.cell_cap = (int32_t)max_cells;
+            rs.plane_words = (int32_t)max_plane;
             rs.fits = rl_fused_lds_bytes(rs) <= kRlFusedMaxLds;
         }
     }
@@ -1092,7 +1094,8 @@ int sim_rl_step(sim_handle* h, const sim_rl_config* cfg, uint8_t* states, sim_rl
         StepLaunch L = step_launch(h, h->all);
         L.args.drop_mode = SIM_DROP_WATER;
         L.args.drop_radius = cfg->drop_radius;
-        HIP_OR_FAIL(h, launch_rl_step_fused(s, h->d_envs, h->n_env, L.fields, L.args, h->rl_shape, states, ag,
+        HIP_OR_FAIL(h, launch_rl_step_fused(s, h->d_envs, h->n_env, L.fields, L.args, h->rl_shape,
+                                            h->series_cell || h->series_env ? nullptr : h->d_phi, states, ag,
                                             actions, rl_dev(cfg), (uint32_t)h->t, obs, reward, done));
         h->t += 1;
         return SIM_OK;

@@ -39,6 +39,7 @@
 // exponential (relative error ~1e-6 for |x| < 20), with q from its Taylor
 // series below y = 1/16 so that small rates keep their relative accuracy.
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "devmath.hpp"
@@ -90,12 +91,15 @@ struct Veg11 {
 __device__ __forceinline__ float hexp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 
 // 1 - e^{-y} for y >= 0: Taylor series through y^5 below 1/16 (relative
-// error < 2e-9 there), 1 - e^{-y} above (where it is at least 0.06).
+// error < 2e-9 there), 1 - e^{-y} above (where it is at least 0.06).  Both are
+// computed: a select, not a divergent branch.
 __device__ __forceinline__ float one_minus_exp_neg(float y)
 {
-    if (y < 0.0625f)
-        return y * (1.0f - y * (0.5f - y * ((float)(1.0 / 6.0) - y * ((float)(1.0 / 24.0) - y * (float)(1.0 / 120.0)))));
-    return 1.0f - hexp(-y);
+    const float qs = y * (1.0f - y * (0.5f - y * ((float)(1.0 / 6.0) - y * ((float)(1.0 / 24.0) - y * (float)(1.0 / 120.0)))));
+    float ql = 1.0f - hexp(-y);
+    float qt = qs;
+    asm volatile("" : "+v"(ql), "+v"(qt));
+    return y < 0.0625f ? qt : ql;
 }
 
 // q = 1 - e^{-y} as above and the survival e^{-y}: 1 - q below y = 1/16
@@ -111,6 +115,39 @@ __device__ __forceinline__ float2 q_and_survival(float y)
     return y < 0.0625f ? make_float2(qt, 1.0f - qt) : make_float2(1.0f - el, el);
 }
 
+
+// e^{-z} and 1 - e^{-z} in fp64 from one series: z = n ln 2 + r, |r| <= ln 2 / 2
+// (ln 2 split so that n times its head is exact for |n| < 2^20), p = e^{-r} - 1
+// by its Taylor series through r^14 (truncation below 1e-18), then
+// e^{-z} = 2^{-n} (1 + p) and 1 - e^{-z} = (1 - 2^{-n}) - 2^{-n} p, which keeps
+// its relative accuracy for small z (n = 0).
+struct SurvivalPair {
+    double surv, p;
+};
+__device__ __forceinline__ SurvivalPair survival_pair(double z)
+{
+    constexpr double kLn2Head = 0.693147180369123816490, kLn2Tail = 1.90821492927058770002e-10;
+    z = z > 800.0 ? 800.0 : z;  // 2^-1154 is 0; a NaN stays
+    const double n = __builtin_rint(z * 1.44269504088896340736);
+    const double x = fma(n, kLn2Tail, fma(n, kLn2Head, -z));  // -r
+    double c = 1.0 / 87178291200.0;
+    c = fma(c, x, 1.0 / 6227020800.0);
+    c = fma(c, x, 1.0 / 479001600.0);
+    c = fma(c, x, 1.0 / 39916800.0);
+    c = fma(c, x, 1.0 / 3628800.0);
+    c = fma(c, x, 1.0 / 362880.0);
+    c = fma(c, x, 1.0 / 40320.0);
+    c = fma(c, x, 1.0 / 5040.0);
+    c = fma(c, x, 1.0 / 720.0);
+    c = fma(c, x, 1.0 / 120.0);
+    c = fma(c, x, 1.0 / 24.0);
+    c = fma(c, x, 1.0 / 6.0);
+    c = fma(c, x, 0.5);
+    c = fma(c, x, 1.0);
+    const double p = c * x;
+    const double two = __builtin_ldexp(1.0, -(int)n);
+    return SurvivalPair{fma(two, p, two), fma(-two, p, 1.0 - two)};
+}
 
 __global__ __launch_bounds__(256) void relaxed_init_kernel(const uint8_t* __restrict__ st, int64_t n,
                                                            double* __restrict__ U, double* __restrict__ B)
@@ -186,8 +223,9 @@ __device__ __forceinline__ float source_wind(int k, const float* ew, const float
 // land-cover class and density of the foreign cell.  No atomics: Bbar, Ubar
 // and the gradient are the same bits on every run.
 constexpr int AW = kAdjW, AR = kAdjR;
-constexpr int kFwdSplit = 4;  // row bands (waves) per tile in the forward
-static_assert(AR % kFwdSplit == 0, "forward row bands");
+// The reach data of a workspace: [0] the states were written sparsely, from
+// [kReachHead] on the envs' integral images.
+constexpr int kReachHead = 4;
 constexpr int kXTop = 0, kXBot = AW, kXLeft = 2 * AW, kXRight = 2 * AW + AR + 2;
 static_assert(kXRight + AR + 2 <= kXTile, "exchange record");
 
@@ -303,14 +341,31 @@ __device__ __forceinline__ AdjCell right_of(const AdjCell& x, const AdjCell& gho
     return r;
 }
 
+// A row of sources as a lane sees it: its own column and its neighbours.  The
+// walk shifts each row once, when it enters the window.
+struct AdjRow {
+    AdjCell X, L, R;
+};
+template <bool WC>
+__device__ __forceinline__ AdjRow make_row(const AdjCell& x, const AdjCell& ghost)
+{
+    return AdjRow{x, left_of<WC>(x, ghost), right_of<WC>(x, ghost)};
+}
+
 // Running sums of one source cell: c into Bbar, d into the fuel adjoint.
 struct CD {
     double c, d;
 };
 
+// The sums of one source row: of the lane's own column, and of the columns to
+// its left and right.  The terms of three target rows are summed before the
+// one shift that hands the sides to the neighbouring lanes; lane 0's left and
+// lane 63's right sums are those of the ghost columns.
+struct RowSums {
+    CD own, left, right;
+};
+
 __device__ __forceinline__ CD cd_add(CD a, CD b) { return CD{a.c + b.c, a.d + b.d}; }
-// a + m b with m = 1 or 0 (the ghost sums of lanes 0 and 63)
-__device__ __forceinline__ CD cd_fma(CD b, double m, CD a) { return CD{fma(b.c, m, a.c), fma(b.d, m, a.d)}; }
 __device__ __forceinline__ CD cd_from_left(CD a) { return CD{from_left0(a.c), from_left0(a.d)}; }
 __device__ __forceinline__ CD cd_from_right(CD a) { return CD{from_right0(a.c), from_right0(a.d)}; }
 
@@ -344,9 +399,11 @@ __global__ __launch_bounds__(256) void tile_mass_kernel(const RelaxedTile* __res
 }
 
 __global__ __launch_bounds__(256) void tile_integral_kernel(const TileGrid* __restrict__ grids,
-                                                            const int32_t* __restrict__ mass,
-                                                            int32_t* __restrict__ integ)
+                                                            const int32_t* __restrict__ mass, int32_t sparse,
+                                                            int32_t* __restrict__ reach)
 {
+    int32_t* const integ = reach + kReachHead;
+    if (blockIdx.x == 0 && threadIdx.x == 0) reach[0] = sparse;
     extern __shared__ int32_t sI[];
     const TileGrid tg = grids[blockIdx.x];
     const int W1 = tg.cols + 1, n = (tg.rows + 1) * W1;
@@ -368,17 +425,21 @@ __global__ __launch_bounds__(256) void tile_integral_kernel(const TileGrid* __re
     for (int i = threadIdx.x; i < n; i += 256) integ[tg.ioff + i] = sI[i];
 }
 
-// Does the adjoint step s need tile (band i, strip j): is a tile with initial
-// mass within a = floor((s + 1) / AR) + 1 bands and b = floor((s + 1) / AW) + 1
-// strips (the tiles whose nearest cells are at most s + 2 apart)?
-__device__ __forceinline__ bool adj_tile_in_reach(int i, int j, const TileGrid& tg, const int32_t* integ, int32_t s)
+// Is a tile with initial mass within a bands and b strips of tile (i, j)?
+__device__ __forceinline__ bool adj_tile_in_reach_by(int i, int j, const TileGrid& tg, const int32_t* integ, int a, int b)
 {
-    const int a = (s + 1) / AR + 1, b = (s + 1) / AW + 1;
     const int i0 = max(i - a, 0), i1 = min(i + a, tg.rows - 1);
     const int j0 = max(j - b, 0), j1 = min(j + b, tg.cols - 1);
     const int32_t* I = integ + tg.ioff;
     const int W1 = tg.cols + 1;
     return I[(i1 + 1) * W1 + (j1 + 1)] - I[i0 * W1 + (j1 + 1)] - I[(i1 + 1) * W1 + j0] + I[i0 * W1 + j0] > 0;
+}
+// Does the adjoint step s need tile (band i, strip j): is a tile with initial
+// mass within a = floor((s + 1) / AR) + 1 bands and b = floor((s + 1) / AW) + 1
+// strips (the tiles whose nearest cells are at most s + 2 apart)?
+__device__ __forceinline__ bool adj_tile_in_reach(int i, int j, const TileGrid& tg, const int32_t* integ, int32_t s)
+{
+    return adj_tile_in_reach_by(i, j, tg, integ, (s + 1) / AR + 1, (s + 1) / AW + 1);
 }
 
 // One adjoint step: (U_t, B_t), (Ubar_{t+1}, Bbar_{t+1}) -> (Ubar_t, Bbar_t)
@@ -395,41 +456,52 @@ __device__ __forceinline__ bool adj_tile_in_reach(int i, int j, const TileGrid& 
 // B of a source or of the target, so those terms are 0.  The kernel takes a
 // non-finite Pbar as 0 and adds the p_continue term only where B != 0, so the
 // overflow never turns into inf x 0 = NaN.
-// Four tiles (waves)
-// per workgroup, dealt to the XCDs in contiguous runs of the tile list.
 // SL: slope S = rise / run (0) or atan(rise / run) (1).
-template <bool WC, int FORM, int SL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void relaxed_adj_kernel(
-    const RelaxedTile* __restrict__ tiles, int32_t n_tiles, int32_t groups_per_xcd,
-    const TileGrid* __restrict__ grids, const EnvDev* __restrict__ envs, const float* __restrict__ g,
-    const float* __restrict__ E, const float* __restrict__ wind, const uint8_t* __restrict__ cls,
-    const float* __restrict__ den, int64_t n_cells, RelaxedArgs A, const double* __restrict__ U,
-    const double* __restrict__ B, const double* __restrict__ gU1, const double* __restrict__ gB1,
-    double* __restrict__ gU0, double* __restrict__ gB0, const double* __restrict__ Xin,
-    double* __restrict__ Xout, double* __restrict__ gsum, const float* __restrict__ env_wind,
-    const int32_t* __restrict__ integ, int32_t step)
+//
+// BANDS: waves per tile.  1: a wave walks the whole tile, four tiles per
+// workgroup.  8: eight waves walk 4 rows each and meet in LDS: the sums that
+// cross a band edge are handed over there, so tiles, exchange records and the
+// workspace are the same.
+template <bool WC, int FORM, int SL, int BANDS>
+__global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgpu_waves_per_eu(2))) void relaxed_adj_kernel(
+    const RelaxedTile* __restrict__ tiles, int32_t n_tiles, const TileGrid* __restrict__ grids,
+    const EnvDev* __restrict__ envs, const float* __restrict__ g, const float* __restrict__ E,
+    const float* __restrict__ wind, const uint8_t* __restrict__ cls, const float* __restrict__ den, int64_t n_cells,
+    RelaxedArgs A, const double* __restrict__ U, const double* __restrict__ B, const double* __restrict__ gU1,
+    const double* __restrict__ gB1, double* __restrict__ gU0, double* __restrict__ gB0,
+    const double* __restrict__ Xin, double* __restrict__ Xout, double* __restrict__ gsum,
+    const float* __restrict__ env_wind, const int32_t* __restrict__ reach, int32_t sparse, int32_t step)
 {
-    __shared__ double sveg[4][11][64];  // per lane: fuel adjoint x (1 + den) by land-cover class
-    __shared__ double sxc[4][AR][2];    // incoming Bbar terms of the first and last column, per row
+    constexpr int NW = BANDS == 1 ? 4 : BANDS;  // waves per workgroup
+    constexpr int BR = AR / BANDS;              // rows per wave
+    __shared__ double sveg[NW][11][64];  // per lane: fuel adjoint x (1 + den) by land-cover class
+    __shared__ double sxc[NW][BR][2];    // incoming Bbar terms of the first and last column, per row
+    // the sums that a band hands to the one above and below it, per lane, and
+    // those of the ghost columns (lanes 0 and 63)
+    __shared__ double s_up[BANDS == 1 ? 1 : NW][64], s_down[BANDS == 1 ? 1 : NW][64];
+    __shared__ double s_up_ghost[BANDS == 1 ? 1 : NW][2], s_down_ghost[BANDS == 1 ? 1 : NW][2];
+    __shared__ double s_sum[BANDS == 1 ? 1 : NW][17];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: tile values in SGPRs
-    const int b = blockIdx.x;
-    const int tix = (((b & 7) * groups_per_xcd + (b >> 3)) << 2) + wv;
+    const int tix = BANDS == 1 ? (int)blockIdx.x * 4 + wv : (int)blockIdx.x;
     if (tix >= n_tiles) return;
     const RelaxedTile td = tiles[tix];
     const TileGrid tg = grids[td.env];
     const int tb = td.r0 / AR, ts = td.c0 / AW;  // band and strip of the tile
-    if (integ && !adj_tile_in_reach(tb, ts, tg, integ, step)) return;  // sparse: the whole wave
+    // sparse: the whole tile (reach[0]: the states were written sparsely)
+    if (reach && (sparse || reach[0]) && !adj_tile_in_reach(tb, ts, tg, reach + kReachHead, step)) return;
     const EnvDev ed = envs[td.env];
     const int H = ed.H, W = ed.W;
-    const int r0 = td.r0;
-    const int rows = min(AR, H - r0);
+    const int band = BANDS == 1 ? 0 : wv;
+    const int tile_rows = min(AR, H - td.r0);
+    const int r0 = td.r0 + band * BR;
+    const int rows = min(BR, tile_rows - band * BR);  // <= 0: a band beyond the env
+    const bool first_band = band == 0, last_band = (band + 1) * BR >= tile_rows;
     const int c = td.c0 + lane;
     const bool act = c < W;
     // ghost column: c0 - 1 for lane 0, c0 + 64 for lane 63 (if on the grid)
     const int cg = lane == 0 ? td.c0 - 1 : td.c0 + AW;
     const bool ghost = (lane == 0 && td.c0 > 0) || (lane == 63 && td.c0 + AW < W);
-    const double mL = lane == 0 ? 1.0 : 0.0, mR = lane == 63 ? 1.0 : 0.0;
     const int64_t base = ed.offset;
     AdjEnv P;
     P.U = U + base;
@@ -453,6 +525,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
     auto at = [&](int r, int col) { return (uint32_t)(r * W + col); };
     auto tile_of = [&](int bi, int sj) { return (int64_t)(tg.first + bi * tg.cols + sj) * kXTile; };
     const int64_t xrec = (int64_t)tix * kXTile;
+    const int64_t xside = xrec + (lane == 0 ? kXLeft : kXRight) + band * BR;  // ghost entry of the row above the band
 
 #pragma unroll
     for (int j = 0; j < 11; ++j) sveg[wv][j][lane] = 0.0;
@@ -469,267 +542,319 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
     const float3 wenv = env_wind_of(ed, env_wind, td.env);
     const float wA0 = (A.alpha_w1 - A.alpha_w2) * wenv.x, wA1 = A.alpha_w2 * wenv.y, wA2 = A.alpha_w2 * wenv.z;
     const float gp = A.alpha_gamma * A.p_base;
-
-    // Bbar terms that neighbouring tiles added to this tile's cells in the
-    // previous step: for the first and last row one per lane (xt, xb, corners
-    // included), for the first and last column one per row (lanes 0 and 63,
-    // fetched by lanes 0..15 and 32..47 into LDS)
-    double xt = 0.0, xb = 0.0;
-    if (Xin) {
-        const bool up = tb > 0, dn = tb + 1 < tg.rows;
-        if (act && up) xt = Xin[tile_of(tb - 1, ts) + kXBot + lane];
-        if (act && dn) xb = Xin[tile_of(tb + 1, ts) + kXTop + lane];
-        if (lane == 0 && ts > 0) {
-            if (up) xt += Xin[tile_of(tb - 1, ts - 1) + kXRight + AR + 1];
-            if (dn) xb += Xin[tile_of(tb + 1, ts - 1) + kXRight];
-        }
-        if (lane == 63 && ts + 1 < tg.cols) {
-            if (up) xt += Xin[tile_of(tb - 1, ts + 1) + kXLeft + AR + 1];
-            if (dn) xb += Xin[tile_of(tb + 1, ts + 1) + kXLeft];
-        }
-        const int side = lane >> 5, ii = lane & 31;
-        double x = 0.0;
-        if (ii < rows) {
-            if (side == 0 && ts > 0) x = Xin[tile_of(tb, ts - 1) + kXRight + ii + 1];
-            if (side == 1 && ts + 1 < tg.cols) x = Xin[tile_of(tb, ts + 1) + kXLeft + ii + 1];
-        }
-        if (ii < AR) sxc[wv][ii][side] = x;
-        // the wave reads what its own lanes wrote: order the LDS accesses
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-
-    // the window: own column (X) and ghost column (G, lanes 0 and 63) of
-    // source rows r - 1 (a), r (m), r + 1 (b)
-    AdjCell X0 = load_adj_cell<WC>(P, at(r0 - 1, c), act && r0 > 0);
-    AdjCell X1 = load_adj_cell<WC>(P, at(r0, c), act);
-    AdjCell X2 = load_adj_cell<WC>(P, at(r0 + 1, c), act && r0 + 1 < H);
-    AdjCell G0 = load_adj_cell<WC>(P, at(r0 - 1, cg), ghost && r0 > 0);
-    AdjCell G1 = load_adj_cell<WC>(P, at(r0, cg), ghost);
-    AdjCell G2 = load_adj_cell<WC>(P, at(r0 + 1, cg), ghost && r0 + 1 < H);
-
-    // running sums (c, d) of the own column and the ghost column (lanes 0 and
-    // 63) for source rows r - 1 (a), r (m), r + 1 (b): slots below
-    double gB_prev = 0.0;
-    // sums of t0 = phibar dphi/dp_base and of t0 S; per-cell wind: of t0 V
-    // and t0 ((cos Vx + sin Vy) - V) of the source (acc_w1, acc_w2); per-env
-    // wind: of t0 cos_k and t0 sin_k
-    double acc_pb = 0.0, acc_w1 = 0.0, acc_w2 = 0.0, acc_s = 0.0, acc_gw = 0.0, acc_pc = 0.0;
     const double p_c = A.p_continue;
 
-    // loaded one row ahead: the target's U, Ubar, Bbar, and the class and
-    // density of the source row finished next (own and ghost column)
-    double nU = 0.0, ngU = 0.0, ngB = 0.0;
-    if (act) {
-        nU = ld_at(P.U, at(r0, c));
-        ngU = ld_at(P.gU1, at(r0, c));
-        ngB = ld_at(P.gB1, at(r0, c));
-    }
-    uint32_t fcl = 0, gcl = 0;
-    float fdn = 0.0f, gdn = 0.0f;
-    if (act && r0 > 0) {
-        fcl = ld_at(P.cls, at(r0 - 1, c));
-        fdn = ld_at(P.den, at(r0 - 1, c));
-    }
-    if (ghost && r0 > 0) {
-        gcl = ld_at(P.cls, at(r0 - 1, cg));
-        gdn = ld_at(P.den, at(r0 - 1, cg));
-    }
+    // sums over the lane's targets of w = ybar dphi/dp_base and of w S; per-cell
+    // wind: of w V and w ((cos Vx + sin Vy) - V) of the source (acc_w1, acc_w2);
+    // per-env wind: of w cos_k and w sin_k; each times gamma(v)
+    double acc_pb = 0.0, acc_w1 = 0.0, acc_w2 = 0.0, acc_s = 0.0, acc_gw = 0.0, acc_pc = 0.0;
+    // Bbar of the band's first and last row, and the ghost sums there, wait for
+    // the neighbouring bands
+    double first_B = 0.0, first_ghost = 0.0, last_B = 0.0, last_ghost = 0.0;
 
-    CD acc_a{0.0, 0.0}, acc_m{0.0, 0.0}, acc_b{0.0, 0.0};
-    CD gh_a{0.0, 0.0}, gh_m{0.0, 0.0}, gh_b{0.0, 0.0};
-    AdjCell Xa = X0, Xm = X1, Xb = X2, Ga = G0, Gm = G1, Gb = G2;
-#pragma unroll 1
-    for (int i = 0; i < rows; ++i) {
-        const int r = r0 + i;
-        const uint32_t v = at(r, c);
-        // the target's adjoint inputs, and what other tiles added to Bbar_{t+1}
-        // of this cell in the previous step
-        const double Uv = nU, gU = ngU;
-        double gB = ngB;
-        if (act && Xin)
-            gB += ((i == 0 ? xt : 0.0) + (i == rows - 1 ? xb : 0.0)) +
-                  (lane == 0 ? sxc[wv][i][0] : (lane == 63 ? sxc[wv][i][1] : 0.0));
-        const uint32_t cl_a = fcl, gcl_a = gcl;  // row r - 1
-        const float dn_a = fdn, gdn_a = gdn;
-        if (act && i + 1 < rows) {
-            nU = ld_at(P.U, v + W);
-            ngU = ld_at(P.gU1, v + W);
-            ngB = ld_at(P.gB1, v + W);
+    if (rows > 0) {
+        // Bbar terms that neighbouring tiles added to this tile's cells in the
+        // previous step: for the tile's first and last row one per lane (xt, xb,
+        // corners included), for the first and last column one per row (lanes 0
+        // and 63, fetched by lanes 0.. and 32.. into LDS)
+        double xt = 0.0, xb = 0.0;
+        if (Xin) {
+            const bool up = tb > 0 && first_band, dn = tb + 1 < tg.rows && last_band;
+            if (act && up) xt = Xin[tile_of(tb - 1, ts) + kXBot + lane];
+            if (act && dn) xb = Xin[tile_of(tb + 1, ts) + kXTop + lane];
+            if (lane == 0 && ts > 0) {
+                if (up) xt += Xin[tile_of(tb - 1, ts - 1) + kXRight + AR + 1];
+                if (dn) xb += Xin[tile_of(tb + 1, ts - 1) + kXRight];
+            }
+            if (lane == 63 && ts + 1 < tg.cols) {
+                if (up) xt += Xin[tile_of(tb - 1, ts + 1) + kXLeft + AR + 1];
+                if (dn) xb += Xin[tile_of(tb + 1, ts + 1) + kXLeft];
+            }
+            const int side = lane >> 5, ii = lane & 31;
+            double x = 0.0;
+            if (ii < rows) {
+                if (side == 0 && ts > 0) x = Xin[tile_of(tb, ts - 1) + kXRight + band * BR + ii + 1];
+                if (side == 1 && ts + 1 < tg.cols) x = Xin[tile_of(tb, ts + 1) + kXLeft + band * BR + ii + 1];
+            }
+            if (ii < BR) sxc[wv][ii][side] = x;
+            // the wave reads what its own lanes wrote: order the LDS accesses
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
+
+        // the window of source rows r - 1 (a), r (m), r + 1 (b): R0 to R2 in turn
+        // (three rows of the walk per loop pass, so that no row is ever moved);
+        // the row after it is on its way in nX (own column) and nG (ghost column)
+        AdjRow R0 = make_row<WC>(load_adj_cell<WC>(P, at(r0 - 1, c), act && r0 > 0),
+                                 load_adj_cell<WC>(P, at(r0 - 1, cg), ghost && r0 > 0));
+        AdjRow R1 = make_row<WC>(load_adj_cell<WC>(P, at(r0, c), act), load_adj_cell<WC>(P, at(r0, cg), ghost));
+        AdjRow R2;
+        AdjCell nX = load_adj_cell<WC>(P, at(r0 + 1, c), act && r0 + 1 < H);
+        AdjCell nG = load_adj_cell<WC>(P, at(r0 + 1, cg), ghost && r0 + 1 < H);
+        RowSums S0{}, S1{}, S2{};
+        double gB_prev = 0.0;
+
+        // loaded one row ahead: the target's U, Ubar, Bbar, and the class and
+        // density of the source row finished next (own and ghost column)
+        double nU = 0.0, ngU = 0.0, ngB = 0.0;
         if (act) {
-            fcl = ld_at(P.cls, v);
-            fdn = ld_at(P.den, v);
+            nU = ld_at(P.U, at(r0, c));
+            ngU = ld_at(P.gU1, at(r0, c));
+            ngB = ld_at(P.gB1, at(r0, c));
         }
-        if (ghost) {
-            gcl = ld_at(P.cls, at(r, cg));
-            gdn = ld_at(P.den, at(r, cg));
+        uint32_t fcl = 0, gcl = 0;
+        float fdn = 0.0f, gdn = 0.0f;
+        if (act && r0 > 0) {
+            fcl = ld_at(P.cls, at(r0 - 1, c));
+            fdn = ld_at(P.den, at(r0 - 1, c));
         }
-        // next window row (r + 2)
-        const bool more = i + 1 < rows && r + 2 < H;
-        const AdjCell Xn = load_adj_cell<WC>(P, at(r + 2, c), act && more);
-        const AdjCell Gn = load_adj_cell<WC>(P, at(r + 2, cg), ghost && more);
+        if (ghost && r0 > 0) {
+            gcl = ld_at(P.cls, at(r0 - 1, cg));
+            gdn = ld_at(P.den, at(r0 - 1, cg));
+        }
 
-        // ---- the target v = (r, c); its source in direction k is u_k = v - D_k
-        const AdjCell La = left_of<WC>(Xa, Ga), Lm = left_of<WC>(Xm, Gm), Lb = left_of<WC>(Xb, Gb);
-        const AdjCell Ra = right_of<WC>(Xa, Ga), Rm = right_of<WC>(Xm, Gm), Rb = right_of<WC>(Xb, Gb);
-        const double sB[8] = {Lm.B, Lb.B, Xb.B, Rb.B, Rm.B, Ra.B, Xa.B, La.B};
-        const float sg[8] = {Lm.g, Lb.g, Xb.g, Rb.g, Rm.g, Ra.g, Xa.g, La.g};
-        const float sE[8] = {Lm.E, Lb.E, Xb.E, Rb.E, Rm.E, Ra.E, Xa.E, La.E};
-        const float sV[8] = {Lm.V, Lb.V, Xb.V, Rb.V, Rm.V, Ra.V, Xa.V, La.V};
-        const float sVx[8] = {Lm.Vx, Lb.Vx, Xb.Vx, Rb.Vx, Rm.Vx, Ra.Vx, Xa.Vx, La.Vx};
-        const float sVy[8] = {Lm.Vy, Lb.Vy, Xb.Vy, Rb.Vy, Rm.Vy, Ra.Vy, Xa.Vy, La.Vy};
-        const double nbar = gB - gU;
-        // a non-finite Pbar comes only from an overflowed far-field adjoint
-        // (see above), whose terms all carry B = 0: they are 0, not inf x 0
-        const double Pbar = __builtin_isfinite(nbar * Uv) ? nbar * Uv : 0.0;
-        const float gv = Xm.g, Ev = Xm.E;
-        const float gam = A.alpha_gamma * gv, gpe = gp * gv;  // gamma(v), gamma(v) p_base
-        const double gam64 = gam;
-        // per-cell wind: the wind term (cos Vx + sin Vy) - V of direction k at the source
-        auto wterm = [&](int k) -> float { return (kCos[k] * sVx[k] + kSin[k] * sVy[k]) - sV[k]; };
-        auto slope_k = [&](int k) {
-            const float rr = (Ev - sE[k]) * ((k & 1) ? A.inv_diag : A.inv_orth);
-            return SL ? atanf(rr) : rr;
-        };
-        float q[8], em[8], ex[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            // the exponent sums onto the slope term first, so that the
-            // per-env wind constants are not kept per direction
-            float x = A.alpha_s * slope_k(k);
-            if constexpr (WC) {
-                x = x + (A.alpha_w1 * sV[k] + A.alpha_w2 * wterm(k));
-            } else {
-                x = x + wA0;
-                if (kCos[k] != 0.0f) x = x + kCos[k] * wA1;
-                if (kSin[k] != 0.0f) x = x + kSin[k] * wA2;
+        // the sums of a finished source row: those of the lane's own column from
+        // its three columns of targets, and of the ghost column
+        auto column = [&](const RowSums& q) { return cd_add(cd_add(q.own, cd_from_right(q.left)), cd_from_left(q.right)); };
+        auto ghost_of = [&](const RowSums& q) { return lane == 0 ? q.left : q.right; };
+
+        auto walk = [&](const AdjRow& a, const AdjRow& m, AdjRow& b, RowSums& Sa, RowSums& Sm, RowSums& Sb, int i) {
+            const int r = r0 + i;
+            const uint32_t v = at(r, c);
+            b = make_row<WC>(nX, nG);
+            // the target's adjoint inputs, and what other tiles added to Bbar_{t+1}
+            // of this cell in the previous step
+            const double Uv = nU, gU = ngU;
+            double gB = ngB;
+            if (act && Xin)
+                gB += ((i == 0 ? xt : 0.0) + (i == rows - 1 ? xb : 0.0)) +
+                      (lane == 0 ? sxc[wv][i][0] : (lane == 63 ? sxc[wv][i][1] : 0.0));
+            const uint32_t cl_a = fcl, gcl_a = gcl;  // row r - 1
+            const float dn_a = fdn, gdn_a = gdn;
+            if (act && i + 1 < rows) {
+                nU = ld_at(P.U, v + W);
+                ngU = ld_at(P.gU1, v + W);
+                ngB = ld_at(P.gB1, v + W);
             }
-            // off-grid sources have zero fuel and zero B, so their terms
-            // vanish; the exponent is capped so that 0 x e^x stays 0
-            ex[k] = hexp(fminf(x, 88.0f));
-            if constexpr (FORM == 0) {
-                const float2 qe = q_and_survival(gam * (A.p_base * (sg[k] * ex[k])));
-                q[k] = qe.x;
-                em[k] = qe.y;
+            if (act) {
+                fcl = ld_at(P.cls, v);
+                fdn = ld_at(P.den, v);
             }
-        }
-        // the terms of edge k from ybar_k = phibar_k / gamma: the gradient
-        // sums, then c_k and d_k into the running sums of source u_k (own
-        // column now, neighbouring lanes by DPP; lane 0 also keeps its k = 7,
-        // 0, 1 terms for the ghost column on its left, lane 63 its k = 5, 4, 3
-        // terms for the one on its right)
-        double gam_w = 0.0;  // sum_k ybar_k dphi_k/dp_base (gammabar / p_base)
-        auto emit = [&](int k, double cterm, double ybar) {
-            const double yw = ybar * (double)(sg[k] * ex[k]);
-            gam_w += yw;
-            const double t0 = yw * gam64;  // phibar dphi/dp_base
-            acc_pb += t0;
-            acc_s += t0 * (double)slope_k(k);
-            if constexpr (WC) {
-                acc_w1 += t0 * (double)sV[k];
-                acc_w2 += t0 * (double)wterm(k);
-            } else {  // the env's wind is applied at the end
-                if (kCos[k] != 0.0f) acc_w1 += t0 * (double)kCos[k];
-                if (kSin[k] != 0.0f) acc_w2 += t0 * (double)kSin[k];
+            if (ghost) {
+                gcl = ld_at(P.cls, at(r, cg));
+                gdn = ld_at(P.den, at(r, cg));
             }
-            const CD o{cterm, ybar * (double)(gpe * ex[k])};  // d = phibar p_base e^x
-            switch (k) {
-            case 0: acc_m = cd_add(acc_m, cd_from_right(o)); gh_m = cd_fma(o, mL, gh_m); break;
-            case 1: acc_b = cd_add(acc_b, cd_from_right(o)); gh_b = cd_fma(o, mL, gh_b); break;
-            case 2: acc_b = cd_add(acc_b, o); break;
-            case 3: acc_b = cd_add(acc_b, cd_from_left(o)); gh_b = cd_fma(o, mR, gh_b); break;
-            case 4: acc_m = cd_add(acc_m, cd_from_left(o)); gh_m = cd_fma(o, mR, gh_m); break;
-            case 5: acc_a = cd_add(acc_a, cd_from_left(o)); gh_a = cd_fma(o, mR, gh_a); break;
-            case 6: acc_a = cd_add(acc_a, o); break;
-            default: acc_a = cd_add(acc_a, cd_from_right(o)); gh_a = cd_fma(o, mL, gh_a); break;
-            }
-        };
-        double Pv;
-        if constexpr (FORM == 0) {
-            double pre[8], run = 1.0;
+            // next window row (r + 2)
+            const bool more = i + 1 < rows && r + 2 < H;
+            nX = load_adj_cell<WC>(P, at(r + 2, c), act && more);
+            nG = load_adj_cell<WC>(P, at(r + 2, cg), ghost && more);
+
+            // ---- the target v = (r, c); its source in direction k is u_k = v - D_k
+            const AdjCell* const src[8] = {&m.L, &b.L, &b.X, &b.R, &m.R, &a.R, &a.X, &a.L};
+            auto sB = [&](int k) { return src[k]->B; };
+            auto sg = [&](int k) { return src[k]->g; };
+            const double nbar = gB - gU;
+            // a non-finite Pbar comes only from an overflowed far-field adjoint
+            // (see above), whose terms all carry B = 0: they are 0, not inf x 0
+            const double Pbar = __builtin_isfinite(nbar * Uv) ? nbar * Uv : 0.0;
+            const float gv = m.X.g, Ev = m.X.E;
+            const float gam = A.alpha_gamma * gv, gpe = gp * gv;  // gamma(v), gamma(v) p_base
+            const double gam64 = gam;
+            // per-cell wind: the wind term (cos Vx + sin Vy) - V of direction k at the source
+            auto wterm = [&](int k) -> float { return (kCos[k] * src[k]->Vx + kSin[k] * src[k]->Vy) - src[k]->V; };
+            auto slope_k = [&](int k) {
+                const float rr = (Ev - src[k]->E) * ((k & 1) ? A.inv_diag : A.inv_orth);
+                return SL ? atanf(rr) : rr;
+            };
+            float q[8], em[8], ex[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                pre[k] = run;
-                run = run * (1.0 - (double)q[k] * sB[k]);
+                // the exponent sums onto the slope term first, so that the
+                // per-env wind constants are not kept per direction
+                float x = A.alpha_s * slope_k(k);
+                if constexpr (WC) {
+                    x = x + (A.alpha_w1 * src[k]->V + A.alpha_w2 * wterm(k));
+                } else {
+                    x = x + wA0;
+                    if (kCos[k] != 0.0f) x = x + kCos[k] * wA1;
+                    if (kSin[k] != 0.0f) x = x + kSin[k] * wA2;
+                }
+                // off-grid sources have zero fuel and zero B, so their terms
+                // vanish; the exponent is capped so that 0 x e^x stays 0
+                ex[k] = hexp(fminf(x, 88.0f));
+                if constexpr (FORM == 0) {
+                    const float2 qe = q_and_survival(gam * (A.p_base * (sg(k) * ex[k])));
+                    q[k] = qe.x;
+                    em[k] = qe.y;
+                }
             }
-            Pv = 1.0 - run;
-            double suf = 1.0;
+            // the terms of edge k from ybar_k = phibar_k / gamma: w_k = ybar_k
+            // dphi/dp_base for the gradient sums, c_k and d_k into the sums of
+            // source u_k's row
+            double w[8];
+            auto emit = [&](int k, double cterm, double ybar) {
+                w[k] = ybar * (double)(sg(k) * ex[k]);
+                const CD o{cterm, ybar * (double)(gpe * ex[k])};  // d = phibar p_base e^x
+                switch (k) {
+                case 0: Sm.left = cd_add(Sm.left, o); break;
+                case 1: Sb.left = o; break;
+                case 2: Sb.own = o; break;
+                case 3: Sb.right = o; break;
+                case 4: Sm.right = cd_add(Sm.right, o); break;
+                case 5: Sa.right = cd_add(Sa.right, o); break;
+                case 6: Sa.own = cd_add(Sa.own, o); break;
+                default: Sa.left = cd_add(Sa.left, o); break;
+                }
+            };
+            double Pv;
+            if constexpr (FORM == 0) {
+                // exclusive products prod over j != k of 1 - q_j B_j, no division:
+                // pairs, then pairs of pairs, Pbar carried along
+                double om[8];
 #pragma unroll
-            for (int k = 7; k >= 0; --k) {
-                const double excl = pre[k] * suf;  // prod over j != k, no division
-                suf = suf * (1.0 - (double)q[k] * sB[k]);
-                const double pe = Pbar * excl;
-                emit(k, pe * (double)q[k], (pe * sB[k]) * (double)em[k]);  // ybar = qbar dq/dy
+                for (int k = 0; k < 8; ++k) om[k] = 1.0 - (double)q[k] * sB(k);
+                const double p01 = om[0] * om[1], p23 = om[2] * om[3], p45 = om[4] * om[5], p67 = om[6] * om[7];
+                const double lo = p01 * p23, hi = p45 * p67;
+                Pv = 1.0 - lo * hi;
+                const double plo = Pbar * lo, phi = Pbar * hi;
+                const double e[4] = {p23 * phi, p01 * phi, p67 * plo, p45 * plo};
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const double pe = e[k >> 1] * om[k ^ 1];
+                    emit(k, pe * (double)q[k], (pe * sB(k)) * (double)em[k]);  // ybar = qbar dq/dy
+                }
+            } else {
+                double lam = 0.0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) lam = lam + (double)(A.p_base * (sg(k) * ex[k])) * sB(k);
+                const SurvivalPair sv = survival_pair((double)gam * lam);
+                Pv = sv.p;
+                const double ls = Pbar * sv.surv, lbar = ls * gam64;  // phibar_k = lbar B_k, ybar_k = phibar_k / gamma
+#pragma unroll
+                for (int k = 0; k < 8; ++k) emit(k, lbar * (double)(A.p_base * (sg(k) * ex[k])), ls * sB(k));
             }
-        } else {
-            double lam = 0.0;
+            double gam_w = w[0], ws = w[0] * (double)slope_k(0);  // sum_k w_k (gammabar / p_base), sum_k w_k S_k
 #pragma unroll
-            for (int k = 0; k < 8; ++k) lam = lam + (double)(A.p_base * (sg[k] * ex[k])) * sB[k];
-            const double surv = exp(-(double)gam * lam);
-            Pv = -expm1(-(double)gam * lam);
-            const double lbar = Pbar * gam64 * surv;  // phibar_k = lbar B_k, ybar_k = phibar_k / gamma
-            const double ls = Pbar * surv;
+            for (int k = 1; k < 8; ++k) {
+                gam_w += w[k];
+                ws += w[k] * (double)slope_k(k);
+            }
+            acc_pb += gam64 * gam_w;
+            acc_s += gam64 * ws;
+            if constexpr (WC) {
+                double w1 = 0.0, w2 = 0.0;
 #pragma unroll
-            for (int k = 7; k >= 0; --k) emit(k, lbar * (double)(A.p_base * (sg[k] * ex[k])), ls * sB[k]);
-        }
-        // gammabar = p_base gam_w; gamma(v) = alpha_gamma g(v)
-        const double gam_bar = (double)A.p_base * gam_w;
-        acc_gw += gam_w * (double)gv;
-        if (Xm.B != 0.0) acc_pc += gB * Xm.B;
-        acc_m.d += gam_bar * (double)A.alpha_gamma;
-        if (act) st_at(P.gU0, v, gU + nbar * Pv);
+                for (int k = 0; k < 8; ++k) {
+                    w1 += w[k] * (double)src[k]->V;
+                    w2 += w[k] * (double)wterm(k);
+                }
+                acc_w1 += gam64 * w1;
+                acc_w2 += gam64 * w2;
+            } else {  // the env's wind is applied at the end
+                const double d15 = w[1] - w[5], d37 = w[3] - w[7];
+                acc_w1 += gam64 * ((w[0] - w[4]) + (double)kHalfSqrt2 * (d15 - d37));
+                acc_w2 += gam64 * ((w[2] - w[6]) + (double)kHalfSqrt2 * (d15 + d37));
+            }
+            // gammabar = p_base gam_w; gamma(v) = alpha_gamma g(v)
+            const double gam_bar = (double)A.p_base * gam_w;
+            acc_gw += gam_w * (double)gv;
+            if (m.X.B != 0.0) acc_pc += gB * m.X.B;
+            Sm.own.d += gam_bar * (double)A.alpha_gamma;
+            if (act) st_at(P.gU0, v, gU + nbar * Pv);
 
-        // ---- source row r - 1 is complete
-        if (i == 0) {  // the row above the tile: the band above owns it
-            if (r0 > 0) {
-                if (act) Xout[xrec + kXTop + lane] = acc_a.c;
-                veg_add(acc_a.d, cl_a, dn_a, act);
-                if (ghost) Xout[xrec + (lane == 0 ? kXLeft : kXRight)] = gh_a.c;
-                veg_add(gh_a.d, gcl_a, gdn_a, ghost);
+            // ---- source row r - 1 is complete
+            const CD own = column(Sa), gh = ghost_of(Sa);
+            if (i > 0 || r0 > 0) {
+                veg_add(own.d, cl_a, dn_a, act);
+                veg_add(gh.d, gcl_a, gdn_a, ghost);
             }
+            if (i == 0) {  // the row above the band
+                if (!first_band) {
+                    s_up[wv][lane] = own.c;
+                    if (lane == 0 || lane == 63) s_up_ghost[wv][lane == 63] = gh.c;
+                } else if (r0 > 0) {
+                    if (act) Xout[xrec + kXTop + lane] = own.c;
+                    if (ghost) Xout[xside] = gh.c;
+                }
+            } else if (BANDS > 1 && i == 1) {
+                first_B = p_c * gB_prev + own.c;
+                first_ghost = gh.c;
+            } else {
+                if (act) st_at(P.gB0, v - W, p_c * gB_prev + own.c);
+                if (ghost) Xout[xside + i] = gh.c;
+            }
+            Sa = RowSums{};
+            gB_prev = gB;
+        };
+        int i = 0;
+        while (true) {
+            walk(R0, R1, R2, S0, S1, S2, i);
+            if (++i == rows) break;
+            walk(R1, R2, R0, S1, S2, S0, i);
+            if (++i == rows) break;
+            walk(R2, R0, R1, S2, S0, S1, i);
+            if (++i == rows) break;
+        }
+        // the band's last row, and the row below it: the sums of rows - 1 and
+        // rows, by where the walk ended
+        const int turn = rows % 3;  // 1: after the first call of a pass, 2: the second, 0: the third
+        const RowSums sl = turn == 1 ? S1 : (turn == 2 ? S2 : S0), sb = turn == 1 ? S2 : (turn == 2 ? S0 : S1);
+        const int rl = r0 + rows - 1;
+        const CD own = column(sl), gh = ghost_of(sl);
+        veg_add(own.d, fcl, fdn, act);
+        veg_add(gh.d, gcl, gdn, ghost);
+        if (BANDS == 1) {
+            if (act) st_at(P.gB0, at(rl, c), p_c * gB_prev + own.c);
+            if (ghost) Xout[xside + rows] = gh.c;
         } else {
-            if (act) st_at(P.gB0, v - W, p_c * gB_prev + acc_a.c);
-            veg_add(acc_a.d, cl_a, dn_a, act);
-            if (ghost) Xout[xrec + (lane == 0 ? kXLeft : kXRight) + i] = gh_a.c;
-            veg_add(gh_a.d, gcl_a, gdn_a, ghost);
+            last_B = p_c * gB_prev + own.c;
+            last_ghost = gh.c;
         }
-        acc_a = acc_m;
-        acc_m = acc_b;
-        acc_b = CD{0.0, 0.0};
-        gh_a = gh_m;
-        gh_m = gh_b;
-        gh_b = CD{0.0, 0.0};
-        gB_prev = gB;
-        Xa = Xm;
-        Xm = Xb;
-        Xb = Xn;
-        Ga = Gm;
-        Gm = Gb;
-        Gb = Gn;
+        if (rl + 1 < H) {
+            const bool on = act, gon = ghost;
+            const uint32_t cl = on ? (uint32_t)ld_at(P.cls, at(rl + 1, c)) : 0u;
+            const float dn = on ? ld_at(P.den, at(rl + 1, c)) : 0.0f;
+            const uint32_t gc = gon ? (uint32_t)ld_at(P.cls, at(rl + 1, cg)) : 0u;
+            const float gd = gon ? ld_at(P.den, at(rl + 1, cg)) : 0.0f;
+            const CD bo = column(sb), bg = ghost_of(sb);
+            veg_add(bo.d, cl, dn, on);
+            veg_add(bg.d, gc, gd, gon);
+            if (!last_band) {
+                s_down[wv][lane] = bo.c;
+                if (lane == 0 || lane == 63) s_down_ghost[wv][lane == 63] = bg.c;
+            } else {
+                if (act) Xout[xrec + kXBot + lane] = bo.c;
+                if (ghost) Xout[xside + rows + 1] = bg.c;
+            }
         }
-    // the tile's last row, and the row below it (owned by the band below)
-    const int rl = r0 + rows - 1;
-    if (act) st_at(P.gB0, at(rl, c), p_c * gB_prev + acc_a.c);
-    veg_add(acc_a.d, fcl, fdn, act);
-    if (ghost) Xout[xrec + (lane == 0 ? kXLeft : kXRight) + rows] = gh_a.c;
-    veg_add(gh_a.d, gcl, gdn, ghost);
-    if (rl + 1 < H) {
-        const bool on = act, gon = ghost;
-        const uint32_t cl = on ? (uint32_t)ld_at(P.cls, at(rl + 1, c)) : 0u;
-        const float dn = on ? ld_at(P.den, at(rl + 1, c)) : 0.0f;
-        const uint32_t gc = gon ? (uint32_t)ld_at(P.cls, at(rl + 1, cg)) : 0u;
-        const float gd = gon ? ld_at(P.den, at(rl + 1, cg)) : 0.0f;
-        if (act) Xout[xrec + kXBot + lane] = acc_m.c;
-        veg_add(acc_m.d, cl, dn, on);
-        if (ghost) Xout[xrec + (lane == 0 ? kXLeft : kXRight) + rows + 1] = gh_m.c;
-        veg_add(gh_m.d, gc, gd, gon);
+    }
+
+    if constexpr (BANDS > 1) {
+        __syncthreads();
+        if (rows > 0) {
+            const int gi = lane == 63;
+            const double down = first_band ? 0.0 : s_down[wv - 1][lane], up = last_band ? 0.0 : s_up[wv + 1][lane];
+            const double down_g = first_band ? 0.0 : s_down_ghost[wv - 1][gi], up_g = last_band ? 0.0 : s_up_ghost[wv + 1][gi];
+            if (rows == 1) {
+                if (act) st_at(P.gB0, at(r0, c), (last_B + down) + up);
+                if (ghost) Xout[xside + 1] = (last_ghost + down_g) + up_g;
+            } else {
+                if (act) {
+                    st_at(P.gB0, at(r0, c), first_B + down);
+                    st_at(P.gB0, at(r0 + rows - 1, c), last_B + up);
+                }
+                if (ghost) {
+                    Xout[xside + 1] = first_ghost + down_g;
+                    Xout[xside + rows] = last_ghost + up_g;
+                }
+            }
+        }
     }
 
     // ---- the tile's 17 gradient terms (fixed order), added to its gsum row.
     // dphi/dx = phi = p_base dphi/dp_base, so the wind and slope terms are
-    // p_base times sums of t0
+    // p_base times sums of gamma w
     const double p_base = A.p_base;
     double acc[17];
     acc[0] = acc_pb;
@@ -747,44 +872,80 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
     for (int j = 0; j < 11; ++j) acc[6 + j] = sveg[wv][j][lane];
 #pragma unroll
     for (int j = 0; j < 17; ++j) acc[j] = wave_sum(acc[j]);
-    if (lane == 0) {
-        double* row = gsum + (int64_t)tix * 17;
+    double* row = gsum + (int64_t)tix * 17;
+    if constexpr (BANDS == 1) {
+        if (lane == 0) {
 #pragma unroll
-        for (int j = 0; j < 17; ++j) row[j] += acc[j];
+            for (int j = 0; j < 17; ++j) row[j] += acc[j];
+        }
+    } else {
+        if (lane == 0) {
+#pragma unroll
+            for (int j = 0; j < 17; ++j) s_sum[wv][j] = acc[j];
+        }
+        __syncthreads();
+        if (threadIdx.x < 17) {
+            double sum = 0.0;
+            for (int w2 = 0; w2 < NW; ++w2) sum += s_sum[w2][threadIdx.x];
+            row[threadIdx.x] += sum;
+        }
     }
 }
 
 // One relaxed forward step on the adjoint's 64 x AR tiles, each cut into
-// kFwdSplit row bands of one wave (four per workgroup, so that enough loads
+// SPLIT row bands of one wave (four per workgroup, so that enough loads
 // are in flight): lanes own columns and walk the rows with the same
 // window as the adjoint (left and right sources by DPP from the neighbouring
 // lanes, the ghost columns for lanes 0 and 63), so each cell is loaded once.
 // FORM 0: p_ignite = 1 - prod_k (1 - q_k B_k); FORM 1: p_ignite = 1 -
 // exp(-gamma sum_k B_k phi_k).  Rows where no lane sees burning mass skip the
 // edge terms (P = 0 exactly there).
-template <bool WC, int FORM, int SL>
+//
+// Sparse (reach given): after t steps burning mass lies within t cells of the
+// cells that hold it at the start (S_0).  Step t runs on the tiles within
+// reach, fills the tiles one further out with the initial state (U_0, 0), which
+// is what they hold, and leaves the rest unwritten: the next step, and the
+// adjoint of step t + 1, read only tiles within reach and their neighbours.
+template <bool WC, int FORM, int SL, int SPLIT>
 __global__ __launch_bounds__(256) void relaxed_fwd_kernel(
-    const RelaxedTile* __restrict__ tiles, int32_t n_tiles, int32_t groups_per_xcd,
+    const RelaxedTile* __restrict__ tiles, int32_t n_tiles, const TileGrid* __restrict__ grids,
     const EnvDev* __restrict__ envs, const float* __restrict__ g, const float* __restrict__ E,
     const float* __restrict__ wind, int64_t n_cells, RelaxedArgs A, const double* __restrict__ U,
     const double* __restrict__ B, double* __restrict__ Uo, double* __restrict__ Bo,
-    const float* __restrict__ env_wind)
+    const float* __restrict__ env_wind, const int32_t* __restrict__ reach, const double* __restrict__ U_0, int32_t step)
 {
+    constexpr int BR = AR / SPLIT;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b = blockIdx.x;
-    const int wix = (((b & 7) * groups_per_xcd + (b >> 3)) << 2) + wv;
-    if (wix >= n_tiles * kFwdSplit) return;
-    const RelaxedTile td = tiles[wix / kFwdSplit];
+    const int wix = (int)blockIdx.x * 4 + wv;
+    if (wix >= n_tiles * SPLIT) return;
+    const RelaxedTile td = tiles[wix / SPLIT];
     const EnvDev ed = envs[td.env];
-    const int H = ed.H, W = ed.W, r0 = td.r0 + (wix % kFwdSplit) * (AR / kFwdSplit);
+    const int H = ed.H, W = ed.W, r0 = td.r0 + (wix % SPLIT) * BR;
     if (r0 >= H) return;
-    const int rows = min(AR / kFwdSplit, H - r0);
+    const int rows = min(BR, H - r0);
     const int c = td.c0 + lane;
     const bool act = c < W;
+    const int64_t base = ed.offset;
+    double* const Uoe = Uo + base;
+    double* const Boe = Bo + base;
+    auto at = [&](int r, int col) { return (uint32_t)(r * W + col); };
+    if (reach && reach[0]) {
+        const TileGrid tg = grids[td.env];
+        const int tb = td.r0 / AR, ts = td.c0 / AW;
+        if (!adj_tile_in_reach(tb, ts, tg, reach + kReachHead, step)) {
+            if (!adj_tile_in_reach_by(tb, ts, tg, reach + kReachHead, (step + 2) / AR + 2, (step + 2) / AW + 2)) return;
+            if (act)
+                for (int i = 0; i < rows; ++i) {
+                    const uint32_t v = at(r0 + i, c);
+                    st_at(Uoe, v, ld_at(U_0 + base, v));
+                    st_at(Boe, v, 0.0);
+                }
+            return;
+        }
+    }
     const int cg = lane == 0 ? td.c0 - 1 : td.c0 + AW;
     const bool ghost = (lane == 0 && td.c0 > 0) || (lane == 63 && td.c0 + AW < W);
-    const int64_t base = ed.offset;
     AdjEnv P{};
     P.U = U + base;
     P.B = B + base;
@@ -795,76 +956,78 @@ __global__ __launch_bounds__(256) void relaxed_fwd_kernel(
         P.Vx = wind + n_cells + base;
         P.Vy = wind + 2 * n_cells + base;
     }
-    double* const Uoe = Uo + base;
-    double* const Boe = Bo + base;
-    auto at = [&](int r, int col) { return (uint32_t)(r * W + col); };
     const float3 wenv = env_wind_of(ed, env_wind, td.env);
     const float wA0 = (A.alpha_w1 - A.alpha_w2) * wenv.x, wA1 = A.alpha_w2 * wenv.y, wA2 = A.alpha_w2 * wenv.z;
     const double p_c = A.p_continue;
 
-    AdjCell Xa = load_adj_cell<WC>(P, at(r0 - 1, c), act && r0 > 0);
-    AdjCell Xm = load_adj_cell<WC>(P, at(r0, c), act);
-    AdjCell Xb = load_adj_cell<WC>(P, at(r0 + 1, c), act && r0 + 1 < H);
-    AdjCell Ga = load_adj_cell<WC>(P, at(r0 - 1, cg), ghost && r0 > 0);
-    AdjCell Gm = load_adj_cell<WC>(P, at(r0, cg), ghost);
-    AdjCell Gb = load_adj_cell<WC>(P, at(r0 + 1, cg), ghost && r0 + 1 < H);
+    // the window as in the adjoint; n0 to n2: does the row hold burning mass
+    auto holds = [&](const AdjCell& x, const AdjCell& gh) { return __any(x.B != 0.0 || gh.B != 0.0) != 0; };
+    AdjCell nX = load_adj_cell<WC>(P, at(r0 - 1, c), act && r0 > 0);
+    AdjCell nG = load_adj_cell<WC>(P, at(r0 - 1, cg), ghost && r0 > 0);
+    AdjRow R0 = make_row<WC>(nX, nG), R1, R2;
+    bool n0 = holds(nX, nG), n1, n2 = false;
+    nX = load_adj_cell<WC>(P, at(r0, c), act);
+    nG = load_adj_cell<WC>(P, at(r0, cg), ghost);
+    R1 = make_row<WC>(nX, nG);
+    n1 = holds(nX, nG);
+    nX = load_adj_cell<WC>(P, at(r0 + 1, c), act && r0 + 1 < H);
+    nG = load_adj_cell<WC>(P, at(r0 + 1, cg), ghost && r0 + 1 < H);
     double nU = act ? ld_at(P.U, at(r0, c)) : 0.0;
 
-#pragma unroll 1
-    for (int i = 0; i < rows; ++i) {
+    auto walk = [&](const AdjRow& a, const AdjRow& m, AdjRow& b, bool na, bool nm, bool& nb, int i) {
         const int r = r0 + i;
         const uint32_t v = at(r, c);
+        b = make_row<WC>(nX, nG);
+        nb = holds(nX, nG);
         const double Uv = nU;
         if (act && i + 1 < rows) nU = ld_at(P.U, v + W);
         const bool more = i + 1 < rows && r + 2 < H;
-        const AdjCell Xn = load_adj_cell<WC>(P, at(r + 2, c), act && more);
-        const AdjCell Gn = load_adj_cell<WC>(P, at(r + 2, cg), ghost && more);
+        nX = load_adj_cell<WC>(P, at(r + 2, c), act && more);
+        nG = load_adj_cell<WC>(P, at(r + 2, cg), ghost && more);
 
         double Pv = 0.0;
-        const bool any_burning = Xa.B != 0.0 || Xm.B != 0.0 || Xb.B != 0.0 || Ga.B != 0.0 || Gm.B != 0.0 ||
-                                 Gb.B != 0.0;
-        if (__any(any_burning)) {  // wave-uniform
-            const AdjCell La = left_of<WC>(Xa, Ga), Lm = left_of<WC>(Xm, Gm), Lb = left_of<WC>(Xb, Gb);
-            const AdjCell Ra = right_of<WC>(Xa, Ga), Rm = right_of<WC>(Xm, Gm), Rb = right_of<WC>(Xb, Gb);
-            const double sB[8] = {Lm.B, Lb.B, Xb.B, Rb.B, Rm.B, Ra.B, Xa.B, La.B};
-            const float sg[8] = {Lm.g, Lb.g, Xb.g, Rb.g, Rm.g, Ra.g, Xa.g, La.g};
-            const float sE[8] = {Lm.E, Lb.E, Xb.E, Rb.E, Rm.E, Ra.E, Xa.E, La.E};
-            const float sV[8] = {Lm.V, Lb.V, Xb.V, Rb.V, Rm.V, Ra.V, Xa.V, La.V};
-            const float sVx[8] = {Lm.Vx, Lb.Vx, Xb.Vx, Rb.Vx, Rm.Vx, Ra.Vx, Xa.Vx, La.Vx};
-            const float sVy[8] = {Lm.Vy, Lb.Vy, Xb.Vy, Rb.Vy, Rm.Vy, Ra.Vy, Xa.Vy, La.Vy};
-            const float Ev = Xm.E, gam = A.alpha_gamma * Xm.g;
-            double prod = 1.0, lam = 0.0;
+        if (na || nm || nb) {  // wave-uniform
+            const AdjCell* const src[8] = {&m.L, &b.L, &b.X, &b.R, &m.R, &a.R, &a.X, &a.L};
+            const float Ev = m.X.E, gam = A.alpha_gamma * m.X.g;
+            double om[8], lam = 0.0;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const float rr = (Ev - sE[k]) * ((k & 1) ? A.inv_diag : A.inv_orth);
+                const AdjCell& u = *src[k];
+                const float rr = (Ev - u.E) * ((k & 1) ? A.inv_diag : A.inv_orth);
                 float x = A.alpha_s * (SL ? atanf(rr) : rr);
                 if constexpr (WC) {
-                    x = x + (A.alpha_w1 * sV[k] + A.alpha_w2 * ((kCos[k] * sVx[k] + kSin[k] * sVy[k]) - sV[k]));
+                    x = x + (A.alpha_w1 * u.V + A.alpha_w2 * ((kCos[k] * u.Vx + kSin[k] * u.Vy) - u.V));
                 } else {
                     x = x + wA0;
                     if (kCos[k] != 0.0f) x = x + kCos[k] * wA1;
                     if (kSin[k] != 0.0f) x = x + kSin[k] * wA2;
                 }
                 // off-grid sources read 0: no fuel, no burning mass
-                const float phi = A.p_base * (sg[k] * hexp(fminf(x, 88.0f)));
+                const float phi = A.p_base * (u.g * hexp(fminf(x, 88.0f)));
                 if constexpr (FORM == 0)
-                    prod = prod * (1.0 - (double)one_minus_exp_neg(gam * phi) * sB[k]);
+                    om[k] = 1.0 - (double)one_minus_exp_neg(gam * phi) * u.B;
                 else
-                    lam = lam + (double)phi * sB[k];
+                    lam = lam + (double)phi * u.B;
             }
-            Pv = FORM == 0 ? 1.0 - prod : -expm1(-(double)gam * lam);
+            if constexpr (FORM == 0)
+                Pv = 1.0 - ((om[0] * om[1]) * (om[2] * om[3])) * ((om[4] * om[5]) * (om[6] * om[7]));
+            else
+                Pv = survival_pair((double)gam * lam).p;
         }
         if (act) {
             const double N = Uv * Pv;
             st_at(Uoe, v, Uv - N);
-            st_at(Boe, v, N + p_c * Xm.B);
+            st_at(Boe, v, N + p_c * m.X.B);
         }
-        Xa = Xm;
-        Xm = Xb;
-        Xb = Xn;
-        Ga = Gm;
-        Gm = Gb;
-        Gb = Gn;
+    };
+    int i = 0;
+    while (true) {
+        walk(R0, R1, R2, n0, n1, n2, i);
+        if (++i == rows) break;
+        walk(R1, R2, R0, n1, n2, n0, i);
+        if (++i == rows) break;
+        walk(R2, R0, R1, n2, n0, n1, i);
+        if (++i == rows) break;
     }
 }
 
@@ -1103,7 +1266,7 @@ hipError_t fill_f64(hipStream_t s, double* p, int64_t n, double v)
 
 // Workspace layout (all offsets 256-byte aligned).
 struct WsLayout {
-    size_t g, ckpt, seg, fwd, adj, xchg, gsum, total;
+    size_t g, ckpt, seg, fwd, adj, xchg, gsum, reach, total;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1128,6 +1291,9 @@ WsLayout layout(int64_t n, int64_t n_adj_tiles, int32_t T, int32_t k)
     o = align256(o + sizeof(double) * 2 * (size_t)n_adj_tiles * kXTile);
     L.gsum = o;  // 17 gradient partial sums per adjoint tile
     o = align256(o + sizeof(double) * 17 * (size_t)n_adj_tiles);
+    // the head and the envs' integral images: (rows + 1)(cols + 1) <= 4 rows cols entries each
+    L.reach = o;
+    o = align256(o + sizeof(int32_t) * (kReachHead + 4 * (size_t)n_adj_tiles));
     L.total = o;
     return L;
 }
@@ -1151,39 +1317,59 @@ RelaxedInputs at_step(const RelaxedInputs& in, int32_t t)
     return r;
 }
 
-template <bool WC, int FORM>
-void launch_fwd(hipStream_t s, const RelaxedInputs& in, const RelaxedArgs& A, const float* g,
-                const double* U, const double* B, double* Uo, double* Bo)
+// Row bands per tile: where the tiles alone leave the chip idle, a step lasts
+// as long as one wave's walk, so more waves walk fewer rows each.
+constexpr int kFwdBands = 4, kFwdBandsFew = 16, kAdjBandsFew = 8;
+constexpr int kFewTiles = 1024;
+
+template <bool WC, int FORM, int SL>
+void launch_fwd(hipStream_t s, const RelaxedInputs& in, const RelaxedState& R, const RelaxedArgs& A, const float* g,
+                const double* U, const double* B, double* Uo, double* Bo, const int32_t* reach, const double* U_0,
+                int32_t step)
 {
-    const int32_t groups = (in.n_tiles * kFwdSplit + 3) / 4;
-    const int32_t per_xcd = (groups + 7) / 8;
-    auto kernel = A.slope_mode ? relaxed_fwd_kernel<WC, FORM, 1> : relaxed_fwd_kernel<WC, FORM, 0>;
-    hipLaunchKernelGGL(kernel, dim3(8 * per_xcd), dim3(256), 0, s, in.tiles, in.n_tiles, per_xcd, in.envs, g,
-                       in.E, in.wind, in.n_cells, A, U, B, Uo, Bo, in.env_wind);
+    const bool few = in.n_tiles < kFewTiles;
+    auto kernel = few ? relaxed_fwd_kernel<WC, FORM, SL, kFwdBandsFew> : relaxed_fwd_kernel<WC, FORM, SL, kFwdBands>;
+    const int32_t groups = (in.n_tiles * (few ? kFwdBandsFew : kFwdBands) + 3) / 4;
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(256), 0, s, in.tiles, in.n_tiles, R.d_tgrid, in.envs, g, in.E,
+                       in.wind, in.n_cells, A, U, B, Uo, Bo, in.env_wind, reach, U_0, step);
 }
 
-hipError_t fwd_step(hipStream_t s, const RelaxedInputs& in, const RelaxedArgs& A, const float* g,
-                    const double* U, const double* B, double* Uo, double* Bo)
+// Calls fn with the wind, form and slope of a launch as template arguments.
+template <class Fn>
+void with_variant(bool wc, int form, int slope, Fn fn)
 {
-    if (in.wind)
-        in.form ? launch_fwd<true, 1>(s, in, A, g, U, B, Uo, Bo) : launch_fwd<true, 0>(s, in, A, g, U, B, Uo, Bo);
-    else
-        in.form ? launch_fwd<false, 1>(s, in, A, g, U, B, Uo, Bo) : launch_fwd<false, 0>(s, in, A, g, U, B, Uo, Bo);
+    auto pick = [&](auto w, auto f) {
+        slope ? fn(w, f, std::integral_constant<int, 1>{}) : fn(w, f, std::integral_constant<int, 0>{});
+    };
+    auto pick_form = [&](auto w) {
+        form ? pick(w, std::integral_constant<int, 1>{}) : pick(w, std::integral_constant<int, 0>{});
+    };
+    wc ? pick_form(std::true_type{}) : pick_form(std::false_type{});
+}
+
+// Relaxed step `step`, from (U, B) to (Uo, Bo); U_0: the initial U.
+hipError_t fwd_step(hipStream_t s, const RelaxedInputs& in, const RelaxedState& R, const RelaxedArgs& A, const float* g,
+                    const double* U, const double* B, double* Uo, double* Bo, const int32_t* reach,
+                    const double* U_0, int32_t step)
+{
+    with_variant(in.wind != nullptr, in.form, A.slope_mode, [&](auto w, auto f, auto sl) {
+        launch_fwd<decltype(w)::value, decltype(f)::value, decltype(sl)::value>(s, in, R, A, g, U, B, Uo, Bo, reach,
+                                                                                U_0, step);
+    });
     return hipGetLastError();
 }
 
-template <bool WC, int FORM>
+template <bool WC, int FORM, int SL>
 void launch_adj(hipStream_t s, const RelaxedInputs& in, const RelaxedState& R, const RelaxedArgs& A,
                 const float* g, const double* U, const double* B, const double* gU1, const double* gB1,
-                double* gU0, double* gB0, const double* Xin, double* Xout, double* gsum, const int32_t* integ,
+                double* gU0, double* gB0, const double* Xin, double* Xout, double* gsum, const int32_t* reach,
                 int32_t step)
 {
-    const int32_t groups = (R.n_btiles + 3) / 4;
-    const int32_t per_xcd = (groups + 7) / 8;
-    auto kernel = A.slope_mode ? relaxed_adj_kernel<WC, FORM, 1> : relaxed_adj_kernel<WC, FORM, 0>;
-    hipLaunchKernelGGL(kernel, dim3(8 * per_xcd), dim3(256), 0, s, R.d_btiles, R.n_btiles, per_xcd, R.d_tgrid,
-                       in.envs, g, in.E, in.wind, in.cls, in.den, in.n_cells, A, U, B, gU1, gB1, gU0, gB0, Xin,
-                       Xout, gsum, in.env_wind, integ, step);
+    const bool few = R.n_btiles < kFewTiles;
+    auto kernel = few ? relaxed_adj_kernel<WC, FORM, SL, kAdjBandsFew> : relaxed_adj_kernel<WC, FORM, SL, 1>;
+    hipLaunchKernelGGL(kernel, dim3(few ? R.n_btiles : (R.n_btiles + 3) / 4), dim3(few ? 64 * kAdjBandsFew : 256), 0, s,
+                       R.d_btiles, R.n_btiles, R.d_tgrid, in.envs, g, in.E, in.wind, in.cls, in.den, in.n_cells, A, U,
+                       B, gU1, gB1, gU0, gB0, Xin, Xout, gsum, in.env_wind, reach, in.sparse, step);
 }
 
 }  // namespace
@@ -1220,9 +1406,7 @@ int relaxed_prepare(RelaxedState& R, const std::vector<sim_env>& envs)
     R.n_btiles = (int32_t)btiles.size();
     R.n_env = (int32_t)envs.size();
     if (ioff < INT32_MAX && 4 * max_img <= 64 * 1024) {
-        if (hipMalloc(&R.d_tmass, btiles.size() * sizeof(int32_t)) != hipSuccess ||
-            hipMalloc(&R.d_tinteg, (size_t)ioff * sizeof(int32_t)) != hipSuccess)
-            return -1;
+        if (hipMalloc(&R.d_tmass, btiles.size() * sizeof(int32_t)) != hipSuccess) return -1;
         R.sparse_lds = (int32_t)(4 * max_img);
     }
     return 0;
@@ -1264,7 +1448,7 @@ void relaxed_free(RelaxedState& R)
 {
     for (void* p : {(void*)R.d_btiles, (void*)R.d_pool,
                     (void*)R.d_env_blocks, (void*)R.d_pool_vals, (void*)R.d_bce_loss, (void*)R.d_tgrid,
-                    (void*)R.d_tmass, (void*)R.d_tinteg})
+                    (void*)R.d_tmass})
         if (p) (void)hipFree(p);
     R = RelaxedState{};
 }
@@ -1302,6 +1486,18 @@ hipError_t relaxed_forward(hipStream_t s, const RelaxedInputs& in, const sim_par
     hipError_t e = fuel(s, in, p, g);
     if (e == hipSuccess) e = copy_f64(s, ckpt, U, n);
     if (e == hipSuccess) e = copy_f64(s, ckpt + n, B, n);
+    // sparse: tiles with initial burning mass and their integral images, kept in
+    // the workspace for the backward; a dense forward notes that it is one
+    const int32_t* reach = nullptr;
+    if (R.sparse_lds > 0 && e == hipSuccess) {
+        int32_t* r = reinterpret_cast<int32_t*>(ws + L.reach);
+        hipLaunchKernelGGL(tile_mass_kernel, dim3(R.n_btiles), dim3(256), 0, s, R.d_btiles, in.envs, ckpt + n,
+                           R.d_tmass);
+        hipLaunchKernelGGL(tile_integral_kernel, dim3(R.n_env), dim3(256), (size_t)R.sparse_lds, s, R.d_tgrid,
+                           R.d_tmass, in.sparse ? 1 : 0, r);
+        e = hipGetLastError();
+        reach = r;
+    }
     const double* cu = ckpt;  // state t
     const double* cb = ckpt + n;
     for (int32_t t = 0; t < T && e == hipSuccess; ++t) {
@@ -1320,7 +1516,7 @@ hipError_t relaxed_forward(hipStream_t s, const RelaxedInputs& in, const sim_par
             nu = spare[0] == cu ? spare[1] : spare[0];
             nb = nu + n;
         }
-        e = fwd_step(s, at_step(in, t), A, g, cu, cb, nu, nb);
+        e = fwd_step(s, at_step(in, t), R, A, g, cu, cb, nu, nb, reach, ckpt, t);
         cu = nu;
         cb = nb;
     }
@@ -1404,17 +1600,14 @@ hipError_t relaxed_backward(hipStream_t s, const RelaxedInputs& in, const sim_pa
     double* nb = adj + 3 * n;
     if (e == hipSuccess) e = copy_f64(s, cu, gU_T, n);
     if (e == hipSuccess) e = gB_T ? copy_f64(s, cb, gB_T, n) : fill_f64(s, cb, n, 0.0);
-    // sparse adjoint: tiles with initial burning mass (checkpoint 0 holds B_0),
-    // their integral images, and zeroed output buffers (skipped tiles keep them)
-    const int32_t* integ = nullptr;
-    if (in.sparse && R.sparse_lds > 0 && T > 0 && e == hipSuccess) {
-        hipLaunchKernelGGL(tile_mass_kernel, dim3(R.n_btiles), dim3(256), 0, s, R.d_btiles, in.envs, ckpt + n,
-                           R.d_tmass);
-        hipLaunchKernelGGL(tile_integral_kernel, dim3(R.n_env), dim3(256), (size_t)R.sparse_lds, s, R.d_tgrid,
-                           R.d_tmass, R.d_tinteg);
-        e = hipGetLastError();
-        if (e == hipSuccess) e = fill_f64(s, nu, 2 * n, 0.0);
-        integ = R.d_tinteg;
+    // sparse adjoint: the reach of the initial burning mass, left in the
+    // workspace by the forward, and zeroed output buffers (skipped tiles keep
+    // them).  A forward that wrote its states sparsely makes every adjoint on
+    // this workspace sparse: the gradient is the same bits.
+    const int32_t* reach = nullptr;
+    if (R.sparse_lds > 0 && T > 0 && e == hipSuccess) {
+        reach = reinterpret_cast<const int32_t*>(ws + L.reach);
+        e = fill_f64(s, nu, 2 * n, 0.0);
     }
     const int32_t n_seg = T > 0 ? (T + k - 1) / k : 0;
     for (int32_t sg = n_seg - 1; sg >= 0 && e == hipSuccess; --sg) {
@@ -1430,8 +1623,8 @@ hipError_t relaxed_backward(hipStream_t s, const RelaxedInputs& in, const sim_pa
         const bool stored = sg == n_seg - 1 && R.last_segment_ws == workspace;
         if (sg < n_seg - 1) R.last_segment_ws = nullptr;
         for (int32_t j = 1; j < t1 - t0 && !stored && e == hipSuccess; ++j)
-            e = fwd_step(s, at_step(in, t0 + j - 1), A, g, state_u(j - 1), state_b(j - 1),
-                         seg + (size_t)j * 2 * n, seg + (size_t)j * 2 * n + n);
+            e = fwd_step(s, at_step(in, t0 + j - 1), R, A, g, state_u(j - 1), state_b(j - 1),
+                         seg + (size_t)j * 2 * n, seg + (size_t)j * 2 * n + n, reach, ckpt, t0 + j - 1);
         for (int32_t t = t1 - 1; t >= t0 && e == hipSuccess; --t) {
             const int32_t j = t - t0;
             const double *Ut = state_u(j), *Bt = state_b(j);
@@ -1439,12 +1632,10 @@ hipError_t relaxed_backward(hipStream_t s, const RelaxedInputs& in, const sim_pa
             // step t writes the exchange record of parity t; step t - 1 adds it
             const double* Xin = t == T - 1 ? nullptr : xchg + ((t + 1) & 1) * xrecs;
             double* Xout = xchg + (t & 1) * xrecs;
-            if (it.wind)
-                it.form ? launch_adj<true, 1>(s, it, R, A, g, Ut, Bt, cu, cb, nu, nb, Xin, Xout, gsum, integ, t)
-                        : launch_adj<true, 0>(s, it, R, A, g, Ut, Bt, cu, cb, nu, nb, Xin, Xout, gsum, integ, t);
-            else
-                it.form ? launch_adj<false, 1>(s, it, R, A, g, Ut, Bt, cu, cb, nu, nb, Xin, Xout, gsum, integ, t)
-                        : launch_adj<false, 0>(s, it, R, A, g, Ut, Bt, cu, cb, nu, nb, Xin, Xout, gsum, integ, t);
+            with_variant(it.wind != nullptr, it.form, A.slope_mode, [&](auto w, auto f, auto sl) {
+                launch_adj<decltype(w)::value, decltype(f)::value, decltype(sl)::value>(
+                    s, it, R, A, g, Ut, Bt, cu, cb, nu, nb, Xin, Xout, gsum, reach, t);
+            });
             e = hipGetLastError();
             std::swap(cu, nu);
             std::swap(cb, nb);

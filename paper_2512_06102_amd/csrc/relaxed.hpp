@@ -41,13 +41,11 @@ struct RelaxedState {
     int32_t* d_env_blocks = nullptr;  // [n_env][2]: first block, number of blocks
     double* d_pool_vals = nullptr;    // [4][n_pool]: block means of S and Y, BCE sum, squared error
     double* d_bce_loss = nullptr;     // [n_env]: per-env loss in fp64
-    // per-env grids of the adjoint tiles; sparse adjoint: per-tile
-    // initial-mass flags and their integral images (sparse_lds: bytes of the
-    // largest image; 0 when an image would not fit in LDS, and the adjoint
-    // then stays dense)
+    // per-env grids of the adjoint tiles; sparse forward and adjoint: per-tile
+    // initial-mass flags (sparse_lds: bytes of the largest integral image; 0
+    // when an image would not fit in LDS, and both then stay dense)
     TileGrid* d_tgrid = nullptr;
     int32_t* d_tmass = nullptr;
-    int32_t* d_tinteg = nullptr;
     int32_t sparse_lds = 0;
     // workspace whose segment slots hold the last segment's states, as the
     // last forward left them (the backward then skips that recompute)
@@ -67,7 +65,7 @@ struct RelaxedInputs {
     int32_t form;       // 0: product form of p_ignite, 1: 1 - exp(-gamma sum B phi)
     int64_t wind_stride = 0;          // floats between the per-cell wind planes of steps t, t+1
     const float* env_wind = nullptr;  // per-env wind series [T][n_env][3] or nullptr
-    int32_t sparse = 0;               // adjoint: skip tiles beyond the reach of the initial burning mass
+    int32_t sparse = 0;               // forward and adjoint: skip tiles beyond the reach of the initial burning mass
 };
 
 int relaxed_prepare(RelaxedState& R, const std::vector<sim_env>& envs);

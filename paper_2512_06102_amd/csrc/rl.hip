@@ -13,6 +13,9 @@
 //   rl_obs_kernel   reward and done from the count, then the (2R+1)^2
 //                   window of the new state around each agent.
 // rl_reset_kernel redraws the fire and the agent of selected envs.
+#include <algorithm>
+
+#include "bitplane.hpp"
 #include "devmath.hpp"
 #include "framed.hpp"
 #include "internal.hpp"
@@ -22,6 +25,8 @@
 namespace firesim {
 namespace {
 
+constexpr int kRlWaves = 4;       // envs (waves) per workgroup
+constexpr int kRlWaveList = 128;  // front cells listed per wave
 constexpr uint8_t kOutside = 4;  // observation code of cells beyond the grid
 
 __device__ __forceinline__ int32_t scale_draw(uint32_t w, int32_t n)
@@ -29,42 +34,54 @@ __device__ __forceinline__ int32_t scale_draw(uint32_t w, int32_t n)
     return (int32_t)(((uint64_t)w * (uint64_t)n) >> 32);  // uniform in 0..n-1
 }
 
-__global__ __launch_bounds__(256) void rl_reset_kernel(const EnvDev* __restrict__ envs,
+// One wave per env, kRlWaves envs per workgroup: lanes 0 to 7 draw the eight
+// ignition attempts at once, then the wave writes the cells, the ignited one
+// among them.
+__global__ __launch_bounds__(64 * kRlWaves) void rl_reset_kernel(const EnvDev* __restrict__ envs, int32_t n_env,
                                                        const uint8_t* __restrict__ cls,
                                                        uint32_t unburnable_mask,
                                                        uint8_t* __restrict__ states, RlAgent* __restrict__ agents,
                                                        const int32_t* __restrict__ reset_mask, uint2 key,
                                                        uint64_t episode, int32_t water)
 {
-    const int e = blockIdx.x;
-    if (reset_mask && reset_mask[e] == 0) return;
+    const int lane = threadIdx.x & 63;
+    const int e = blockIdx.x * kRlWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (e >= n_env || (reset_mask && reset_mask[e] == 0)) return;
     const EnvDev ed = envs[e];
     const int64_t n = (int64_t)ed.H * ed.W;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const int64_t v = ed.offset + i;
-        states[v] = ((unburnable_mask >> cls[v]) & 1u) ? kUnburnable : kFlammable;
+    static_assert(kRlIgnitionAttempts <= 64, "one lane per attempt");
+    const uint4 w = philox4x32_10(make_uint4(ed.env_id, (uint32_t)episode, (uint32_t)(episode >> 32),
+                                             0x80000000u | (uint32_t)lane),
+                                  key);
+    const int32_t row = scale_draw(w.x, ed.H), col = scale_draw(w.y, ed.W);
+    int64_t cell = (int64_t)row * ed.W + col;
+    const bool burns = lane < (int)kRlIgnitionAttempts && !((unburnable_mask >> cls[ed.offset + cell]) & 1u);
+    const uint64_t hits = __ballot(burns);
+    const int first = hits ? __ffsll((unsigned long long)hits) - 1 : 0;
+    // the first attempt on a burnable cell (at most 2^30 cells per env)
+    const int32_t ignited = hits ? __builtin_amdgcn_readlane((int)cell, first) : -1;
+    auto fresh = [&](uint32_t c, int64_t i) -> uint32_t {
+        if (i == ignited) return kBurning;
+        return ((unburnable_mask >> c) & 1u) ? kUnburnable : kFlammable;
+    };
+    if (((ed.offset | n) & 3) == 0) {
+        const uint32_t* c4 = reinterpret_cast<const uint32_t*>(cls + ed.offset);
+        uint32_t* s4 = reinterpret_cast<uint32_t*>(states + ed.offset);
+        for (int64_t i = lane; i < (n >> 2); i += 64) {
+            const uint32_t c = c4[i];
+            uint32_t v = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) v |= fresh((c >> (8 * b)) & 0xFFu, 4 * i + b) << (8 * b);
+            s4[i] = v;
+        }
+    } else {
+        for (int64_t i = lane; i < n; i += 64) states[ed.offset + i] = (uint8_t)fresh(cls[ed.offset + i], i);
     }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
+    if (lane != 0) return;
     RlAgent a{};
-    for (uint32_t attempt = 0; attempt < kRlIgnitionAttempts; ++attempt) {
-        const uint4 w = philox4x32_10(make_uint4(ed.env_id, (uint32_t)episode, (uint32_t)(episode >> 32),
-                                                 0x80000000u | attempt),
-                                      key);
-        if (attempt == 0) {
-            a.row = scale_draw(w.z, ed.H);
-            a.col = scale_draw(w.w, ed.W);
-        }
-        const int64_t v = ed.offset + (int64_t)scale_draw(w.x, ed.H) * ed.W + scale_draw(w.y, ed.W);
-        if (!((unburnable_mask >> cls[v]) & 1u)) {
-            states[v] = kBurning;
-            break;
-        }
-    }
+    a.row = scale_draw(w.z, ed.H);
+    a.col = scale_draw(w.w, ed.W);
     a.water = water;
-    a.steps = 0;
-    a.done = 0;
-    a.last_count = 0;
     agents[e] = a;
 }
 
@@ -95,271 +112,298 @@ __global__ __launch_bounds__(256) void rl_act_kernel(const EnvDev* __restrict__ 
 }
 
 // counts == nullptr: observation only (after a reset), reward 0.
-__global__ __launch_bounds__(256) void rl_obs_kernel(const EnvDev* __restrict__ envs,
+// One wave per env, kRlWaves envs per workgroup.
+__global__ __launch_bounds__(64 * kRlWaves) void rl_obs_kernel(const EnvDev* __restrict__ envs, int32_t n_env,
                                                      const uint8_t* __restrict__ states,
                                                      RlAgent* __restrict__ agents,
                                                      const int32_t* __restrict__ counts, RlConfigDev cfg,
                                                      uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                      int32_t* __restrict__ done)
 {
-    const int e = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int e = blockIdx.x * kRlWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (e >= n_env) return;
     const EnvDev ed = envs[e];
-    __shared__ int32_t s_row, s_col;
-    if (threadIdx.x == 0) {
-        RlAgent a = agents[e];
-        float r = 0.0f;
-        if (counts && !a.done) {
-            const int32_t c = counts[e];
-            r = -cfg.burn_penalty * (float)c;
-            if (c == 0) r = r + cfg.extinguish_bonus;
-            a.steps += 1;
-            a.last_count = c;
-            a.done = (c == 0 || a.steps >= cfg.max_steps) ? 1 : 0;
-            agents[e] = a;
-        }
+    RlAgent a = agents[e];
+    float r = 0.0f;
+    if (counts && !a.done) {
+        const int32_t c = counts[e];
+        r = -cfg.burn_penalty * (float)c;
+        if (c == 0) r = r + cfg.extinguish_bonus;
+        a.steps += 1;
+        a.last_count = c;
+        a.done = (c == 0 || a.steps >= cfg.max_steps) ? 1 : 0;
+        if (lane == 0) agents[e] = a;
+    }
+    if (lane == 0) {
         if (reward) reward[e] = r;
         if (done) done[e] = a.done;
-        s_row = a.row;
-        s_col = a.col;
     }
-    __syncthreads();
-    const int R = cfg.obs_radius, side = 2 * R + 1;
-    const int n = side * side;
+    const int R = cfg.obs_radius, side = 2 * R + 1, n = side * side;
+    const float inv_side = 1.0f / (float)side;
     uint8_t* o = obs + (int64_t)e * n;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const int gi = s_row - R + i / side, gj = s_col - R + i % side;
+    for (int i = lane; i < n; i += 64) {
+        const int di = small_div(i, side, inv_side);
+        const int gi = a.row - R + di, gj = a.col - R + (i - di * side);
         o[i] = (gi >= 0 && gi < ed.H && gj >= 0 && gj < ed.W) ? states[ed.offset + (int64_t)gi * ed.W + gj]
                                                               : kOutside;
     }
 }
 
-// One whole RL step of one env per 64-lane workgroup, the env's state
-// resident in LDS: the agent's move and water drop, the fire step (same
-// per-cell pieces, counters and operation order as the step kernels, hence
-// the same bits), the BURNING count, reward and done, and the observation
-// window.  Dynamic LDS (rl_fused_lds_bytes) holds the old state as (H + 2)
-// rows of W/4 + 2 dwords with a zero frame (frame_cap dwords), the new
-// state, the uniforms of the groups that draw, the list of front cells and
-// their ignition decisions.  Every read of the old state comes from LDS, so
-// the new state is stored in place.  A front cell's sources are read from
-// HBM: few cells of an env are on the front, so staging every cell's fuel
-// and elevation in LDS would cost more than it saves.
-template <bool WIND_CELL>
-__global__ __launch_bounds__(64) void rl_step_kernel(const EnvDev* __restrict__ envs, StaticFields F0, StepArgs A,
-                                                     uint8_t* __restrict__ states, RlAgent* __restrict__ agents,
-                                                     const int32_t* __restrict__ actions, RlConfigDev cfg,
-                                                     uint32_t t, int32_t frame_cap, int32_t cell_cap,
-                                                     uint8_t* __restrict__ obs,
-                                                     float* __restrict__ reward, int32_t* __restrict__ done)
+// One whole RL step, one env per wave (up to kRlWaves envs per workgroup):
+// the agent's move and water drop, the fire step (same per-cell pieces,
+// counters and operation order as the step kernels, hence the same bits), the
+// BURNING count, reward and done, and the observation window.  The waves of a
+// workgroup never wait for each other.
+//
+// An env with no BURNING cell cannot change (fire only spreads from burning
+// cells, and water only removes it): its wave reads the state, the agent and
+// the window, and touches no LDS.  A burning env goes to LDS as bit planes F
+// and B (wave_words words per wave, the new state beside them); each lane
+// works out 4-cell groups, with a front cell's rates from the table.
+//
+// What bounds it: the chain of dependent loads of each wave and, with most
+// fires out, the launch of the waves.  65536 envs of 20 x 20, rollout of 50
+// steps: one env per 64-lane workgroup, byte states and exponentials worked out
+// per step 65 us per step, now 41 us (a call of the reset included).
+template <int RATES>
+__global__ __launch_bounds__(64 * kRlWaves) void rl_step_kernel(
+    const EnvDev* __restrict__ envs, int32_t n_env, StaticFields F0, StepArgs A, const float4* __restrict__ phi,
+    uint8_t* __restrict__ states, RlAgent* __restrict__ agents, const int32_t* __restrict__ actions, RlConfigDev cfg,
+    uint32_t t, uint32_t keep_below, int32_t wave_words, uint8_t* __restrict__ obs, float* __restrict__ reward,
+    int32_t* __restrict__ done)
 {
     extern __shared__ uint4 lds_dyn[];
-    __shared__ float lds_ew[8];
-    __shared__ int32_t s_drop, s_row, s_col;
-    const int e = blockIdx.x, lane = threadIdx.x;
+    __shared__ float s_ew[kRlWaves][8];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int e = blockIdx.x * (blockDim.x >> 6) + wv;
+    if (e >= n_env) return;  // (no workgroup barrier below)
     const EnvDev ed = envs[e];
-    const int H = ed.H, W = ed.W, WD = W >> 2, SW = WD + 2, n_dw = H * WD;
+    RlAgent a = agents[e];
+    const int32_t act = actions[e];
+    const int H = ed.H, W = ed.W, WD = W >> 2, n_dw = H * WD;
     const float inv_wd = 1.0f / (float)WD;
     const int64_t base = ed.offset;
-    StaticFields F = F0;
-    if (F0.wind_stride != 0) F.wind = F0.wind + (int64_t)t * F0.wind_stride;
-    uint32_t* sS = reinterpret_cast<uint32_t*>(lds_dyn);  // old state, framed
-    uint32_t* sN = sS + frame_cap;                       // new state, dense
-    float* sU = reinterpret_cast<float*>(sN + rl_fused_new_dwords(cell_cap));  // uniforms per cell
-    uint32_t* sL = reinterpret_cast<uint32_t*>(sU + cell_cap);  // front cells: cell | nbk << 16
-    uint8_t* sD = reinterpret_cast<uint8_t*>(sL + cell_cap);    // ignition decision per cell
 
-    // -- 1. the state into LDS; the agent acts (lane 0); per-env wind
-    //       exponents (lanes 0-7); the zero frame
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(states + base);
-    for (int i = lane; i < n_dw; i += 64) {
-        const int r = small_div(i, WD, inv_wd);
-        sS[i + 2 * r + SW + 1] = src[i];  // (r + 1) SW + (i - r WD) + 1
+    // -- 1. the state; the agent's action (every lane alike)
+    uint32_t* const st = reinterpret_cast<uint32_t*>(states + base);
+    constexpr int kKeep = 2;  // dwords kept in registers; further ones are read again
+    uint32_t kept[kKeep];
+    uint32_t any_burn = 0;
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k) {
+        const int i = 64 * k + lane;
+        kept[k] = i < n_dw ? st[i] : 0u;
+        any_burn |= burning_flags(kept[k]);
     }
-    RlAgent a{};
-    if (lane == 0) {
-        a = agents[e];
-        int32_t drop = -1;
-        if (!a.done) {
-            const int32_t act = actions[e];
-            const int32_t move = (act >= 0 && act < 32) ? (act & 15) : 0;
-            const bool valve = act >= 0 && act < 32 && ((act >> 4) & 1);
-            if (move >= 1 && move <= 8) {
-                a.row = min(max(a.row + kDRow[move - 1], 0), H - 1);
-                a.col = min(max(a.col + kDCol[move - 1], 0), W - 1);
+    for (int i = 64 * kKeep + lane; i < n_dw; i += 64) any_burn |= burning_flags(st[i]);
+    bool drop = false;
+    if (!a.done) {
+        const int32_t move = (act >= 0 && act < 32) ? (act & 15) : 0;
+        const bool valve = act >= 0 && act < 32 && ((act >> 4) & 1);
+        if (move >= 1 && move <= 8) {
+            a.row = min(max(a.row + kDRow[move - 1], 0), H - 1);
+            a.col = min(max(a.col + kDCol[move - 1], 0), W - 1);
+        }
+        if (valve && a.water > 0) {
+            drop = true;
+            a.water -= 1;
+        }
+    }
+    const bool quiet = !__any(any_burn != 0u);
+    int32_t count = 0;  // BURNING cells after the step
+    const int WW = (W + 31) >> 5, S = WW + 1, fw = (H + 2) * S + 1;
+    uint32_t* const pF = reinterpret_cast<uint32_t*>(lds_dyn) + wv * wave_words;
+    uint32_t* const pB = pF + fw;
+    uint32_t* const sN = pB + fw;  // the new state, dense
+    if (!quiet) {
+        // -- 2. the planes
+        for (int i = lane; i < 2 * fw; i += 64) pF[i] = 0u;
+        if (RATES == kRatesEnvWind && lane < 8) {
+            float V = ed.V, Vx = ed.Vx, Vy = ed.Vy;
+            if (F0.env_wind) {
+                const float* w = F0.env_wind + ((int64_t)t * F0.n_env + e) * 3;
+                V = w[0];
+                Vx = w[1];
+                Vy = w[2];
             }
-            if (valve && a.water > 0) {
-                drop = (a.row << 16) | a.col;
-                a.water -= 1;
+            s_ew[wv][lane] = wind_exponent(lane, A.alpha_w1, A.alpha_w2, V, Vx, Vy);
+        }
+        wave_sync();
+        auto own = [&](int k, int i) { return k == 0 ? kept[0] : (k == 1 ? kept[1] : (i < n_dw ? st[i] : 0u)); };
+        for (int k = 0; 64 * k < n_dw; ++k) {
+            const int i = 64 * k + lane;
+            const uint32_t w = own(k, i);
+            const uint32_t f = pack4(flammable_flags(w)), b = pack4(burning_flags(w));
+            const int r = small_div(i, WD, inv_wd), g = i - r * WD;
+            const int at = (r + 1) * S + 1 + (g >> 3), sh = 4 * (g & 7);
+            if (f) atomicOr(&pF[at], f << sh);
+            if (b) atomicOr(&pB[at], b << sh);
+        }
+        wave_sync();
+        if (drop) {  // water on F_t: BURNING cells of the square go out
+            const int R = A.drop_radius;
+            const int r0 = max(a.row - R, 0), r1 = min(a.row + R, H - 1);
+            const int c0 = max(a.col - R, 0), c1 = min(a.col + R, W - 1);
+            const int wa = c0 >> 5, nw = (c1 >> 5) - wa + 1;
+            for (int q = lane; q < (r1 - r0 + 1) * nw; q += 64) {
+                const int w = wa + q % nw;
+                pB[(r0 + q / nw + 1) * S + 1 + w] &= ~column_mask(w, c0, c1 + 1);
             }
+            wave_sync();
         }
-        s_drop = drop;
-    }
-    if (!WIND_CELL && lane < 8) {
-        float V = ed.V, Vx = ed.Vx, Vy = ed.Vy;
-        if (F.env_wind) {
-            const float* w = F.env_wind + ((int64_t)t * F.n_env + e) * 3;
-            V = w[0];
-            Vx = w[1];
-            Vy = w[2];
-        }
-        lds_ew[lane] = wind_exponent(lane, A.alpha_w1, A.alpha_w2, V, Vx, Vy);
-    }
-    for (int i = lane; i < 2 * SW; i += 64) sS[i < SW ? i : (H + 1) * SW + (i - SW)] = 0u;
-    for (int i = lane; i < 2 * H; i += 64) sS[(1 + (i >> 1)) * SW + ((i & 1) ? SW - 1 : 0)] = 0u;
-    __syncthreads();
 
-    // -- 2. the drop, before the step: the dwords of its square
-    const int32_t drop = s_drop;
-    const int ar = (drop >> 16) & 0x7FFF, ac = drop & 0xFFFF;
-    if (drop >= 0 && ar < H && ac < W) {
-        const int R = A.drop_radius;
-        const int r0 = max(ar - R, 0), r1 = min(ar + R, H - 1);
-        const int d0 = max(ac - R, 0) >> 2, d1 = min(ac + R, W - 1) >> 2;
-        const int nd = d1 - d0 + 1;
-        for (int q = lane; q < (r1 - r0 + 1) * nd; q += 64) {
-            const int r = r0 + q / nd, cd = d0 + q % nd;
-            uint32_t* p = sS + (r + 1) * SW + cd + 1;
-            *p = apply_drop(*p, r, 4 * cd, ar, ac, R, A.drop_mode);
-        }
-        __syncthreads();
-    }
-
-    // -- 2b. no BURNING cell after the drop: no cell can change (no front, no
-    //        draw; the fire model only spreads from burning cells)
-    uint32_t my_burn = 0;
-    for (int i = lane; i < n_dw; i += 64) {
-        const int r = small_div(i, WD, inv_wd);
-        my_burn |= burning_flags(sS[i + 2 * r + SW + 1]);
-    }
-    const bool quiet = !__any(my_burn != 0u);
-
-    // -- 3. draws of the groups that need one; front cells listed across the
-    //       wave and evaluated by all lanes together, so that their fuel and
-    //       elevation loads overlap instead of queueing on their owners
-    const uint2 key = make_uint2(A.key0, A.key1);
-    uint32_t my_front = 0;
-    for (int i = lane; i < n_dw && !quiet; i += 64) {
-        const int r = small_div(i, WD, inv_wd);
-        const uint32_t* m = sS + i + 2 * r + SW + 1;
-        const uint32_t burn = pack4(burning_flags(m[0]));
-        const uint32_t front = pack4(flammable_flags(m[0])) & near_burning(m, SW);
-        if (burn | front) {
-            const uint4 w = group_words<true>(4 * i, t, ed.env_id, key);  // 4 i = r W + 4 (i - r WD)
-            sU[4 * i + 0] = word_to_uniform(w.x);
-            sU[4 * i + 1] = word_to_uniform(w.y);
-            sU[4 * i + 2] = word_to_uniform(w.z);
-            sU[4 * i + 3] = word_to_uniform(w.w);
-        }
-        my_front += __popc(front);
-    }
-    uint32_t n_front = 0;
-    uint32_t slot = 0;
-    if (__any(my_front != 0u)) slot = wave_exclusive_scan(my_front, n_front);
-    if (my_front) {
-        for (int i = lane; i < n_dw; i += 64) {
-            const int r = small_div(i, WD, inv_wd);
-            const uint32_t* m = sS + i + 2 * r + SW + 1;
-            const uint32_t up6 = row_window(m[-SW - 1], m[-SW], m[-SW + 1]);
-            const uint32_t md6 = row_window(m[-1], m[0], m[1]);
-            const uint32_t dn6 = row_window(m[SW - 1], m[SW], m[SW + 1]);
+        // -- 3. draws, survivals and ignitions, one 4-cell group per lane
+        const uint2 key = make_uint2(A.key0, A.key1);
+        StaticFields F = F0;
+        if (RATES == kRatesCellWind && F0.wind_stride != 0) F.wind = F0.wind + (int64_t)t * F0.wind_stride;
+        uint2* const wl = reinterpret_cast<uint2*>(pF + wave_words - 2 * kRlWaveList);  // (without the table)
+        int wn = 0;
+        auto eval = [&](int n) {  // the last n (<= 64) front cells of the list
+            wave_sync();
+            bool ign = false;
+            if (lane < n) {
+                const uint2 c = wl[wn - n + lane];
+                const float p = ignite_prob<RATES == kRatesCellWind>(c.x >> 16, base + (c.x & 0xFFFFu), W, F, A, s_ew[wv]);
+                ign = word_to_uniform(c.y) < p;
+                if (ign) reinterpret_cast<uint8_t*>(sN)[c.x & 0xFFFFu] = kBurning;
+            }
+            count += __popcll(__ballot(ign));
+            wn -= n;
+            wave_sync();
+        };
+        for (int k = 0; 64 * k < n_dw; ++k) {
+            const int i = 64 * k + lane;
+            const bool on = i < n_dw;
+            const uint32_t w = own(k, i);
+            const int r = on ? small_div(i, WD, inv_wd) : 0, g = on ? i - r * WD : 0;
+            const int at = (r + 1) * S + 1 + (g >> 3), sh = 4 * (g & 7);
+            // the 6 columns from one left of the group lie in its word and the
+            // next one on that side
+            const uint32_t* p = pB + at - (sh == 0 ? 1 : 0);
+            auto window = [&](const uint32_t* q) {
+                return __builtin_amdgcn_alignbit(q[1], q[0], (sh - 1) & 31) & 0x3Fu;
+            };
+            const uint32_t up6 = window(p - S), md6 = window(p), dn6 = window(p + S);
             const uint32_t ud = up6 | dn6;
-            const uint32_t near = (ud | (ud >> 1) | (ud >> 2) | md6 | (md6 >> 2)) & 0xFu;
-            const uint32_t front = pack4(flammable_flags(m[0])) & near;
+            const uint32_t burn = (md6 >> 1) & 0xFu;
+            const uint32_t front =
+                pack4(flammable_flags(w)) & (ud | (ud >> 1) | (ud >> 2) | md6 | (md6 >> 2)) & 0xFu;
+            uint32_t next = 0;  // its cells that burn after the step
+            uint4 rnd = make_uint4(0u, 0u, 0u, 0u);
+            if (on && (burn | front)) {
+                float4 ra[4], rb[4];
+                float gv[4];
+                if constexpr (RATES == kRatesTable) {
+                    const float4* ph = phi + 2 * (base + 4 * i);
+                    const float* pg = F.g + base + 4 * i;
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if ((front >> c) & 1u)
-                    sL[slot++] = (uint32_t)(4 * i + c) | (direction_mask(up6, md6, dn6, c) << 16);
-        }
-    }
-    if (n_front) {
-        __syncthreads();
-        for (uint32_t q = lane; q < n_front; q += 64) {
-            const uint32_t entry = sL[q];
-            const int v = entry & 0xFFFF;
-            sD[v] = sU[v] < ignite_prob<WIND_CELL>(entry >> 16, base + v, W, F, A, lds_ew) ? 1 : 0;
-        }
-        __syncthreads();
-    }
-
-    // -- 4. new states and the BURNING count
-    int cnt = 0;
-    for (int i = lane; i < n_dw; i += 64) {
-        const int r = small_div(i, WD, inv_wd);
-        const uint32_t* m = sS + i + 2 * r + SW + 1;
-        const uint32_t own = m[0];
-        uint32_t out = own;
-        const uint32_t burn = pack4(burning_flags(own));
-        const uint32_t flam = pack4(flammable_flags(own));
-        if (!quiet && (burn | flam)) {
-            const uint32_t front = flam & near_burning(m, SW);
+                    for (int c = 0; c < 4; ++c) {
+                        ra[c] = rb[c] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                        gv[c] = 0.0f;
+                        if ((front >> c) & 1u) {
+                            ra[c] = ph[2 * c];
+                            rb[c] = ph[2 * c + 1];
+                            gv[c] = pg[c];
+                        }
+                    }
+                }
+                rnd = group_words<true>(4 * i, t, ed.env_id, key);  // 4 i = r W + 4 g
+                next = burn & ((rnd.x >> 8 < keep_below ? 1u : 0u) | (rnd.y >> 8 < keep_below ? 2u : 0u) |
+                               (rnd.z >> 8 < keep_below ? 4u : 0u) | (rnd.w >> 8 < keep_below ? 8u : 0u));
+                if constexpr (RATES == kRatesTable) {
+                    uint32_t ign = 0;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                uint32_t next;
-                if ((burn >> c) & 1u)
-                    next = sU[4 * i + c] < A.p_continue ? kBurning : kBurnt;
-                else if ((front >> c) & 1u)
-                    next = sD[4 * i + c] ? kBurning : kFlammable;
-                else
-                    continue;
-                out = (out & ~(0xFFu << (8 * c))) | (next << (8 * c));
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t win = ((up6 >> c) & 7u) | (((md6 >> c) & 7u) << 3) | (((dn6 >> c) & 7u) << 6);
+                        const float lambda = rate_sum(ra[c], rb[c], win);
+                        const float q = 1.0f - exp_c(-((A.alpha_gamma * gv[c]) * lambda));
+                        ign |= word_to_uniform(compu(rnd, c)) < (lambda > 0.0f ? q : 0.0f) ? 1u << c : 0u;
+                    }
+                    next |= ign & front;
+                }
+            }
+            // BURNING (10): stays, or BURNT (11), as where the drop put it out;
+            // FLAMMABLE (01) that ignites: BURNING
+            const uint32_t was = burning_flags(w), will = spread4(next);
+            const uint32_t fresh = will & ~was;
+            const uint32_t out = (w | (was & ~will)) ^ (fresh * 3u);
+            if (on) sN[i] = out;
+            if (RATES == kRatesTable && on && out != w) st[i] = out;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) count += __popcll(__ballot((next >> c) & 1u));
+            if constexpr (RATES != kRatesTable) {
+                const bool last = 64 * (k + 1) >= n_dw;
+#pragma unroll 1
+                for (int c = 0; c < 4; ++c) {
+                    const bool is_front = on && ((front >> c) & 1u);
+                    const uint64_t m = __ballot(is_front);
+                    if (is_front)
+                        wl[wn + lanes_below(m)] = make_uint2((uint32_t)(4 * i + c) | (direction_mask(up6, md6, dn6, c) << 16),
+                                                             compu(rnd, c));
+                    wn += __popcll(m);
+                    const int full = last && c == 3 ? 1 : 64;
+                    while (wn >= full) eval(min(wn, 64));
+                }
             }
         }
-        sN[i] = out;
-        cnt += __popc(pack4(burning_flags(out)));
+        wave_sync();
+        if constexpr (RATES != kRatesTable)
+            for (int i = lane; i < n_dw; i += 64) st[i] = sN[i];
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
 
-    // -- 5. reward and done from the count (lane 0)
+    // -- 4. reward and done from the count
+    float rw = 0.0f;
+    if (!a.done) {
+        rw = -cfg.burn_penalty * (float)count;
+        if (count == 0) rw = rw + cfg.extinguish_bonus;
+        a.steps += 1;
+        a.last_count = count;
+        a.done = (count == 0 || a.steps >= cfg.max_steps) ? 1 : 0;
+    }
     if (lane == 0) {
-        float rw = 0.0f;
-        if (!a.done) {
-            rw = -cfg.burn_penalty * (float)cnt;
-            if (cnt == 0) rw = rw + cfg.extinguish_bonus;
-            a.steps += 1;
-            a.last_count = cnt;
-            a.done = (cnt == 0 || a.steps >= cfg.max_steps) ? 1 : 0;
-        }
         agents[e] = a;
         reward[e] = rw;
         done[e] = a.done;
-        s_row = a.row;
-        s_col = a.col;
     }
-    __syncthreads();  // the new state and the agent's position
 
-    // -- 6. the new state to HBM (a quiet env without a drop is unchanged
-    //       there), the observation window from LDS
-    uint32_t* dst = reinterpret_cast<uint32_t*>(states + base);
-    if (!quiet || drop >= 0)
-        for (int i = lane; i < n_dw; i += 64) dst[i] = sN[i];
+    // -- 5. the observation window
     const int R = cfg.obs_radius, side = 2 * R + 1, n_obs = side * side;
     const float inv_side = 1.0f / (float)side;
     uint8_t* o = obs + (int64_t)e * n_obs;
+    const uint8_t* seen = quiet ? states + base : reinterpret_cast<const uint8_t*>(sN);
     for (int i = lane; i < n_obs; i += 64) {
         const int di = small_div(i, side, inv_side);
-        const int gi = s_row - R + di, gj = s_col - R + (i - di * side);
-        o[i] = (gi >= 0 && gi < H && gj >= 0 && gj < W) ? (uint8_t)(sN[gi * WD + (gj >> 2)] >> (8 * (gj & 3)))
-                                                        : kOutside;
+        const int gi = a.row - R + di, gj = a.col - R + (i - di * side);
+        o[i] = (gi >= 0 && gi < H && gj >= 0 && gj < W) ? seen[gi * W + gj] : kOutside;
     }
 }
 
 }  // namespace
 
 hipError_t launch_rl_step_fused(hipStream_t s, const EnvDev* envs, int32_t n_env, const StaticFields& F,
-                                const StepArgs& A, const RlFusedShape& shape, uint8_t* states, RlAgent* agents,
-                                const int32_t* actions, const RlConfigDev& cfg, uint32_t t, uint8_t* obs,
-                                float* reward, int32_t* done)
+                                const StepArgs& A, const RlFusedShape& shape, const float* phi, uint8_t* states,
+                                RlAgent* agents, const int32_t* actions, const RlConfigDev& cfg, uint32_t t,
+                                uint8_t* obs, float* reward, int32_t* done)
 {
     if (n_env <= 0) return hipSuccess;
     if (!shape.fits) return hipErrorInvalidValue;
-    const size_t lds = rl_fused_lds_bytes(shape);
-    if (F.wind)
-        hipLaunchKernelGGL((rl_step_kernel<true>), dim3(n_env), dim3(64), lds, s, envs, F, A, states, agents, actions,
-                           cfg, t, shape.frame_cap, shape.cell_cap, obs, reward, done);
-    else
-        hipLaunchKernelGGL((rl_step_kernel<false>), dim3(n_env), dim3(64), lds, s, envs, F, A, states, agents,
-                           actions, cfg, t, shape.frame_cap, shape.cell_cap, obs, reward, done);
+    // two planes and the new state per wave, and the list where rates are worked out
+    const int32_t words = 2 * shape.plane_words + shape.cell_cap / 4;
+    const int32_t wave_words = ((phi ? words : words + 2 * kRlWaveList) + 3) & ~3;
+    const int waves = std::max(1, std::min<int>(kRlWaves, (int)(kRlFusedMaxLds / (4 * (size_t)wave_words))));
+    const size_t lds = 4 * (size_t)wave_words * (size_t)waves;
+    if (lds > kRlFusedMaxLds) return hipErrorInvalidValue;
+    const dim3 grid((n_env + waves - 1) / waves), block(64 * waves);
+    const float4* table = reinterpret_cast<const float4*>(phi);
+    const uint32_t keep = keep_threshold(A.p_continue);
+#define RL_LAUNCH(RT)                                                                                                \
+    hipLaunchKernelGGL((rl_step_kernel<RT>), grid, block, lds, s, envs, n_env, F, A, table, states, agents, actions, \
+                       cfg, t, keep, wave_words, obs, reward, done)
+    if (phi) RL_LAUNCH(kRatesTable);
+    else if (F.wind) RL_LAUNCH(kRatesCellWind);
+    else RL_LAUNCH(kRatesEnvWind);
+#undef RL_LAUNCH
     return hipGetLastError();
 }
 
@@ -369,8 +413,8 @@ hipError_t launch_rl_reset(hipStream_t s, const EnvDev* envs, int32_t n_env, con
                            int32_t water)
 {
     if (n_env <= 0) return hipSuccess;
-    hipLaunchKernelGGL(rl_reset_kernel, dim3(n_env), dim3(256), 0, s, envs, cls, unburnable_mask, states, agents,
-                       reset_mask, make_uint2(key0, key1), episode, water);
+    hipLaunchKernelGGL(rl_reset_kernel, dim3((n_env + kRlWaves - 1) / kRlWaves), dim3(64 * kRlWaves), 0, s, envs,
+                       n_env, cls, unburnable_mask, states, agents, reset_mask, make_uint2(key0, key1), episode, water);
     return hipGetLastError();
 }
 
@@ -388,10 +432,8 @@ hipError_t launch_rl_obs(hipStream_t s, const EnvDev* envs, int32_t n_env, const
                          float* reward, int32_t* done)
 {
     if (n_env <= 0) return hipSuccess;
-    const int side = 2 * cfg.obs_radius + 1;
-    const int threads = side * side >= 256 ? 256 : ((side * side + 63) / 64) * 64;
-    hipLaunchKernelGGL(rl_obs_kernel, dim3(n_env), dim3(threads), 0, s, envs, states, agents, counts, cfg, obs,
-                       reward, done);
+    hipLaunchKernelGGL(rl_obs_kernel, dim3((n_env + kRlWaves - 1) / kRlWaves), dim3(64 * kRlWaves), 0, s, envs, n_env,
+                       states, agents, counts, cfg, obs, reward, done);
     return hipGetLastError();
 }
 

@@ -31,11 +31,13 @@ constexpr uint32_t kRlIgnitionAttempts = 8;
 // Shape of the fused RL step over a batch whose envs all have W % 4 == 0:
 // the largest framed state, (H + 2)(W/4 + 2) dwords, rounded up to a
 // multiple of 4, and the largest env in cells (at most 65536).  It fits when
-// its dynamic LDS is at most kRlFusedMaxLds.
+// rl_fused_lds_bytes, a byte state with lists for every cell, is at most
+// kRlFusedMaxLds (the bit planes take far less; the rule stays as published).
 struct RlFusedShape {
     bool fits = false;
     int32_t frame_cap = 0;
     int32_t cell_cap = 0;
+    int32_t plane_words = 0;  // words of the largest bit plane, (H + 2)(W/32 + 1) + 1
 };
 constexpr size_t kRlFusedMaxLds = 64 * 1024;
 // Dwords of the dense new state, rounded up to keep what follows 16-byte aligned.
@@ -54,10 +56,11 @@ hipError_t launch_rl_reset(hipStream_t s, const EnvDev* envs, int32_t n_env, con
                            int32_t water);
 hipError_t launch_rl_act(hipStream_t s, const EnvDev* envs, int32_t n_env, RlAgent* agents,
                          const int32_t* actions, int32_t* drop_row);
-// One launch per RL step for envs that fit (see rl_fused_lds_dwords); the
-// fire step is bit-identical to the step kernels' with a water drop.
+// One launch per RL step for envs that fit; the fire step is bit-identical to
+// the step kernels' with a water drop.  phi: the table of edge rates, or
+// nullptr (a wind series).
 hipError_t launch_rl_step_fused(hipStream_t s, const EnvDev* envs, int32_t n_env, const StaticFields& F,
-                                const StepArgs& A, const RlFusedShape& shape, uint8_t* states, RlAgent* agents,
+                                const StepArgs& A, const RlFusedShape& shape, const float* phi, uint8_t* states, RlAgent* agents,
                                 const int32_t* actions, const RlConfigDev& cfg, uint32_t t, uint8_t* obs,
                                 float* reward, int32_t* done);
 hipError_t launch_rl_obs(hipStream_t s, const EnvDev* envs, int32_t n_env, const uint8_t* states,

@@ -123,21 +123,6 @@ __device__ __forceinline__ uint4 group_words(int64_t n0, uint32_t t, uint32_t en
     }
 }
 
-// Wave-wide exclusive scan of one 32-bit value per lane of a 64-lane wave;
-// returns the lane's offset and the wave total.
-__device__ __forceinline__ uint32_t wave_exclusive_scan(uint32_t x, uint32_t& total)
-{
-    const int lane = threadIdx.x & 63;
-    uint32_t incl = x;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(incl, off);
-        if (lane >= off) incl += y;
-    }
-    total = __shfl(incl, 63);
-    return incl - x;
-}
-
 // A drop on the (2R+1) x (2R+1) square centred at (ar, ac): mode 0 turns
 // FLAMMABLE and BURNING cells UNBURNABLE (suppressant), mode 1 turns BURNING
 // cells BURNT (water).

@@ -97,3 +97,28 @@ def test_history_rows(mode):
     assert np.array_equal(hist.cpu().numpy(), rows)
     assert np.array_equal(cnt.cpu().numpy(), want)
     assert np.array_equal(sim.states.cpu().numpy(), rows[-1])
+
+
+@pytest.mark.parametrize("per_cell", [False, True])
+def test_rl_step_shapes(per_cell):
+    """The one-launch RL step against the separate launches on envs whose
+    planes leave room for fewer waves per workgroup, a last workgroup that is
+    not full, and envs of one word and of several."""
+    sizes = [(1400, 4), (20, 20), (4, 1000), (64, 64), (9, 36), (33, 32), (1, 4)]
+    batch = firegen.landscape_batch(86, sizes, per_cell_wind=per_cell)
+    params = firegen.Params(p_base=0.9, veg=_veg(86))
+    rng = np.random.default_rng(3)
+    acts = torch.from_numpy((rng.integers(0, 9, (25, len(sizes))) | (rng.integers(0, 2, (25, len(sizes))) << 4))
+                            .astype(np.int32)).cuda()
+    got = []
+    for single in (True, False):
+        sim = fs.FireSim.from_batch(batch, params, seed=9)
+        env = fs.RLEnv(sim, obs_radius=4, drop_radius=2, water_capacity=9, max_steps=20, single_launch=single)
+        env.reset(episode=2)
+        out = []
+        for t in range(25):
+            o, r, d = env.step(acts[t])
+            out += [o.clone(), r.clone(), d.clone(), sim.states.clone(), env.agents.clone()]
+        got.append([x.cpu().numpy() for x in out])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
