@@ -251,8 +251,9 @@ int sim_rl_step(sim_handle* h, const sim_rl_config* cfg, uint8_t* states, sim_rl
 int sim_get_step(const sim_handle* h, uint64_t* t);
 int sim_set_step(sim_handle* h, uint64_t t);
 
-/* Launch plan of sim_step, and of sim_step_relaxed_bwd for `sparse` (results
- * never depend on it, up to the summation order of the relaxed gradient).
+/* Launch plan of sim_step, and of sim_step_relaxed_fwd and _bwd for `sparse`
+ * (results never depend on it, up to the summation order of the relaxed
+ * gradient).
  * A new handle starts with {tile_rows 4, tile_width 64, temporal 1,
  * skip_static 1, sparse 1, graph 0, resident r}: fuel and elevation are read only at
  * front cells and tiles with no fire in reach are skipped.  r is 0 unless
@@ -280,10 +281,12 @@ int sim_set_step(sim_handle* h, uint64_t t);
  *  sparse       1: after the first step of a call, a tile with no burning
  *               cell in it or in its 8 neighbouring tiles, and no drop on it,
  *               is not computed (its cells cannot change); 0: every tile runs.
- *               In sim_step_relaxed_bwd, 1 skips the adjoint step s on tiles
- *               farther than s + 1 cells from every cell with initial burning
- *               mass (B_0 != 0): the parameter gradient is unchanged, since
- *               it only sums terms carrying B_s, which is zero there.
+ *               In sim_step_relaxed_fwd, 1 computes step s only on tiles within
+ *               s + 1 cells of a cell with initial burning mass (B_0 != 0),
+ *               the others keep their state; in sim_step_relaxed_bwd it skips
+ *               adjoint step s on tiles farther than that: the parameter
+ *               gradient is unchanged, since it only sums terms carrying B_s,
+ *               which is zero there.
  *  graph        1: capture the T launches of a call into a HIP graph and
  *               replay it (re-captured when T, the pointers or the plan
  *               change); 0: launch directly

@@ -21,14 +21,14 @@
 // Both directions work on 64 x 32 tiles (kAdjW x kAdjR) whose lanes own
 // columns and walk the rows, passing neighbouring values and terms by DPP
 // lane shifts, so each cell is loaded once per step.  The forward cuts a tile
-// into four 8-row bands, one wave each.  The adjoint's transpose stencil
+// into row bands of one wave each.  The adjoint's transpose stencil
 // (Bbar(u) gathers the terms of the targets around u, and those need B two
-// cells away) runs one wave per tile, one launch per step; terms that cross
-// into another tile go through an exchange record that the owning tile adds
-// in the next step.  Every sum runs in a fixed order (no atomics), so the gradient
-// is the same bits on every run.  Parameter gradients are summed per lane,
-// reduced per wave and added to the tile's own row of partial sums; a last
-// kernel sums the rows.
+// cells away) runs one wave per tile or band, one launch per step; terms that
+// cross into another tile go through an exchange record that the owning tile
+// adds in the next step.  Every sum runs in a fixed order (no atomics), so the
+// gradient is the same bits on every run.  Parameter gradients are summed per
+// lane, reduced per wave and added to the tile's own row of partial sums; a
+// last kernel sums the rows.
 //
 // Precision: the recurrence amplifies small burning mass exponentially (in
 // the mean-field model every region reachable from a burning cell
@@ -115,10 +115,9 @@ __device__ __forceinline__ float2 q_and_survival(float y)
     return y < 0.0625f ? make_float2(qt, 1.0f - qt) : make_float2(1.0f - el, el);
 }
 
-
 // e^{-z} and 1 - e^{-z} in fp64 from one series: z = n ln 2 + r, |r| <= ln 2 / 2
-// (ln 2 split so that n times its head is exact for |n| < 2^20), p = e^{-r} - 1
-// by its Taylor series through r^14 (truncation below 1e-18), then
+// (ln 2 split into its leading 40 bits, whose product with n is exact, and the
+// rest), p = e^{-r} - 1 by its Taylor series through r^14 (truncation below 1e-18), then
 // e^{-z} = 2^{-n} (1 + p) and 1 - e^{-z} = (1 - 2^{-n}) - 2^{-n} p, which keeps
 // its relative accuracy for small z (n = 0).
 struct SurvivalPair {
@@ -126,7 +125,7 @@ struct SurvivalPair {
 };
 __device__ __forceinline__ SurvivalPair survival_pair(double z)
 {
-    constexpr double kLn2Head = 0.693147180369123816490, kLn2Tail = 1.90821492927058770002e-10;
+    constexpr double kLn2Head = 762123384785.0 / 1099511627776.0, kLn2Tail = 7.37100256516779889989e-13;
     z = z > 800.0 ? 800.0 : z;  // 2^-1154 is 0; a NaN stays
     const double n = __builtin_rint(z * 1.44269504088896340736);
     const double x = fma(n, kLn2Tail, fma(n, kLn2Head, -z));  // -r
@@ -261,13 +260,24 @@ __device__ __forceinline__ double from_right_or(double edge, double v)
 __device__ __forceinline__ double from_left0(double v) { return mk64(shr1<true>(0, lo32(v)), shr1<true>(0, hi32(v))); }
 __device__ __forceinline__ double from_right0(double v) { return mk64(shl1<true>(0, lo32(v)), shl1<true>(0, hi32(v))); }
 
-// Sum over the 64 lanes of a wave by xor butterflies (every lane receives the
-// same bits: each level adds the same two values, only their order differs).
+// Sum over the 64 lanes of a wave, returned to every lane: within rows of 16
+// and across them by DPP moves (a butterfly of lane shuffles goes through LDS,
+// 12 round trips per value).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
+{
+    return v + mk64(__builtin_amdgcn_update_dpp(0, lo32(v), CTRL, ROWS, 0xf, false),
+                    __builtin_amdgcn_update_dpp(0, hi32(v), CTRL, ROWS, 0xf, false));
+}
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    v = dpp_add<0x111, 0xf>(v);  // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);  // row_shr:2
+    v = dpp_add<0x114, 0xf>(v);  // row_shr:4
+    v = dpp_add<0x118, 0xf>(v);  // row_shr:8
+    v = dpp_add<0x142, 0xa>(v);  // row_bcast:15
+    v = dpp_add<0x143, 0xc>(v);  // row_bcast:31
+    return mk64(__builtin_amdgcn_readlane(lo32(v), 63), __builtin_amdgcn_readlane(hi32(v), 63));
 }
 
 // A source cell as the adjoint reads it: B, fuel g, elevation E and (per-cell
@@ -298,20 +308,20 @@ __device__ __forceinline__ void st_at(T* base, uint32_t i, T v)
     *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * (uint32_t)sizeof(T)) = v;
 }
 
+// The source cell at offset o, which lies on the grid whatever `in` says: no
+// lane branches, and an off-grid cell gets no fuel and no burning mass (its
+// other values are finite, so all its terms vanish).
 template <bool WC>
 __device__ __forceinline__ AdjCell load_adj_cell(const AdjEnv& P, uint32_t o, bool in)
 {
-    AdjCell c{0.0, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    if (in) {
-        c.B = ld_at(P.B, o);
-        c.g = ld_at(P.g, o);
-        c.E = ld_at(P.E, o);
-        if constexpr (WC) {
-            c.V = ld_at(P.V, o);
-            c.Vx = ld_at(P.Vx, o);
-            c.Vy = ld_at(P.Vy, o);
-        }
+    AdjCell c{ld_at(P.B, o), ld_at(P.g, o), ld_at(P.E, o), 0.0f, 0.0f, 0.0f};
+    if constexpr (WC) {
+        c.V = ld_at(P.V, o);
+        c.Vx = ld_at(P.Vx, o);
+        c.Vy = ld_at(P.Vy, o);
     }
+    c.B = in ? c.B : 0.0;
+    c.g = in ? c.g : 0.0f;
     return c;
 }
 
@@ -350,6 +360,21 @@ template <bool WC>
 __device__ __forceinline__ AdjRow make_row(const AdjCell& x, const AdjCell& ghost)
 {
     return AdjRow{x, left_of<WC>(x, ghost), right_of<WC>(x, ghost)};
+}
+
+// The wind term (cos Vx + sin Vy) - V of direction k at source u, and the
+// exponent of its edge under per-cell wind.  The multiply-adds are written out:
+// a source's products serve three targets, and which of two products fuses
+// would otherwise depend on what else the compiler shares.
+__device__ __forceinline__ float wind_term(int k, const AdjCell& u)
+{
+    const float along = kCos[k] == 1.0f || kCos[k] == -1.0f ? __builtin_fmaf(kSin[k], u.Vy, kCos[k] * u.Vx)
+                                                            : __builtin_fmaf(kCos[k], u.Vx, kSin[k] * u.Vy);
+    return along - u.V;
+}
+__device__ __forceinline__ float cell_wind_exponent(int k, const AdjCell& u, float slope, const RelaxedArgs& A)
+{
+    return __builtin_fmaf(A.alpha_s, slope, __builtin_fmaf(A.alpha_w1, u.V, A.alpha_w2 * wind_term(k, u)));
 }
 
 // Running sums of one source cell: c into Bbar, d into the fuel adjoint.
@@ -425,6 +450,14 @@ __global__ __launch_bounds__(256) void tile_integral_kernel(const TileGrid* __re
     for (int i = threadIdx.x; i < n; i += 256) integ[tg.ioff + i] = sI[i];
 }
 
+// The block of tiles that workgroup b takes.  per_xcd > 0: a contiguous run
+// of that many blocks per XCD (workgroup b runs on XCD b % 8), so that
+// neighbouring tiles meet in its L2; 0: in order.
+__device__ __forceinline__ int dealt_block(uint32_t b, int32_t per_xcd)
+{
+    return per_xcd > 0 ? (int)(b & 7) * per_xcd + (int)(b >> 3) : (int)b;
+}
+
 // Is a tile with initial mass within a bands and b strips of tile (i, j)?
 __device__ __forceinline__ bool adj_tile_in_reach_by(int i, int j, const TileGrid& tg, const int32_t* integ, int a, int b)
 {
@@ -459,12 +492,20 @@ __device__ __forceinline__ bool adj_tile_in_reach(int i, int j, const TileGrid& 
 // SL: slope S = rise / run (0) or atan(rise / run) (1).
 //
 // BANDS: waves per tile.  1: a wave walks the whole tile, four tiles per
-// workgroup.  8: eight waves walk 4 rows each and meet in LDS: the sums that
-// cross a band edge are handed over there, so tiles, exchange records and the
-// workspace are the same.
+// workgroup.  More: the waves walk AR / BANDS rows each and meet in LDS: the
+// sums that cross a band edge are handed over there, so tiles, exchange records
+// and the workspace are the same.
+//
+// What bounds it: VALU issue when every tile runs (its instructions alone take
+// 56 of the 72 us below), else the walk of one wave.  256 envs of 128 x
+// 128: 81 us per step with a shift per term and the rows moved through the
+// window, 72 now; with 8 bands 118, so a full chip keeps 1.  One env of 128 x
+// 128 (8 tiles): 43 us with 1 band, 13 with 8.  2048 x 2048 with per-cell wind,
+// 200 steps, tiles in reach of the fire only: 59 us with 1 band, 41 with 8, 29
+// with 4.
 template <bool WC, int FORM, int SL, int BANDS>
 __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgpu_waves_per_eu(2))) void relaxed_adj_kernel(
-    const RelaxedTile* __restrict__ tiles, int32_t n_tiles, const TileGrid* __restrict__ grids,
+    const RelaxedTile* __restrict__ tiles, int32_t n_tiles, int32_t per_xcd, const TileGrid* __restrict__ grids,
     const EnvDev* __restrict__ envs, const float* __restrict__ g, const float* __restrict__ E,
     const float* __restrict__ wind, const uint8_t* __restrict__ cls, const float* __restrict__ den, int64_t n_cells,
     RelaxedArgs A, const double* __restrict__ U, const double* __restrict__ B, const double* __restrict__ gU1,
@@ -483,7 +524,8 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
     __shared__ double s_sum[BANDS == 1 ? 1 : NW][17];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: tile values in SGPRs
-    const int tix = BANDS == 1 ? (int)blockIdx.x * 4 + wv : (int)blockIdx.x;
+    const int block = dealt_block(blockIdx.x, per_xcd);
+    const int tix = BANDS == 1 ? block * 4 + wv : block;
     if (tix >= n_tiles) return;
     const RelaxedTile td = tiles[tix];
     const TileGrid tg = grids[td.env];
@@ -521,8 +563,11 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
     } else {
         P.V = P.Vx = P.Vy = nullptr;
     }
-    // cell (r, col) of the env; wraps for the row above row 0, which is never read
     auto at = [&](int r, int col) { return (uint32_t)(r * W + col); };
+    // the lane's own and ghost columns, and rows, kept on the grid for the loads of the window
+    const int cc = min(c, W - 1), gc = min(max(cg, 0), W - 1);
+    auto own_cell = [&](int r, bool in) { return load_adj_cell<WC>(P, at(min(max(r, 0), H - 1), cc), act && in); };
+    auto ghost_cell = [&](int r, bool in) { return load_adj_cell<WC>(P, at(min(max(r, 0), H - 1), gc), ghost && in); };
     auto tile_of = [&](int bi, int sj) { return (int64_t)(tg.first + bi * tg.cols + sj) * kXTile; };
     const int64_t xrec = (int64_t)tix * kXTile;
     const int64_t xside = xrec + (lane == 0 ? kXLeft : kXRight) + band * BR;  // ghost entry of the row above the band
@@ -586,12 +631,10 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
         // the window of source rows r - 1 (a), r (m), r + 1 (b): R0 to R2 in turn
         // (three rows of the walk per loop pass, so that no row is ever moved);
         // the row after it is on its way in nX (own column) and nG (ghost column)
-        AdjRow R0 = make_row<WC>(load_adj_cell<WC>(P, at(r0 - 1, c), act && r0 > 0),
-                                 load_adj_cell<WC>(P, at(r0 - 1, cg), ghost && r0 > 0));
-        AdjRow R1 = make_row<WC>(load_adj_cell<WC>(P, at(r0, c), act), load_adj_cell<WC>(P, at(r0, cg), ghost));
+        AdjRow R0 = make_row<WC>(own_cell(r0 - 1, r0 > 0), ghost_cell(r0 - 1, r0 > 0));
+        AdjRow R1 = make_row<WC>(own_cell(r0, true), ghost_cell(r0, true));
         AdjRow R2;
-        AdjCell nX = load_adj_cell<WC>(P, at(r0 + 1, c), act && r0 + 1 < H);
-        AdjCell nG = load_adj_cell<WC>(P, at(r0 + 1, cg), ghost && r0 + 1 < H);
+        AdjCell nX = own_cell(r0 + 1, r0 + 1 < H), nG = ghost_cell(r0 + 1, r0 + 1 < H);
         RowSums S0{}, S1{}, S2{};
         double gB_prev = 0.0;
 
@@ -647,8 +690,8 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
             }
             // next window row (r + 2)
             const bool more = i + 1 < rows && r + 2 < H;
-            nX = load_adj_cell<WC>(P, at(r + 2, c), act && more);
-            nG = load_adj_cell<WC>(P, at(r + 2, cg), ghost && more);
+            nX = own_cell(r + 2, more);
+            nG = ghost_cell(r + 2, more);
 
             // ---- the target v = (r, c); its source in direction k is u_k = v - D_k
             const AdjCell* const src[8] = {&m.L, &b.L, &b.X, &b.R, &m.R, &a.R, &a.X, &a.L};
@@ -662,7 +705,7 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
             const float gam = A.alpha_gamma * gv, gpe = gp * gv;  // gamma(v), gamma(v) p_base
             const double gam64 = gam;
             // per-cell wind: the wind term (cos Vx + sin Vy) - V of direction k at the source
-            auto wterm = [&](int k) -> float { return (kCos[k] * src[k]->Vx + kSin[k] * src[k]->Vy) - src[k]->V; };
+            auto wterm = [&](int k) { return wind_term(k, *src[k]); };
             auto slope_k = [&](int k) {
                 const float rr = (Ev - src[k]->E) * ((k & 1) ? A.inv_diag : A.inv_orth);
                 return SL ? atanf(rr) : rr;
@@ -672,11 +715,11 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
             for (int k = 0; k < 8; ++k) {
                 // the exponent sums onto the slope term first, so that the
                 // per-env wind constants are not kept per direction
-                float x = A.alpha_s * slope_k(k);
+                float x;
                 if constexpr (WC) {
-                    x = x + (A.alpha_w1 * src[k]->V + A.alpha_w2 * wterm(k));
+                    x = cell_wind_exponent(k, *src[k], slope_k(k), A);
                 } else {
-                    x = x + wA0;
+                    x = A.alpha_s * slope_k(k) + wA0;
                     if (kCos[k] != 0.0f) x = x + kCos[k] * wA1;
                     if (kSin[k] != 0.0f) x = x + kSin[k] * wA2;
                 }
@@ -716,7 +759,12 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
                 for (int k = 0; k < 8; ++k) om[k] = 1.0 - (double)q[k] * sB(k);
                 const double p01 = om[0] * om[1], p23 = om[2] * om[3], p45 = om[4] * om[5], p67 = om[6] * om[7];
                 const double lo = p01 * p23, hi = p45 * p67;
-                Pv = 1.0 - lo * hi;
+                // P's own product runs in the forward's order: where the burning
+                // mass is below 1e-16 its rounding is all there is to P
+                double run = 1.0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) run = run * om[k];
+                Pv = 1.0 - run;
                 const double plo = Pbar * lo, phi = Pbar * hi;
                 const double e[4] = {p23 * phi, p01 * phi, p67 * plo, p45 * plo};
 #pragma unroll
@@ -784,7 +832,6 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
                 if (act) st_at(P.gB0, v - W, p_c * gB_prev + own.c);
                 if (ghost) Xout[xside + i] = gh.c;
             }
-            Sa = RowSums{};
             gB_prev = gB;
         };
         int i = 0;
@@ -815,11 +862,11 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
             const bool on = act, gon = ghost;
             const uint32_t cl = on ? (uint32_t)ld_at(P.cls, at(rl + 1, c)) : 0u;
             const float dn = on ? ld_at(P.den, at(rl + 1, c)) : 0.0f;
-            const uint32_t gc = gon ? (uint32_t)ld_at(P.cls, at(rl + 1, cg)) : 0u;
+            const uint32_t gcl_b = gon ? (uint32_t)ld_at(P.cls, at(rl + 1, cg)) : 0u;
             const float gd = gon ? ld_at(P.den, at(rl + 1, cg)) : 0.0f;
             const CD bo = column(sb), bg = ghost_of(sb);
             veg_add(bo.d, cl, dn, on);
-            veg_add(bg.d, gc, gd, gon);
+            veg_add(bg.d, gcl_b, gd, gon);
             if (!last_band) {
                 s_down[wv][lane] = bo.c;
                 if (lane == 0 || lane == 63) s_down_ghost[wv][lane == 63] = bg.c;
@@ -901,6 +948,11 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
 // exp(-gamma sum_k B_k phi_k).  Rows where no lane sees burning mass skip the
 // edge terms (P = 0 exactly there).
 //
+// What bounds it: memory, at the rate of a copy, when every tile runs (256 envs
+// of 128 x 128: 38 us per step at 40 bytes per cell); 2048 x 2048 with per-cell
+// wind took 42 us per step with every tile and takes 13 with those in reach
+// over 200 steps; one env of 128 x 128 8 us with 8-row bands, 4.5 with 2 rows.
+//
 // Sparse (reach given): after t steps burning mass lies within t cells of the
 // cells that hold it at the start (S_0).  Step t runs on the tiles within
 // reach, fills the tiles one further out with the initial state (U_0, 0), which
@@ -908,7 +960,7 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
 // adjoint of step t + 1, read only tiles within reach and their neighbours.
 template <bool WC, int FORM, int SL, int SPLIT>
 __global__ __launch_bounds__(256) void relaxed_fwd_kernel(
-    const RelaxedTile* __restrict__ tiles, int32_t n_tiles, const TileGrid* __restrict__ grids,
+    const RelaxedTile* __restrict__ tiles, int32_t n_tiles, int32_t per_xcd, const TileGrid* __restrict__ grids,
     const EnvDev* __restrict__ envs, const float* __restrict__ g, const float* __restrict__ E,
     const float* __restrict__ wind, int64_t n_cells, RelaxedArgs A, const double* __restrict__ U,
     const double* __restrict__ B, double* __restrict__ Uo, double* __restrict__ Bo,
@@ -917,7 +969,7 @@ __global__ __launch_bounds__(256) void relaxed_fwd_kernel(
     constexpr int BR = AR / SPLIT;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wix = (int)blockIdx.x * 4 + wv;
+    const int wix = dealt_block(blockIdx.x, per_xcd) * 4 + wv;
     if (wix >= n_tiles * SPLIT) return;
     const RelaxedTile td = tiles[wix / SPLIT];
     const EnvDev ed = envs[td.env];
@@ -960,18 +1012,20 @@ __global__ __launch_bounds__(256) void relaxed_fwd_kernel(
     const float wA0 = (A.alpha_w1 - A.alpha_w2) * wenv.x, wA1 = A.alpha_w2 * wenv.y, wA2 = A.alpha_w2 * wenv.z;
     const double p_c = A.p_continue;
 
+    const int cc = min(c, W - 1), gc = min(max(cg, 0), W - 1);
+    auto own_cell = [&](int r, bool in) { return load_adj_cell<WC>(P, at(min(max(r, 0), H - 1), cc), act && in); };
+    auto ghost_cell = [&](int r, bool in) { return load_adj_cell<WC>(P, at(min(max(r, 0), H - 1), gc), ghost && in); };
     // the window as in the adjoint; n0 to n2: does the row hold burning mass
     auto holds = [&](const AdjCell& x, const AdjCell& gh) { return __any(x.B != 0.0 || gh.B != 0.0) != 0; };
-    AdjCell nX = load_adj_cell<WC>(P, at(r0 - 1, c), act && r0 > 0);
-    AdjCell nG = load_adj_cell<WC>(P, at(r0 - 1, cg), ghost && r0 > 0);
+    AdjCell nX = own_cell(r0 - 1, r0 > 0), nG = ghost_cell(r0 - 1, r0 > 0);
     AdjRow R0 = make_row<WC>(nX, nG), R1, R2;
     bool n0 = holds(nX, nG), n1, n2 = false;
-    nX = load_adj_cell<WC>(P, at(r0, c), act);
-    nG = load_adj_cell<WC>(P, at(r0, cg), ghost);
+    nX = own_cell(r0, true);
+    nG = ghost_cell(r0, true);
     R1 = make_row<WC>(nX, nG);
     n1 = holds(nX, nG);
-    nX = load_adj_cell<WC>(P, at(r0 + 1, c), act && r0 + 1 < H);
-    nG = load_adj_cell<WC>(P, at(r0 + 1, cg), ghost && r0 + 1 < H);
+    nX = own_cell(r0 + 1, r0 + 1 < H);
+    nG = ghost_cell(r0 + 1, r0 + 1 < H);
     double nU = act ? ld_at(P.U, at(r0, c)) : 0.0;
 
     auto walk = [&](const AdjRow& a, const AdjRow& m, AdjRow& b, bool na, bool nm, bool& nb, int i) {
@@ -982,35 +1036,37 @@ __global__ __launch_bounds__(256) void relaxed_fwd_kernel(
         const double Uv = nU;
         if (act && i + 1 < rows) nU = ld_at(P.U, v + W);
         const bool more = i + 1 < rows && r + 2 < H;
-        nX = load_adj_cell<WC>(P, at(r + 2, c), act && more);
-        nG = load_adj_cell<WC>(P, at(r + 2, cg), ghost && more);
+        nX = own_cell(r + 2, more);
+        nG = ghost_cell(r + 2, more);
 
         double Pv = 0.0;
         if (na || nm || nb) {  // wave-uniform
             const AdjCell* const src[8] = {&m.L, &b.L, &b.X, &b.R, &m.R, &a.R, &a.X, &a.L};
             const float Ev = m.X.E, gam = A.alpha_gamma * m.X.g;
-            double om[8], lam = 0.0;
+            // (the product in ascending order, one factor at a time: where the
+            // burning mass is below 1e-16 its rounding is all there is to P)
+            double prod = 1.0, lam = 0.0;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const AdjCell& u = *src[k];
                 const float rr = (Ev - u.E) * ((k & 1) ? A.inv_diag : A.inv_orth);
-                float x = A.alpha_s * (SL ? atanf(rr) : rr);
+                float x;
                 if constexpr (WC) {
-                    x = x + (A.alpha_w1 * u.V + A.alpha_w2 * ((kCos[k] * u.Vx + kSin[k] * u.Vy) - u.V));
+                    x = cell_wind_exponent(k, u, SL ? atanf(rr) : rr, A);
                 } else {
-                    x = x + wA0;
+                    x = A.alpha_s * (SL ? atanf(rr) : rr) + wA0;
                     if (kCos[k] != 0.0f) x = x + kCos[k] * wA1;
                     if (kSin[k] != 0.0f) x = x + kSin[k] * wA2;
                 }
                 // off-grid sources read 0: no fuel, no burning mass
                 const float phi = A.p_base * (u.g * hexp(fminf(x, 88.0f)));
                 if constexpr (FORM == 0)
-                    om[k] = 1.0 - (double)one_minus_exp_neg(gam * phi) * u.B;
+                    prod = prod * (1.0 - (double)one_minus_exp_neg(gam * phi) * u.B);
                 else
                     lam = lam + (double)phi * u.B;
             }
             if constexpr (FORM == 0)
-                Pv = 1.0 - ((om[0] * om[1]) * (om[2] * om[3])) * ((om[4] * om[5]) * (om[6] * om[7]));
+                Pv = 1.0 - prod;
             else
                 Pv = survival_pair((double)gam * lam).p;
         }
@@ -1046,7 +1102,7 @@ __global__ __launch_bounds__(256) void gsum_reduce_kernel(const double* __restri
 }
 // ---------------------------------------------------------------- losses
 // Every reduction below runs in a fixed order (lane-strided partial sums,
-// xor butterflies, then the four wave sums in order), so the losses, the
+// DPP sums within a wave, then the four wave sums in order), so the losses, the
 // objective and the seed are the same bits on every call.
 
 // Sum over a 256-lane workgroup, returned to every lane.
@@ -1291,9 +1347,10 @@ WsLayout layout(int64_t n, int64_t n_adj_tiles, int32_t T, int32_t k)
     o = align256(o + sizeof(double) * 2 * (size_t)n_adj_tiles * kXTile);
     L.gsum = o;  // 17 gradient partial sums per adjoint tile
     o = align256(o + sizeof(double) * 17 * (size_t)n_adj_tiles);
-    // the head and the envs' integral images: (rows + 1)(cols + 1) <= 4 rows cols entries each
+    // the head, the envs' integral images ((rows + 1)(cols + 1) <= 4 rows cols
+    // entries each) and the tiles' flags
     L.reach = o;
-    o = align256(o + sizeof(int32_t) * (kReachHead + 4 * (size_t)n_adj_tiles));
+    o = align256(o + sizeof(int32_t) * (kReachHead + 5 * (size_t)n_adj_tiles));
     L.total = o;
     return L;
 }
@@ -1317,10 +1374,24 @@ RelaxedInputs at_step(const RelaxedInputs& in, int32_t t)
     return r;
 }
 
-// Row bands per tile: where the tiles alone leave the chip idle, a step lasts
-// as long as one wave's walk, so more waves walk fewer rows each.
-constexpr int kFwdBands = 4, kFwdBandsFew = 16, kAdjBandsFew = 8;
+// Row bands per tile: where the tiles alone (or those in reach of the fire)
+// leave the chip idle, a step lasts as long as one wave's walk, so more waves
+// walk fewer rows each (both sides measured at the kernels).
+constexpr int kFwdBands = 4, kFwdBandsFew = 16, kAdjBandsFew = 8, kAdjBandsPart = 4;
 constexpr int kFewTiles = 1024;
+
+// Do only some of the tiles run in most steps: large envs under a sparse plan?
+bool partly_active(const RelaxedInputs& in, const RelaxedState& R)
+{
+    return in.sparse && R.sparse_lds > 0 && in.n_tiles >= 64 * in.n_env;
+}
+// Blocks per XCD (0: deal them in order).  In runs per XCD a forward step of 256 envs
+// of 128 x 128 takes 37.1 us, in order 38.8; where the fire decides which tiles
+// run, they would leave most XCDs idle.
+int32_t blocks_per_xcd(const RelaxedInputs& in, const RelaxedState& R, int32_t blocks)
+{
+    return partly_active(in, R) ? 0 : (blocks + 7) / 8;
+}
 
 template <bool WC, int FORM, int SL>
 void launch_fwd(hipStream_t s, const RelaxedInputs& in, const RelaxedState& R, const RelaxedArgs& A, const float* g,
@@ -1330,7 +1401,8 @@ void launch_fwd(hipStream_t s, const RelaxedInputs& in, const RelaxedState& R, c
     const bool few = in.n_tiles < kFewTiles;
     auto kernel = few ? relaxed_fwd_kernel<WC, FORM, SL, kFwdBandsFew> : relaxed_fwd_kernel<WC, FORM, SL, kFwdBands>;
     const int32_t groups = (in.n_tiles * (few ? kFwdBandsFew : kFwdBands) + 3) / 4;
-    hipLaunchKernelGGL(kernel, dim3(groups), dim3(256), 0, s, in.tiles, in.n_tiles, R.d_tgrid, in.envs, g, in.E,
+    const int32_t per_xcd = blocks_per_xcd(in, R, groups);
+    hipLaunchKernelGGL(kernel, dim3(per_xcd ? 8 * per_xcd : groups), dim3(256), 0, s, in.tiles, in.n_tiles, per_xcd, R.d_tgrid, in.envs, g, in.E,
                        in.wind, in.n_cells, A, U, B, Uo, Bo, in.env_wind, reach, U_0, step);
 }
 
@@ -1365,10 +1437,14 @@ void launch_adj(hipStream_t s, const RelaxedInputs& in, const RelaxedState& R, c
                 double* gU0, double* gB0, const double* Xin, double* Xout, double* gsum, const int32_t* reach,
                 int32_t step)
 {
-    const bool few = R.n_btiles < kFewTiles;
-    auto kernel = few ? relaxed_adj_kernel<WC, FORM, SL, kAdjBandsFew> : relaxed_adj_kernel<WC, FORM, SL, 1>;
-    hipLaunchKernelGGL(kernel, dim3(few ? R.n_btiles : (R.n_btiles + 3) / 4), dim3(few ? 64 * kAdjBandsFew : 256), 0, s,
-                       R.d_btiles, R.n_btiles, R.d_tgrid, in.envs, g, in.E, in.wind, in.cls, in.den, in.n_cells, A, U,
+    const int bands = R.n_btiles < kFewTiles ? kAdjBandsFew : (partly_active(in, R) ? kAdjBandsPart : 1);
+    auto kernel = bands == kAdjBandsFew    ? relaxed_adj_kernel<WC, FORM, SL, kAdjBandsFew>
+                  : bands == kAdjBandsPart ? relaxed_adj_kernel<WC, FORM, SL, kAdjBandsPart>
+                                           : relaxed_adj_kernel<WC, FORM, SL, 1>;
+    const int32_t blocks = bands > 1 ? R.n_btiles : (R.n_btiles + 3) / 4;
+    const int32_t per_xcd = blocks_per_xcd(in, R, blocks);
+    hipLaunchKernelGGL(kernel, dim3(per_xcd ? 8 * per_xcd : blocks), dim3(bands > 1 ? 64 * bands : 256), 0, s,
+                       R.d_btiles, R.n_btiles, per_xcd, R.d_tgrid, in.envs, g, in.E, in.wind, in.cls, in.den, in.n_cells, A, U,
                        B, gU1, gB1, gU0, gB0, Xin, Xout, gsum, in.env_wind, reach, in.sparse, step);
 }
 
@@ -1405,10 +1481,7 @@ int relaxed_prepare(RelaxedState& R, const std::vector<sim_env>& envs)
         return -1;
     R.n_btiles = (int32_t)btiles.size();
     R.n_env = (int32_t)envs.size();
-    if (ioff < INT32_MAX && 4 * max_img <= 64 * 1024) {
-        if (hipMalloc(&R.d_tmass, btiles.size() * sizeof(int32_t)) != hipSuccess) return -1;
-        R.sparse_lds = (int32_t)(4 * max_img);
-    }
+    if (ioff < INT32_MAX && 4 * max_img <= 64 * 1024) R.sparse_lds = (int32_t)(4 * max_img);
     return 0;
 }
 
@@ -1447,8 +1520,7 @@ int relaxed_prepare_pool(RelaxedState& R, const std::vector<sim_env>& envs, int 
 void relaxed_free(RelaxedState& R)
 {
     for (void* p : {(void*)R.d_btiles, (void*)R.d_pool,
-                    (void*)R.d_env_blocks, (void*)R.d_pool_vals, (void*)R.d_bce_loss, (void*)R.d_tgrid,
-                    (void*)R.d_tmass})
+                    (void*)R.d_env_blocks, (void*)R.d_pool_vals, (void*)R.d_bce_loss, (void*)R.d_tgrid})
         if (p) (void)hipFree(p);
     R = RelaxedState{};
 }
@@ -1491,10 +1563,11 @@ hipError_t relaxed_forward(hipStream_t s, const RelaxedInputs& in, const sim_par
     const int32_t* reach = nullptr;
     if (R.sparse_lds > 0 && e == hipSuccess) {
         int32_t* r = reinterpret_cast<int32_t*>(ws + L.reach);
+        int32_t* mass = r + kReachHead + 4 * (size_t)R.n_btiles;
         hipLaunchKernelGGL(tile_mass_kernel, dim3(R.n_btiles), dim3(256), 0, s, R.d_btiles, in.envs, ckpt + n,
-                           R.d_tmass);
+                           mass);
         hipLaunchKernelGGL(tile_integral_kernel, dim3(R.n_env), dim3(256), (size_t)R.sparse_lds, s, R.d_tgrid,
-                           R.d_tmass, in.sparse ? 1 : 0, r);
+                           mass, in.sparse ? 1 : 0, r);
         e = hipGetLastError();
         reach = r;
     }

@@ -41,11 +41,10 @@ struct RelaxedState {
     int32_t* d_env_blocks = nullptr;  // [n_env][2]: first block, number of blocks
     double* d_pool_vals = nullptr;    // [4][n_pool]: block means of S and Y, BCE sum, squared error
     double* d_bce_loss = nullptr;     // [n_env]: per-env loss in fp64
-    // per-env grids of the adjoint tiles; sparse forward and adjoint: per-tile
-    // initial-mass flags (sparse_lds: bytes of the largest integral image; 0
-    // when an image would not fit in LDS, and both then stay dense)
+    // per-env grids of the tiles; sparse_lds: bytes of the largest integral
+    // image of the initial mass (0 when one would not fit in LDS: the forward and
+    // the adjoint then stay dense)
     TileGrid* d_tgrid = nullptr;
-    int32_t* d_tmass = nullptr;
     int32_t sparse_lds = 0;
     // workspace whose segment slots hold the last segment's states, as the
     // last forward left them (the backward then skips that recompute)
