@@ -364,6 +364,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
         // strips of one row have a scan of their own: it reads 3 rows, not 6
         auto scan = [&](auto rows_at_once) {
             constexpr int ROWS = decltype(rows_at_once)::value;
+            const int rs = n_strips * S;
             for (int w0 = 0; w0 < WW; w0 += w_step)
                 for (int j = 0; j < per; j += ROWS) {
                     // a lane's word column and rows ra, ra + n_strips, ...: a
@@ -372,6 +373,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
                     // groups while the others wait, 2900 of 11500 cycles)
                     const int cw = w0 + my_w, ra = lo + my_strip + j * n_strips;
                     if (my_strip >= n_strips || cw >= WW || ra >= hi) continue;
+                    const int at0 = (ra + 1) * S + 1 + cw;
                     uint32_t m[ROWS], h[ROWS], f[ROWS];
                     int at[ROWS];
                     auto reach = [&](const uint32_t* p, uint32_t& mid) {
@@ -382,7 +384,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
                     };
 #pragma unroll
                     for (int q = 0; q < ROWS; ++q) {
-                        at[q] = (min(ra + q * n_strips, RH - 1) + 1) * S + 1 + cw;
+                        at[q] = ra + q * n_strips < hi ? at0 + q * rs : at0;
                         const uint32_t* p = cur + at[q];
                         uint32_t above, below;
                         h[q] = reach(p - S, above) | reach(p, m[q]) | reach(p + S, below);
@@ -401,13 +403,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
                         todo |= (in ? nz : 0u) << q;
                     }
                     if (todo == 0u) continue;
-                    uint32_t slot = lds_add(&s_n[s & 1], (uint32_t)__popc(todo));
+                    const uint32_t n = (uint32_t)__popc(todo);
+                    const uint32_t slot = lds_add(&s_n[s & 1], n);
+                    if (slot + n > (uint32_t)K.list_cap) continue;  // (a list that overflows is not read)
                     const uint32_t id0 = ((uint32_t)ra << gshift) | (uint32_t)(8 * cw);
                     const uint32_t id_row = (uint32_t)n_strips << gshift;
+                    uint16_t* put = list + slot;
                     for (; todo; todo &= todo - 1) {
                         const uint32_t bit = (uint32_t)__ffs(todo) - 1u;
-                        if (slot < (uint32_t)K.list_cap) list[slot] = (uint16_t)(id0 + (bit & 3u) * id_row + (bit >> 2));
-                        ++slot;
+                        *put++ = (uint16_t)(id0 + (bit & 3u) * id_row + (bit >> 2));
                     }
                 }
         };

@@ -43,8 +43,8 @@ inline bool plane_indexable(int64_t rows, int64_t cols)
     while ((int64_t{1} << shift) < 8 * ((cols + 31) / 32)) ++shift;
     return (rows << shift) <= 65536;
 }
-// Listed 4-cell groups of a region (further groups are worked out by the lane
-// that finds them): an eighth of them, at least 256 and at most 4096.
+// Listed 4-cell groups of a region (with more found, every group of the rows
+// is looked at): an eighth of them, at least 256 and at most 4096.
 inline int32_t plane_list_cap(int64_t rows, int64_t cols)
 {
     const int64_t groups = rows * ((cols + 3) / 4);
