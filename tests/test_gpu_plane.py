@@ -122,3 +122,32 @@ def test_rl_step_shapes(per_cell):
         got.append([x.cpu().numpy() for x in out])
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("mode", [None, 0])
+def test_launches_beside_each_other(mode, graph):
+    """Envs of two kinds, which step beside each other, on a stream of the
+    caller's: calls of few and of many steps without a wait in between (with
+    `graph`, from captures, where they step in order)."""
+    splits = (3, 4, 5, 4, 30)
+    batch = firegen.landscape_batch(87, [(700, 640), (65, 129), (40, 33)], ign_range=(40, 40))
+    params = firegen.Params(p_base=1.0, p_continue=0.7, veg=_veg(87))
+    act = None if mode is None else firegen.random_actions(43, batch, sum(splits), p_none=0.3)
+    ref = oracle.Sim(batch, params, seed=8)
+    want = ref.step(sum(splits), actions=act, counts=True, threads=8, drop_mode=0, drop_radius=3)
+    sim = fs.FireSim.from_batch(batch, params, seed=8)
+    sim.set_plan(**PLAN, graph=graph)
+    sim.set_drop(0, 3)
+    acts = None if act is None else torch.from_numpy(act).cuda()
+    got, t = [], 0
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        for n in splits:
+            got.append(sim.step(n, actions=None if acts is None else acts[t:t + n], counts=True).clone())
+            t += n
+        states = sim.states.clone()
+    stream.synchronize()
+    assert np.array_equal(states.cpu().numpy(), ref.states)
+    assert np.array_equal(torch.cat(got).cpu().numpy(), want)
