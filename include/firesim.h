@@ -290,19 +290,25 @@ int sim_set_step(sim_handle* h, uint64_t t);
  *  graph        1: capture the T launches of a call into a HIP graph and
  *               replay it (re-captured when T, the pointers or the plan
  *               change); 0: launch directly
- *  resident     0: off; 64, 256, 512 or 1024: sim_step runs all T steps
- *               of a call in ONE launch, one workgroup of that many lanes per
- *               env holding the env's state, fuel and elevation in LDS for
- *               the whole call (per-cell wind read from HBM at front cells),
- *               with results bit-identical to the other plans.  For batches
- *               of small envs: needs W % 4 == 0 and offset % 4 == 0 in every
- *               env, at most 65536 cells and (H + 2)(W/4 + 2) 8 + 16 H W
- *               bytes of LDS per env within the device's LDS per workgroup
- *               less 2.5 KiB (160 KiB on MI355X: up to 92 x 92; a 64 x 64
- *               env takes 75040), and temporal 1 (else SIM_EINVAL); tile_rows, tile_width and skip_static are then
- *               unused by the stochastic step (sparse still applies to
- *               sim_step_relaxed_bwd).  sim_step_history runs it one step per
- *               launch. */
+ *  resident     0: off; 64, 256, 512 or 1024: sim_step and sim_step_history
+ *               run all T steps of a call in ONE launch, one workgroup of that
+ *               many lanes per env holding the env's state in LDS for the
+ *               whole call, with results bit-identical to the other plans.
+ *               Needs W % 4 == 0 and offset % 4 == 0 in every env, at most
+ *               65536 cells and (H + 2)(W/4 + 2) 8 + 16 H W no more than the
+ *               device's LDS per workgroup less 2.5 KiB (160 KiB on MI355X:
+ *               up to 92 x 92), and temporal 1 (else SIM_EINVAL); tile_rows,
+ *               tile_width and skip_static are then unused by the stochastic
+ *               step (sparse still applies to the relaxed step).
+ * With resident 0, skip_static 1, sparse 1 and temporal 1 the same kernel runs
+ * with workgroup sizes of its own choice, for envs of any size: those whose
+ * state does not fit LDS as bits are cut into parts that take up to 24 steps
+ * per launch (their sim_step_history runs one step per launch).  Envs of
+ * different sizes are launches of their own, which outside captures run
+ * beside each other on a stream of the handle's; the caller's stream waits
+ * for it.  sim_init builds a table of the ignition rates of every edge, 32
+ * bytes per cell, for it when that takes at most a quarter of the free device
+ * memory; without it the rates are worked out in the step. */
 typedef struct {
     int32_t tile_rows, tile_width, temporal, skip_static, sparse, graph, resident;
 } sim_plan;
