@@ -39,6 +39,7 @@
 // exponential (relative error ~1e-6 for |x| < 20), with q from its Taylor
 // series below y = 1/16 so that small rates keep their relative accuracy.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <vector>
 
@@ -405,19 +406,24 @@ __device__ __forceinline__ CD cd_from_right(CD a) { return CD{from_right0(a.c), 
 // start at zero) only ever meets B = 0 in the gradient sums, so only the
 // parameter gradient is returned.
 //
-// tile_mass_kernel flags the adjoint tiles holding initial burning mass;
+// tile_mass_kernel flags the adjoint tiles holding initial burning mass (or a
+// U that is not finite);
 // tile_integral_kernel builds each env's integral image of the flags (one
 // workgroup per env, in LDS).
 __global__ __launch_bounds__(256) void tile_mass_kernel(const RelaxedTile* __restrict__ tiles,
                                                         const EnvDev* __restrict__ envs,
-                                                        const double* __restrict__ B, int32_t* __restrict__ mass)
+                                                        const double* __restrict__ U, const double* __restrict__ B,
+                                                        int32_t* __restrict__ mass)
 {
     const RelaxedTile td = tiles[blockIdx.x];
     const EnvDev ed = envs[td.env];
     int any = 0;
     for (int idx = threadIdx.x; idx < AW * AR; idx += 256) {
         const int gi = td.r0 + idx / AW, gj = td.c0 + idx % AW;
-        if (gi < ed.H && gj < ed.W && B[ed.offset + (int64_t)gi * ed.W + gj] != 0.0) any = 1;
+        if (gi >= ed.H || gj >= ed.W) continue;
+        const int64_t i = ed.offset + (int64_t)gi * ed.W + gj;
+        // (U P is not 0 where U is no number or infinite)
+        if (B[i] != 0.0 || !(fabs(U[i]) < __builtin_inf())) any = 1;
     }
     any = __syncthreads_or(any);
     if (threadIdx.x == 0) mass[blockIdx.x] = any ? 1 : 0;
@@ -1564,10 +1570,12 @@ hipError_t relaxed_forward(hipStream_t s, const RelaxedInputs& in, const sim_par
     if (R.sparse_lds > 0 && e == hipSuccess) {
         int32_t* r = reinterpret_cast<int32_t*>(ws + L.reach);
         int32_t* mass = r + kReachHead + 4 * (size_t)R.n_btiles;
-        hipLaunchKernelGGL(tile_mass_kernel, dim3(R.n_btiles), dim3(256), 0, s, R.d_btiles, in.envs, ckpt + n,
-                           mass);
+        // (B' = N + p_continue B is not 0 out of reach if p_continue is not finite)
+        const bool sparse = in.sparse && std::isfinite(p.p_continue);
+        hipLaunchKernelGGL(tile_mass_kernel, dim3(R.n_btiles), dim3(256), 0, s, R.d_btiles, in.envs, ckpt,
+                           ckpt + n, mass);
         hipLaunchKernelGGL(tile_integral_kernel, dim3(R.n_env), dim3(256), (size_t)R.sparse_lds, s, R.d_tgrid,
-                           mass, in.sparse ? 1 : 0, r);
+                           mass, sparse ? 1 : 0, r);
         e = hipGetLastError();
         reach = r;
     }

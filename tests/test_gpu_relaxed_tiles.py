@@ -77,3 +77,26 @@ def test_reach_of_the_fire(size, per_cell):
         U, B, g = _run(batch, params, Y, T, k, "product", fwd, bwd)
         assert np.array_equal(U, U0) and np.array_equal(B, B0), (fwd, bwd)
         assert np.max(np.abs(g - g0)) <= 1e-11 * np.max(np.abs(g0)), (fwd, bwd)
+
+
+@pytest.mark.parametrize("p_continue,u", [(float("inf"), None), (float("nan"), None), (0.5, float("inf")),
+                                          (0.5, float("nan"))])
+def test_values_that_are_not_finite(p_continue, u):
+    """0 times such a value is no 0: the sparse forward gives what the dense one gives, far from the fire too."""
+    batch = firegen.landscape_batch(95, [(200, 300), (40, 70)], ign_range=(1, 1))
+    params = _params(95, p_continue=p_continue)
+    got = []
+    for sparse in (0, 1):
+        sim = fs.FireSim.from_batch(batch, params, seed=0)
+        p = fs.make_params(params)
+        p.unburnable_mask = batch.unburnable_mask
+        sim.set_plan(sparse=sparse)
+        U, B = sim.relaxed_init()
+        if u is not None:
+            U[7] = u
+            U[200 * 300 - 9] = u
+        ws = sim.relaxed_workspace(6, 3)
+        sim.relaxed_fwd(p, U, B, 6, 3, ws, "product")
+        got.append((U.cpu().numpy(), B.cpu().numpy()))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b, equal_nan=True)
