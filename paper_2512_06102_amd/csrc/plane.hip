@@ -27,13 +27,15 @@
 //
 // What bounds it: the chain of a step (LDS round trips, one Philox block, one
 // table load, one exponential, the barriers; 4000 to 10000 cycles at one
-// workgroup per compute unit) and the instructions of the lanes that have
-// little to do (VALU issue about half of the chip's rate at 1024 envs), not
-// memory.  Measured against one launch per step over 64-lane tiles (the other
-// step kernel): 1024 envs of 256 x 256, 200 steps, 11.5 -> 2.3 ms; 1024 envs
-// of 64 to 512 squared with a drop per step, 300 steps, 18.1 -> 6.6 ms; 8 envs
-// of 2048 x 2048 with per-cell wind, 1000 steps, 26.9 -> 6.6 ms (parts of 64 x
-// 128 with 24 steps of halo; 7.2 ms with 12 steps, 8.3 ms with 128 x 128).
+// workgroup per compute unit), the instructions of the lanes that have little
+// to do while the fires burn, and the longest fire of a launch (at 1024 envs of
+// 256 x 256 the compute units are busy 57% of it; one env alone takes half its
+// time), not memory.  Measured against one launch per step over 64-lane tiles
+// (the other step kernel): 1024 envs of 256 x 256, 200 steps, 11.6 -> 2.3 ms;
+// 1024 envs of 64 to 512 squared with a drop per step, 300 steps, 18.5 -> 6.0
+// ms (its two launches beside each other; 7.6 in order); 8 envs of 2048 x 2048
+// with per-cell wind, 1000 steps, 28.1 -> 5.9 ms (parts of 64 x 128 with 24
+// steps of halo; 0.6 ms more with 12 steps, 1.7 ms more with 128 x 128).
 // Against one workgroup per env with byte states and the exponentials worked
 // out per step: 64 envs of 64 x 64, 200 steps, 491 -> 255 us.
 //
