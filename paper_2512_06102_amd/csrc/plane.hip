@@ -114,7 +114,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     __shared__ float s_ew[RATES == kRatesEnvWind ? kPlaneChunk : 1][8];
     __shared__ int32_t s_act[kPlaneChunk];
     __shared__ uint32_t s_n[2];               // groups listed in step s, slot s % 2
-    __shared__ uint32_t s_all[2];             // BURNING cells worked out in step s, slot s % 2
+    // BURNING cells worked out in step s, slot s % 3: step s reads the slot of
+    // step s - 1, adds to its own and clears that of step s + 1, which no wave
+    // reads or adds to between two openings of a step.  (A small region has no
+    // other barrier in a step: of two slots, the clear could meet the adds.)
+    __shared__ uint32_t s_all[3];
     __shared__ uint32_t s_tile[kPlaneChunk];  // those of the tile itself, slot s % kPlaneChunk
     __shared__ int32_t s_run;
 
@@ -189,10 +193,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
 
     // -- planes cleared (frames included), then filled from the source bytes
     for (int i = tid; i < (3 + (HALO ? K.has_u : 0)) * K.frame_words; i += NT) pF[i] = 0u;
-    if (tid < 2) {
-        s_n[tid] = 0u;
-        s_all[tid] = 0u;
-    }
+    if (tid < 2) s_n[tid] = 0u;
+    if (tid < 3) s_all[tid] = 0u;
     if (tid < kPlaneChunk) s_tile[tid] = 0u;
     __syncthreads();
     const int g_step = G <= NT ? G : NT, g_rows = G <= NT ? NT / G : 1;
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
                     }
                     any |= bu;
                 }
-        if (any) s_all[1] = 1u;  // read before step 0: does anything burn?
+        if (any) s_all[2] = 1u;  // read by step 0: does anything burn?
     }
 
     // bytes of the 4 cells of group g in row r
@@ -292,7 +294,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     const bool small = !HALO && RH * GW <= kSmallRounds * NT;
     bool quiet = false, stopped = false;
     int32_t s = 0;
-    for (; s < K.steps; ++s) {
+    uint32_t s3 = 0;  // s % 3
+    for (; s < K.steps; ++s, s3 = s3 == 2 ? 0 : s3 + 1) {
         const uint32_t t = t0 + (uint32_t)s;
         const int kc = s % kPlaneChunk;
         if (kc == 0) {
@@ -311,9 +314,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
                 }
         }
         lds_barrier();  // F_t complete, the chunk staged, the last step's cells counted
-        const uint32_t prev = s_all[(s + 1) & 1];
+        const uint32_t prev = s_all[s3 == 0 ? 2 : s3 - 1];
         if (tid == 0) {
-            s_all[s & 1] = 0u;
+            s_all[s3 == 2 ? 0 : s3 + 1] = 0u;
             s_n[(s + 1) & 1] = 0u;
         }
         // nothing burns: no cell can ignite or burn out any more, only the
@@ -567,7 +570,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
             }
         }
         if (n_all) {
-            lds_add(&s_all[s & 1], n_all);
+            lds_add(&s_all[s3], n_all);
             if (!HALO || n_tile) lds_add(&s_tile[kc], HALO ? n_tile : n_all);
         }
         uint32_t* tmp = cur;
