@@ -322,7 +322,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
         // nothing burns: no cell can ignite or burn out any more, only the
         // drops can still change the state (the remaining counts stay 0)
         quiet = prev == 0u;
-        if (K.history && s > 0) store_tile(K.history + (int64_t)(s - 1) * K.F.n_cells);
+        if (K.history && s > 0) {
+            store_tile(K.history + (int64_t)(s - 1) * K.F.n_cells);
+            // where no scan follows and rows end within a word (they are padded
+            // to whole words for the draws, not for the store), another wave may
+            // step the groups that this one stores, and would take ignited cells
+            // out of F
+            if (small && G != GW) lds_barrier();
+        }
         if (quiet && !K.actions && !K.history) {
             stopped = true;
             break;

@@ -48,3 +48,17 @@ def test_counts_of_every_step(size, threads, mode, series):
     got = sim.step(T, actions=act, counts=True)
     assert np.array_equal(got.cpu().numpy(), want)
     assert np.array_equal(sim.states.cpu().numpy(), ref.states)
+
+
+@pytest.mark.parametrize("series", [False, True])
+@pytest.mark.parametrize("mode", [None, 1])
+@pytest.mark.parametrize("size,threads", SHAPES)
+def test_history_of_every_step(size, threads, mode, series):
+    """Row k is the state after step k, whichever wave steps the group that
+    another one stores; and the counts beside it."""
+    sim, ref, act, kw = _pair(size, threads, mode, series)
+    rows, want = ref.step(T, history=True, **kw)
+    hist, got = sim.step_history(T, actions=act, counts=True)
+    assert np.array_equal(hist.cpu().numpy(), rows)
+    assert np.array_equal(got.cpu().numpy(), want)
+    assert np.array_equal(sim.states.cpu().numpy(), rows[-1])
