@@ -437,8 +437,17 @@ int build_planes(sim_handle* h, PlanGroup& g)
     size_t first_lds = 0;
     for (const Whole& w : whole) {
         const int H = h->envs[w.env].H, W = h->envs[w.env].W;
-        const bool fits_on = !g.plane_whole.empty() && (g.plane_whole.back().n_tiles < room ||
-                                                        w.lds * 4 > 3 * first_lds);
+        const int32_t frame_words = (int32_t)plane_frame_words(H, W), list_cap = plane_list_cap(H, W);
+        bool fits_on = false;
+        if (!g.plane_whole.empty()) {
+            // the launch gives every env the largest planes and the longest list
+            // among them, which need not be one env's (a long strip has large
+            // planes and a short list): together they have to fit as well
+            const PlaneLaunch& L = g.plane_whole.back();
+            fits_on = (L.n_tiles < room || w.lds * 4 > 3 * first_lds) &&
+                      plane_lds_bytes(std::max(L.frame_words, frame_words), 3, L.threads,
+                                      std::max(L.list_cap, list_cap)) <= limit;
+        }
         if (!fits_on) {
             PlaneLaunch L{};
             L.threads = w.threads;
@@ -448,8 +457,8 @@ int build_planes(sim_handle* h, PlanGroup& g)
         }
         PlaneLaunch& L = g.plane_whole.back();
         L.n_tiles += 1;
-        L.frame_words = std::max(L.frame_words, (int32_t)plane_frame_words(H, W));
-        L.list_cap = std::max(L.list_cap, plane_list_cap(H, W));
+        L.frame_words = std::max(L.frame_words, frame_words);
+        L.list_cap = std::max(L.list_cap, list_cap);
         tiles.push_back(PlaneTile{w.env, 0, 0, H, W});
     }
     const size_t n_whole = tiles.size(), n_parts = parts.size();
