@@ -198,6 +198,7 @@ __global__ __launch_bounds__(64 * kRlWaves) void rl_step_kernel(
     }
     for (int i = 64 * kKeep + lane; i < n_dw; i += 64) any_burn |= burning_flags(st[i]);
     bool drop = false;
+    int drop_r = 0, drop_c = 0;  // centre of the drop, a cell of the env
     if (!a.done) {
         const int32_t move = (act >= 0 && act < 32) ? (act & 15) : 0;
         const bool valve = act >= 0 && act < 32 && ((act >> 4) & 1);
@@ -206,7 +207,12 @@ __global__ __launch_bounds__(64 * kRlWaves) void rl_step_kernel(
             a.col = min(max(a.col + kDCol[move - 1], 0), W - 1);
         }
         if (valve && a.water > 0) {
-            drop = true;
+            // as in a row of drops: one that lies outside the grid (the agents
+            // are the caller's to set) spends its water and wets nothing
+            const int32_t code = (int32_t)(((uint32_t)a.row << 16) | (uint32_t)a.col);
+            drop_r = (code >> 16) & 0x7FFF;
+            drop_c = code & 0xFFFF;
+            drop = code >= 0 && drop_r < H && drop_c < W;
             a.water -= 1;
         }
     }
@@ -243,8 +249,8 @@ __global__ __launch_bounds__(64 * kRlWaves) void rl_step_kernel(
         wave_sync();
         if (drop) {  // water on F_t: BURNING cells of the square go out
             const int R = A.drop_radius;
-            const int r0 = max(a.row - R, 0), r1 = min(a.row + R, H - 1);
-            const int c0 = max(a.col - R, 0), c1 = min(a.col + R, W - 1);
+            const int r0 = max(drop_r - R, 0), r1 = min(drop_r + R, H - 1);
+            const int c0 = max(drop_c - R, 0), c1 = min(drop_c + R, W - 1);
             const int wa = c0 >> 5, nw = (c1 >> 5) - wa + 1;
             for (int q = lane; q < (r1 - r0 + 1) * nw; q += 64) {
                 const int w = wa + q % nw;
