@@ -64,7 +64,8 @@ __global__ __launch_bounds__(64 * kRlWaves) void rl_reset_kernel(const EnvDev* _
         if (i == ignited) return kBurning;
         return ((unburnable_mask >> c) & 1u) ? kUnburnable : kFlammable;
     };
-    if (((ed.offset | n) & 3) == 0) {
+    // (the handle's classes start on a 4-byte boundary, the caller's states need not)
+    if (((ed.offset | n | (int64_t)(uintptr_t)states) & 3) == 0) {
         const uint32_t* c4 = reinterpret_cast<const uint32_t*>(cls + ed.offset);
         uint32_t* s4 = reinterpret_cast<uint32_t*>(states + ed.offset);
         for (int64_t i = lane; i < (n >> 2); i += 64) {

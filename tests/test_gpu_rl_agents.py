@@ -1,6 +1,6 @@
-"""The one-launch RL step with agents that a caller has set off the grid: as
-the separate launches have it, such an agent spends its water, wets no cell
-and sees only what lies on the grid.
+"""What the RL layer takes from the caller's memory: agents set off the grid
+(in one launch as in the separate ones, such an agent spends its water, wets no
+cell and sees only what lies on the grid), and states at any address.
 """
 import numpy as np
 import pytest
@@ -36,6 +36,29 @@ def test_agents_off_the_grid(drop_radius):
             act = torch.full((len(POSITIONS),), 16 + (1 if t == 5 else 0), dtype=torch.int32, device="cuda")
             o, r, d = env.step(act)
             out += [o.clone(), r.clone(), d.clone(), sim.states.clone(), env.agents.clone()]
+        got.append([x.cpu().numpy() for x in out])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_reset_of_states_at_any_address(shift):
+    """Envs of a multiple of 4 cells whose widths are none: byte steps, and a
+    reset that must not assume 4-byte words either."""
+    batch = firegen.landscape_batch(94, [(8, 6), (20, 10), (4, 3)])
+    params = firegen.Params(p_base=0.9, veg=tuple(float(v) for v in firegen.veg_table(np.random.default_rng(94))))
+    got = []
+    for at in (0, shift):
+        sim = fs.FireSim.from_batch(batch, params, seed=15)
+        store = torch.full((sim.n_cells + 8,), 9, dtype=torch.uint8, device="cuda")
+        store[at:at + sim.n_cells].copy_(sim.states)
+        sim.states = store[at:at + sim.n_cells]
+        env = fs.RLEnv(sim, obs_radius=2, drop_radius=1)
+        obs, _ = env.reset(episode=4)
+        out = [obs.clone(), sim.states.clone()]
+        o, r, d = env.step(torch.zeros(3, dtype=torch.int32, device="cuda"))
+        out += [o.clone(), r.clone(), d.clone(), sim.states.clone()]
+        assert int((store == 9).sum()) == 8
         got.append([x.cpu().numpy() for x in out])
     for a, b in zip(*got):
         assert np.array_equal(a, b)
