@@ -82,8 +82,8 @@ struct PlanGroup {
     PlaneTile* d_ptiles = nullptr;
     int32_t* d_ptile_nbr = nullptr;  // [parts][8] neighbouring tiles (-1 off the env)
     int32_t* d_part_work = nullptr;  // their marks [2][parts], list counts [4], lists [2][parts]
-    int32_t* d_part_envs = nullptr;  // envs cut into parts
-    int32_t n_part_envs = 0;
+    int32_t min_steps = 1;           // fewest steps of a call that run on the bit-plane kernel,
+    int32_t min_history = 1;         // and of one that keeps every state (set_plane_min_steps)
     // a second stream for the launches that run beside the largest envs
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
@@ -91,8 +91,7 @@ struct PlanGroup {
 
 void free_planes(PlanGroup& g)
 {
-    for (void** p : {(void**)&g.d_ptiles, (void**)&g.d_ptile_nbr, (void**)&g.d_part_work,
-                     (void**)&g.d_part_envs}) {
+    for (void** p : {(void**)&g.d_ptiles, (void**)&g.d_ptile_nbr, (void**)&g.d_part_work}) {
         if (*p) (void)hipFree(*p);
         *p = nullptr;
     }
@@ -104,7 +103,7 @@ void free_planes(PlanGroup& g)
     g.plane_whole.clear();
     g.plane_parts = PlaneLaunch{};
     g.plane_threads = -1;
-    g.n_part_envs = 0;
+    g.min_steps = g.min_history = 1;
 }
 
 void free_group(PlanGroup& g)
@@ -382,10 +381,67 @@ int plane_threads_for(int64_t cells, int64_t per_cu)
     return cells < 1536 ? 64 : (per_cu > 3 ? 256 : 512);
 }
 
+// Envs of more cells than this weigh on one workgroup: see thick_fires and
+// set_plane_min_steps.
+constexpr int64_t kLargeEnvCells = 160 * 160;
+constexpr int32_t kNever = INT32_MAX;
+
+// Fires that burn on for long fill an env: a step then works out most of its
+// groups, and takes as long as the few lanes of its one workgroup need for
+// them.  In parts the work is spread over the chip.  Measured, 100 steps, whole
+// and in parts: 1024 envs of 256 x 256 1.93 and 3.59 ms with p_continue 0.7,
+// 5.63 and 4.65 ms with 0.8, 12.3 and 7.5 ms with 0.9; 256 of 512 x 512 2.9 and
+// 2.3, 9.5 and 2.8, 11.3 and 4.8 ms; 64 of 192 x 192 1.01 and 0.67, 1.47 and
+// 1.01, 2.3 and 1.75 ms; 256 of 128 x 128 with 0.95 1.15 and 1.58 ms.
+bool thick_fires(const sim_handle* h, int64_t cells)
+{
+    return h->params.p_continue > 0.75f && cells > kLargeEnvCells;
+}
+
 // The tiles and launches of group g's bit-plane steps.  An env is taken whole
-// where its planes fit LDS, else in parts of kPartRows x kPartCols.
+// where its planes fit LDS and its fires stay thin, else in parts of kPartRows x
+// kPartCols.
 constexpr int kPartRows = 64, kPartCols = 128, kPartSteps = 24;
 constexpr int kSideSteps = 4;  // fewest steps for which launches run beside each other
+
+// The fewest steps of a call for which the bit-plane kernel, which first takes
+// an env's states into LDS and at last writes them back, beats one launch per
+// step over tiles (about 11 us each for few envs).  Measured, bit planes and
+// tiles, us per call of 1, 3, 4, 6 and 8 steps:
+//   256 envs of 128 x 128   23  25 |  49  57 |  60  71
+//   1 of 256 x 256          24  17 |  34  37 |  38  46
+//   1 of 512 x 512          43  18 |  58  38 |  65  46 |  79  66 | 100  94
+//   128 of 512 x 512        63  44 |  79  85 |  86  94
+//   1024 of 256 x 256       74  84 | 100 187 | 113 212
+//   1 of 640 x 640 in parts 45  18 |  40  38 |  44  45 |  52  67
+//   16 of 1024 x 1024       118  32 |  88  65 |  94  70 | 103 103 | 114 137
+//   8 of 2048 x 2048        339  41 | 129  79 | 135  86 | 143 122 | 151 162
+// A history is written by the env's one workgroup as well (us per call of 1, 4
+// and 16 steps): 1 of 128 x 128 18 24 | 42 67 | 89 190; 32 of 256 x 256 39 25 |
+// 90 81 | 252 241; 16 of 512 x 512 66 25 | 147 79 | 405 246; 256 of 256 x 256
+// 47 38 | 111 120 | 328 477.
+void set_plane_min_steps(PlanGroup& g, int64_t n_large, int64_t largest, int cus)
+{
+    const bool fills = n_large >= cus;  // a large env for every compute unit
+    int32_t steps = 1;
+    if (n_large > 0 && !fills) steps = 4 * n_large >= cus || largest <= 256 * 256 ? 3 : 10;
+    if (g.plane_parts.n_tiles) steps = std::max(steps, 4 + std::min(g.plane_parts.n_tiles / 1024, 4));
+    g.min_steps = steps;
+    // (a history of envs in parts needs each state in memory between the steps)
+    g.min_history = g.plane_parts.n_tiles || (n_large > 0 && !fills) ? kNever : (fills ? 4 : 1);
+}
+
+// The same for a call now: where the rates are worked out in the step, the
+// bit-plane kernel's steps cost more, and pay later (1 env of 512 x 512 under a
+// wind series, us per call of 8 and 16 steps: 110 and 180 on bit planes, 87 and
+// 169 over tiles).
+int32_t plane_min_steps(const sim_handle* h, const PlanGroup& g, bool history)
+{
+    const int32_t steps = history ? g.min_history : g.min_steps;
+    const bool table = h->d_phi && !h->series_env && !h->series_cell;
+    return table || steps == 1 || steps == kNever ? steps : 2 * steps;
+}
+
 int build_planes(sim_handle* h, PlanGroup& g)
 {
     free_planes(g);
@@ -401,7 +457,8 @@ int build_planes(sim_handle* h, PlanGroup& g)
     };
     std::vector<Whole> whole;
     std::vector<PlaneTile> tiles, parts;
-    std::vector<int32_t> nbr, part_envs;
+    std::vector<int32_t> nbr;
+    int64_t n_large = 0, largest = 0;  // of the envs taken whole
     const int32_t n_members = g.envs.empty() ? h->n_env : (int32_t)g.envs.size();
     for (int32_t q = 0; q < n_members; ++q) {
         const int32_t e = g.envs.empty() ? q : g.envs[q];
@@ -410,11 +467,12 @@ int build_planes(sim_handle* h, PlanGroup& g)
         const int threads = g.plan.resident ? g.plan.resident : plane_threads_for(cells, n_members / cus);
         const size_t lds =
             plane_lds_bytes(plane_frame_words(H, W), 3, threads, plane_list_cap(H, W));
-        if (plane_indexable(H, W) && lds <= limit) {
+        if (plane_indexable(H, W) && lds <= limit && !thick_fires(h, cells)) {
             whole.push_back({e, threads, lds});
+            n_large += cells > kLargeEnvCells;
+            largest = std::max(largest, cells);
             continue;
         }
-        part_envs.push_back(e);
         const int nr = (H + kPartRows - 1) / kPartRows, nc = (W + kPartCols - 1) / kPartCols;
         const int32_t first = (int32_t)parts.size();
         for (int i = 0; i < nr; ++i)
@@ -470,7 +528,6 @@ int build_planes(sim_handle* h, PlanGroup& g)
     bool ok = upload(&g.d_ptiles, tiles.data(), tiles.size());
     if (n_parts)
         ok = ok && upload(&g.d_ptile_nbr, nbr.data(), nbr.size()) &&
-             upload(&g.d_part_envs, part_envs.data(), part_envs.size()) &&
              hipMalloc(&g.d_part_work, (4 * n_parts + 4) * sizeof(int32_t)) == hipSuccess;
     if (!ok) {
         free_planes(g);
@@ -490,8 +547,8 @@ int build_planes(sim_handle* h, PlanGroup& g)
         const int rows = kPartRows + 2 * kPartSteps, cols = kPartCols + 2 * kPlaneHaloCols;
         L.frame_words = (int32_t)plane_frame_words(rows, cols);
         L.list_cap = plane_list_cap(rows, cols);
-        g.n_part_envs = (int32_t)part_envs.size();
     }
+    set_plane_min_steps(g, n_large, largest, cus);
     if (g.plane_whole.size() + (n_parts ? 1 : 0) > 1 &&
         (hipStreamCreateWithFlags(&g.side, hipStreamNonBlocking) != hipSuccess ||
          hipEventCreateWithFlags(&g.fork, hipEventDisableTiming) != hipSuccess ||
@@ -504,17 +561,13 @@ int build_planes(sim_handle* h, PlanGroup& g)
 
 bool has_planes(const PlanGroup& g) { return !g.plane_whole.empty() || g.plane_parts.n_tiles > 0; }
 
-// Rebuild a group's tile lists if its plan changed the geometry.  A group
-// whose envs all run whole on the bit-plane kernel needs no other tiles.
+// Rebuild a group's tile lists if its plan changed the geometry.
 int ensure_group_tiles(sim_handle* h, PlanGroup& g)
 {
-    if (wants_planes(g.plan)) {
-        if (g.plane_threads != g.plan.resident) {
-            h->graph.valid = false;
-            const int rc = build_planes(h, g);
-            if (rc != SIM_OK) return rc;
-        }
-        if (has_planes(g) && g.plane_parts.n_tiles == 0) return SIM_OK;
+    if (wants_planes(g.plan) && g.plane_threads != g.plan.resident) {
+        h->graph.valid = false;
+        const int rc = build_planes(h, g);
+        if (rc != SIM_OK) return rc;
     }
     if (g.tiles_rt == tiles_key(g.plan) && g.tiles_tw == g.plan.tile_width) return SIM_OK;
     h->graph.valid = false;
@@ -618,9 +671,9 @@ hipError_t copy_group(sim_handle* h, hipStream_t s, const PlanGroup& g, uint8_t*
     return launch_copy_envs(s, h->d_envs, g.d_list, (int32_t)g.envs.size(), dst, src);
 }
 
-// The T steps of the envs in parts: launches of up to kPartSteps steps between
-// the two state buffers (an even number of them where T allows, so that the
-// result ends in `states`).
+// The T > 1 steps of the envs in parts: launches of up to kPartSteps steps
+// between the two state buffers, an even number of them, so that the result ends
+// in `states`.
 hipError_t enqueue_parts(sim_handle* h, PlanGroup& g, hipStream_t s, const PlaneLaunch& P, uint8_t* states,
                          const int32_t* actions, int32_t T, int32_t* counts)
 {
@@ -630,7 +683,7 @@ hipError_t enqueue_parts(sim_handle* h, PlanGroup& g, hipStream_t s, const Plane
     int32_t* const list = n_list + 4;
     if ((e = launch_fill_i32(s, mark, 2 * (int64_t)P.n_tiles + 4, 0)) != hipSuccess) return e;
     int32_t n = (T + kPartSteps - 1) / kPartSteps;
-    if (n % 2 && T > 1) ++n;
+    n += n % 2;
     uint8_t *cur = states, *nxt = h->d_tmp;
     for (int32_t i = 0, k = 0; i < n; ++i) {
         const int32_t steps = (T - k + (n - i) - 1) / (n - i);
@@ -654,7 +707,6 @@ hipError_t enqueue_parts(sim_handle* h, PlanGroup& g, hipStream_t s, const Plane
         k += steps;
         std::swap(cur, nxt);
     }
-    if (cur != states) return launch_copy_envs(s, h->d_envs, g.d_part_envs, g.n_part_envs, states, cur);
     return hipSuccess;
 }
 
@@ -718,8 +770,7 @@ hipError_t enqueue_group(sim_handle* h, PlanGroup& g, hipStream_t s, uint8_t* st
     const sim_plan& plan = g.plan;
     uint8_t* cur = states;
     uint8_t* nxt = history ? history : h->d_tmp;
-    // (a history of envs in parts needs each state in memory between the steps)
-    if (wants_planes(plan) && has_planes(g) && !(history && g.plane_parts.n_tiles))
+    if (wants_planes(plan) && has_planes(g) && T >= plane_min_steps(h, g, history != nullptr))
         return enqueue_planes(h, g, s, L, states, actions, T, counts, history);
     const bool sparse = plan.sparse != 0;
     if (sparse) {  // nothing is known yet about how the two buffers compare
