@@ -1436,7 +1436,8 @@ int sim_set_plan(sim_handle* h, const sim_plan* plan)
     drop_classes(h);
     h->plan = p;
     h->all.plan = p;
-    return SIM_OK;
+    // here and not in the next step, which may be under capture
+    return ensure_group_tiles(h, h->all);
 }
 
 int sim_get_plan(const sim_handle* h, sim_plan* plan)
@@ -1484,7 +1485,7 @@ int sim_set_class_plan(sim_handle* h, int32_t size_class, const sim_plan* plan)
     g->tuned_ms = 0.0f;
     g->from_cache = false;
     h->graph.valid = false;
-    return SIM_OK;
+    return ensure_group_tiles(h, *g);  // (as in sim_set_plan)
 }
 
 int sim_get_class_plans(const sim_handle* h, sim_class_plan* out, int32_t max_out, int32_t* n_out)
