@@ -306,14 +306,22 @@ int sim_set_step(sim_handle* h, uint64_t t);
  * per launch (their sim_step_history runs one step per launch).  Envs of
  * different sizes are launches of their own, which outside captures run
  * beside each other on a stream of the handle's; the caller's stream waits
- * for it.  sim_init builds a table of the ignition rates of every edge, 32
- * bytes per cell, for it when that takes at most a quarter of the free device
- * memory; without it the rates are worked out in the step. */
+ * for it.  Under static wind it reads the table of sim_set_rate_table. */
 typedef struct {
     int32_t tile_rows, tile_width, temporal, skip_static, sparse, graph, resident;
 } sim_plan;
 int sim_set_plan(sim_handle* h, const sim_plan* plan);
 int sim_get_plan(const sim_handle* h, sim_plan* plan);
+
+/* The table of the ignition rates of every edge under the static wind, 32
+ * bytes per cell (sim_step under the plans above and sim_rl_step read it; no
+ * result depends on it).  sim_init builds it when it takes at most a quarter
+ * of the free device memory; without it the rates are worked out in every
+ * step, which then takes longer.  on 0 frees it, for instance on a handle
+ * that only calibrates (waits for the device; not during a capture); on 1
+ * builds it again (synchronises `stream`; SIM_ENOMEM if it would take more
+ * than a quarter of the free memory). */
+int sim_set_rate_table(sim_handle* h, int32_t on, void* stream);
 
 /* Autotuner: times every candidate plan (tile_rows 1/2/4/8 x tile_width
  * 64/256, with skip_static 0 and, if allow_skip, 1; sparse = allow_sparse;

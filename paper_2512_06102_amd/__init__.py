@@ -39,7 +39,7 @@ THETA_NAMES = ("p_base", "alpha_w1", "alpha_w2", "alpha_s", "alpha_gamma", "p_co
 
 EXPORTED = ("sim_init", "sim_step", "sim_get_step", "sim_set_step", "sim_set_plan", "sim_get_plan",
             "sim_autotune", "sim_set_class_plan", "sim_get_class_plans", "sim_autotune_classes",
-            "sim_set_wind_series", "sim_step_history", "sim_set_drop",
+            "sim_set_wind_series", "sim_step_history", "sim_set_drop", "sim_set_rate_table",
             "sim_rl_reset", "sim_rl_step",
             "sim_relaxed_init", "sim_relaxed_workspace_bytes", "sim_step_relaxed_fwd",
             "sim_relaxed_loss", "sim_relaxed_loss_noalloc", "sim_relaxed_loss_bce", "sim_step_relaxed_bwd", "sim_debug_exp", "sim_debug_atan", "sim_debug_philox", "sim_debug_stream",
@@ -109,6 +109,7 @@ def lib() -> ctypes.CDLL:
         L.sim_set_wind_series.argtypes = [P, P, P, I64]
         L.sim_step_history.argtypes = [P, P, P, I32, P, P, P]
         L.sim_set_drop.argtypes = [P, I32, I32]
+        L.sim_set_rate_table.argtypes = [P, I32, P]
         L.sim_rl_reset.argtypes = [P, P, P, P, P, U64, P, P, P]
         L.sim_rl_step.argtypes = [P, P, P, P, P, P, P, P, P]
         L.sim_autotune.argtypes = [P, P, I32, I32, I32, P, I32, ctypes.POINTER(I32), P]
@@ -331,6 +332,12 @@ class FireSim:
         mode 1 (water) BURNING -> BURNT, on (2 radius + 1)^2 cells."""
         _check(lib().sim_set_drop(self.handle, int(mode), int(radius)), self.handle)
 
+    def set_rate_table(self, on: bool = True):
+        """Free (or build again) the table of ignition rates under static wind,
+        32 bytes per cell.  Steps give the same results without it, and take
+        longer; the relaxed path does not use it."""
+        _check(lib().sim_set_rate_table(self.handle, int(bool(on)), self._s()), self.handle)
+
     @property
     def t(self) -> int:
         v = ctypes.c_uint64()
@@ -412,8 +419,12 @@ class FireSim:
         return U, B
 
     def relaxed_workspace(self, T: int, ckpt_every: int) -> torch.Tensor:
-        n = lib().sim_relaxed_workspace_bytes(self.handle, int(T), int(ckpt_every))
-        return torch.empty(max(int(n), 1), dtype=torch.uint8, device=self.device)
+        n = max(int(lib().sim_relaxed_workspace_bytes(self.handle, int(T), int(ckpt_every))), 1)
+        try:
+            return torch.empty(n, dtype=torch.uint8, device=self.device)
+        except torch.OutOfMemoryError:  # the relaxed path does not read the table
+            self.set_rate_table(False)
+        return torch.empty(n, dtype=torch.uint8, device=self.device)
 
     def relaxed_fwd(self, params: SimParams, U, B, T, ckpt_every, ws, form: str = "product"):
         _check(lib().sim_step_relaxed_fwd(self.handle, ctypes.byref(params), _ptr(U), _ptr(B),

@@ -851,6 +851,21 @@ hipError_t enqueue_steps(sim_handle* h, hipStream_t s, uint8_t* states, const in
     return hipSuccess;
 }
 
+// The table of edge rates, where it takes at most a quarter of the free memory
+// (without it, d_phi stays nullptr and the steps work the rates out).
+hipError_t build_rate_table(sim_handle* h, hipStream_t s)
+{
+    const size_t bytes = 32 * (size_t)h->n_cells;
+    size_t mem_free = 0, mem_total = 0;
+    if (hipMemGetInfo(&mem_free, &mem_total) == hipSuccess && bytes <= mem_free / 4 &&
+        hipMalloc(&h->d_phi, bytes) != hipSuccess)
+        h->d_phi = nullptr;
+    (void)hipGetLastError();  // a refused allocation is not an error of this call
+    if (!h->d_phi) return hipSuccess;
+    const StaticFields F{h->d_g, h->d_E, h->wind_cell ? h->d_wind : nullptr, h->n_cells, 0, nullptr, h->n_env};
+    return launch_phi_table(s, h->d_envs, h->d_chunk_env, h->n_chunks, F, step_args(h), h->d_phi);
+}
+
 bool same_plan(const sim_plan& a, const sim_plan& b)
 {
     return a.tile_rows == b.tile_rows && a.tile_width == b.tile_width && a.temporal == b.temporal &&
@@ -1038,19 +1053,7 @@ int sim_init(sim_handle** out, const sim_params* p, int32_t n_env, const sim_env
                                      h->d_den, h->d_wind, states_out);
     if (e == hipSuccess) e = launch_ignite(s, d_ign, n_ign, h->d_envs, states_out);
     if (e == hipSuccess) e = launch_copy_u8(s, h->d_init_states, states_out, n_cells);
-    // the table of edge rates, where it takes at most a quarter of the free
-    // memory (without it the steps work the rates out)
-    {
-        size_t mem_free = 0, mem_total = 0;
-        if (hipMemGetInfo(&mem_free, &mem_total) == hipSuccess && 32 * n <= mem_free / 4 &&
-            hipMalloc(&h->d_phi, 32 * n) != hipSuccess)
-            h->d_phi = nullptr;
-        (void)hipGetLastError();  // a refused allocation is not an error of this call
-    }
-    if (e == hipSuccess && h->d_phi) {
-        const StaticFields F{h->d_g, h->d_E, h->wind_cell ? h->d_wind : nullptr, n_cells, 0, nullptr, n_env};
-        e = launch_phi_table(s, h->d_envs, h->d_chunk_env, h->n_chunks, F, step_args(h), h->d_phi);
-    }
+    if (e == hipSuccess) e = build_rate_table(h, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (d_ign) (void)hipFree(d_ign);
     if (e != hipSuccess) {
@@ -1239,6 +1242,25 @@ int sim_set_wind_series(sim_handle* h, const float* env_wind, const float* cell_
     h->series_cell = cell_wind;
     h->series_T = series_T;
     h->graph.valid = false;  // the series pointers are kernel arguments
+    return SIM_OK;
+}
+
+int sim_set_rate_table(sim_handle* h, int32_t on, void* stream)
+{
+    CallScope scope("sim_set_rate_table", h);
+    if (!h) return fail(nullptr, SIM_EINVAL, "handle is NULL");
+    if (on != 0 && on != 1) return fail(h, SIM_EINVAL, "on must be 0 or 1");
+    h->graph.valid = false;  // the table is a kernel argument
+    if (!on) {
+        if (h->d_phi) HIP_OR_FAIL(h, hipFree(h->d_phi));
+        h->d_phi = nullptr;
+    } else if (!h->d_phi) {
+        hipStream_t s = (hipStream_t)stream;
+        HIP_OR_FAIL(h, build_rate_table(h, s));
+        HIP_OR_FAIL(h, hipStreamSynchronize(s));
+        if (!h->d_phi)
+            return fail(h, SIM_ENOMEM, "the table of ignition rates takes more than a quarter of the free memory");
+    }
     return SIM_OK;
 }
 
