@@ -283,10 +283,10 @@ int sim_set_step(sim_handle* h, uint64_t t);
  *               is not computed (its cells cannot change); 0: every tile runs.
  *               In sim_step_relaxed_fwd, 1 computes step s only on tiles within
  *               s + 1 cells of a cell with initial burning mass (B_0 != 0),
- *               the others keep their state; in sim_step_relaxed_bwd it skips
- *               adjoint step s on tiles farther than that: the parameter
- *               gradient is unchanged, since it only sums terms carrying B_s,
- *               which is zero there.
+ *               the others keep their state, and sim_step_relaxed_bwd on its
+ *               workspace skips adjoint step s on tiles farther than that:
+ *               the parameter gradient is unchanged, since it only sums terms
+ *               carrying B_s, which is zero there.
  *  graph        1: capture the T launches of a call into a HIP graph and
  *               replay it (re-captured when T, the pointers or the plan
  *               change); 0: launch directly

@@ -172,9 +172,12 @@ __global__ __launch_bounds__(256) void fuel_kernel(const uint8_t* __restrict__ c
         g[i] = (1.0f + sveg[cls[i]]) * (1.0f + den[i]);
 }
 
+// (clear: a word set to 0 on the way, or nullptr)
 __global__ __launch_bounds__(256) void copy_f64_kernel(double* __restrict__ dst,
-                                                       const double* __restrict__ src, int64_t n)
+                                                       const double* __restrict__ src, int64_t n,
+                                                       int32_t* __restrict__ clear)
 {
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
     const int64_t n2 = n >> 1;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n2;
          i += (int64_t)gridDim.x * blockDim.x)
@@ -184,8 +187,10 @@ __global__ __launch_bounds__(256) void copy_f64_kernel(double* __restrict__ dst,
         dst[i] = src[i];
 }
 
-__global__ void fill_f64_kernel(double* p, int64_t n, double v)
+// (only_if: nullptr, or nothing is filled where it points to 0)
+__global__ void fill_f64_kernel(double* p, int64_t n, double v, const int32_t* only_if)
 {
+    if (only_if && *only_if == 0) return;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
@@ -406,35 +411,56 @@ __device__ __forceinline__ CD cd_from_right(CD a) { return CD{from_right0(a.c), 
 // start at zero) only ever meets B = 0 in the gradient sums, so only the
 // parameter gradient is returned.
 //
-// tile_mass_kernel flags the adjoint tiles holding initial burning mass (or a
-// U that is not finite);
+// first_state_kernel copies the initial state to its checkpoint and flags the
+// tiles holding initial burning mass (or a U that is not finite) on the way, one
+// workgroup per tile: with the flags in a pass of their own a forward call of one
+// step of 256 envs of 128 x 128 took 94 us, now 83, and of one env of 2048 x 2048
+// 85, now 67.  Where an env is one strip wide, its tiles are contiguous and are
+// copied as such.
 // tile_integral_kernel builds each env's integral image of the flags (one
 // workgroup per env, in LDS).
-__global__ __launch_bounds__(256) void tile_mass_kernel(const RelaxedTile* __restrict__ tiles,
-                                                        const EnvDev* __restrict__ envs,
-                                                        const double* __restrict__ U, const double* __restrict__ B,
-                                                        int32_t* __restrict__ mass)
+__global__ __launch_bounds__(256) void first_state_kernel(const RelaxedTile* __restrict__ tiles,
+                                                          const EnvDev* __restrict__ envs,
+                                                          const double* __restrict__ U, const double* __restrict__ B,
+                                                          double* __restrict__ Uo, double* __restrict__ Bo,
+                                                          int32_t* __restrict__ mass)
 {
     const RelaxedTile td = tiles[blockIdx.x];
     const EnvDev ed = envs[td.env];
+    const int rows = min(AR, ed.H - td.r0), cols = min(AW, ed.W - td.c0);
+    const bool strip = ed.W <= AW;
+    const int64_t base = ed.offset + (int64_t)td.r0 * ed.W + td.c0;
+    constexpr int N = AW * AR / 256;
+    double u[N], b[N];
+    int64_t at[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int q = 256 * k + (int)threadIdx.x, r = q / AW, c = q % AW;
+        const bool in = strip ? q < rows * ed.W : r < rows && c < cols;
+        at[k] = in ? base + (strip ? (int64_t)q : (int64_t)r * ed.W + c) : -1;
+        u[k] = in ? U[at[k]] : 0.0;
+        b[k] = in ? B[at[k]] : 0.0;
+    }
     int any = 0;
-    for (int idx = threadIdx.x; idx < AW * AR; idx += 256) {
-        const int gi = td.r0 + idx / AW, gj = td.c0 + idx % AW;
-        if (gi >= ed.H || gj >= ed.W) continue;
-        const int64_t i = ed.offset + (int64_t)gi * ed.W + gj;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        if (at[k] >= 0) {
+            Uo[at[k]] = u[k];
+            Bo[at[k]] = b[k];
+        }
         // (U P is not 0 where U is no number or infinite)
-        if (B[i] != 0.0 || !(fabs(U[i]) < __builtin_inf())) any = 1;
+        if (b[k] != 0.0 || !(fabs(u[k]) < __builtin_inf())) any = 1;
     }
     any = __syncthreads_or(any);
     if (threadIdx.x == 0) mass[blockIdx.x] = any ? 1 : 0;
 }
 
 __global__ __launch_bounds__(256) void tile_integral_kernel(const TileGrid* __restrict__ grids,
-                                                            const int32_t* __restrict__ mass, int32_t sparse,
+                                                            const int32_t* __restrict__ mass,
                                                             int32_t* __restrict__ reach)
 {
     int32_t* const integ = reach + kReachHead;
-    if (blockIdx.x == 0 && threadIdx.x == 0) reach[0] = sparse;
+    if (blockIdx.x == 0 && threadIdx.x == 0) reach[0] = 1;
     extern __shared__ int32_t sI[];
     const TileGrid tg = grids[blockIdx.x];
     const int W1 = tg.cols + 1, n = (tg.rows + 1) * W1;
@@ -517,7 +543,7 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
     RelaxedArgs A, const double* __restrict__ U, const double* __restrict__ B, const double* __restrict__ gU1,
     const double* __restrict__ gB1, double* __restrict__ gU0, double* __restrict__ gB0,
     const double* __restrict__ Xin, double* __restrict__ Xout, double* __restrict__ gsum,
-    const float* __restrict__ env_wind, const int32_t* __restrict__ reach, int32_t sparse, int32_t step)
+    const float* __restrict__ env_wind, const int32_t* __restrict__ reach, int32_t step)
 {
     constexpr int NW = BANDS == 1 ? 4 : BANDS;  // waves per workgroup
     constexpr int BR = AR / BANDS;              // rows per wave
@@ -536,8 +562,8 @@ __global__ __launch_bounds__(BANDS == 1 ? 256 : 64 * BANDS) __attribute__((amdgp
     const RelaxedTile td = tiles[tix];
     const TileGrid tg = grids[td.env];
     const int tb = td.r0 / AR, ts = td.c0 / AW;  // band and strip of the tile
-    // sparse: the whole tile (reach[0]: the states were written sparsely)
-    if (reach && (sparse || reach[0]) && !adj_tile_in_reach(tb, ts, tg, reach + kReachHead, step)) return;
+    // sparse: the whole tile
+    if (reach && reach[0] && !adj_tile_in_reach(tb, ts, tg, reach + kReachHead, step)) return;
     const EnvDev ed = envs[td.env];
     const int H = ed.H, W = ed.W;
     const int band = BANDS == 1 ? 0 : wv;
@@ -1314,15 +1340,15 @@ int blocks_for(int64_t n)
     return (int)std::max<int64_t>(1, std::min<int64_t>(b, 65536));
 }
 
-hipError_t copy_f64(hipStream_t s, double* dst, const double* src, int64_t n)
+hipError_t copy_f64(hipStream_t s, double* dst, const double* src, int64_t n, int32_t* clear = nullptr)
 {
-    hipLaunchKernelGGL(copy_f64_kernel, dim3(blocks_for((n >> 1) + 1)), dim3(256), 0, s, dst, src, n);
+    hipLaunchKernelGGL(copy_f64_kernel, dim3(blocks_for((n >> 1) + 1)), dim3(256), 0, s, dst, src, n, clear);
     return hipGetLastError();
 }
 
-hipError_t fill_f64(hipStream_t s, double* p, int64_t n, double v)
+hipError_t fill_f64(hipStream_t s, double* p, int64_t n, double v, const int32_t* only_if = nullptr)
 {
-    hipLaunchKernelGGL(fill_f64_kernel, dim3(blocks_for(n)), dim3(256), 0, s, p, n, v);
+    hipLaunchKernelGGL(fill_f64_kernel, dim3(blocks_for(n)), dim3(256), 0, s, p, n, v, only_if);
     return hipGetLastError();
 }
 
@@ -1451,7 +1477,7 @@ void launch_adj(hipStream_t s, const RelaxedInputs& in, const RelaxedState& R, c
     const int32_t per_xcd = blocks_per_xcd(in, R, blocks);
     hipLaunchKernelGGL(kernel, dim3(per_xcd ? 8 * per_xcd : blocks), dim3(bands > 1 ? 64 * bands : 256), 0, s,
                        R.d_btiles, R.n_btiles, per_xcd, R.d_tgrid, in.envs, g, in.E, in.wind, in.cls, in.den, in.n_cells, A, U,
-                       B, gU1, gB1, gU0, gB0, Xin, Xout, gsum, in.env_wind, reach, in.sparse, step);
+                       B, gU1, gB1, gU0, gB0, Xin, Xout, gsum, in.env_wind, reach, step);
 }
 
 }  // namespace
@@ -1562,22 +1588,24 @@ hipError_t relaxed_forward(hipStream_t s, const RelaxedInputs& in, const sim_par
     const RelaxedArgs A = relaxed_args(p);
     const int32_t t_last = ((T - 1) / k) * k;  // first step of the last segment
     hipError_t e = fuel(s, in, p, g);
-    if (e == hipSuccess) e = copy_f64(s, ckpt, U, n);
-    if (e == hipSuccess) e = copy_f64(s, ckpt + n, B, n);
     // sparse: tiles with initial burning mass and their integral images, kept in
     // the workspace for the backward; a dense forward notes that it is one
+    // (B' = N + p_continue B is not 0 out of reach if p_continue is not finite)
+    int32_t* const r = R.sparse_lds > 0 ? reinterpret_cast<int32_t*>(ws + L.reach) : nullptr;
     const int32_t* reach = nullptr;
-    if (R.sparse_lds > 0 && e == hipSuccess) {
-        int32_t* r = reinterpret_cast<int32_t*>(ws + L.reach);
+    if (r && in.sparse && std::isfinite(p.p_continue)) {
         int32_t* mass = r + kReachHead + 4 * (size_t)R.n_btiles;
-        // (B' = N + p_continue B is not 0 out of reach if p_continue is not finite)
-        const bool sparse = in.sparse && std::isfinite(p.p_continue);
-        hipLaunchKernelGGL(tile_mass_kernel, dim3(R.n_btiles), dim3(256), 0, s, R.d_btiles, in.envs, ckpt,
-                           ckpt + n, mass);
-        hipLaunchKernelGGL(tile_integral_kernel, dim3(R.n_env), dim3(256), (size_t)R.sparse_lds, s, R.d_tgrid,
-                           mass, sparse ? 1 : 0, r);
-        e = hipGetLastError();
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(first_state_kernel, dim3(R.n_btiles), dim3(256), 0, s, R.d_btiles, in.envs, U, B, ckpt,
+                               ckpt + n, mass);
+            hipLaunchKernelGGL(tile_integral_kernel, dim3(R.n_env), dim3(256), (size_t)R.sparse_lds, s, R.d_tgrid,
+                               mass, r);
+            e = hipGetLastError();
+        }
         reach = r;
+    } else {
+        if (e == hipSuccess) e = copy_f64(s, ckpt, U, n, r);
+        if (e == hipSuccess) e = copy_f64(s, ckpt + n, B, n);
     }
     const double* cu = ckpt;  // state t
     const double* cb = ckpt + n;
@@ -1681,14 +1709,13 @@ hipError_t relaxed_backward(hipStream_t s, const RelaxedInputs& in, const sim_pa
     double* nb = adj + 3 * n;
     if (e == hipSuccess) e = copy_f64(s, cu, gU_T, n);
     if (e == hipSuccess) e = gB_T ? copy_f64(s, cb, gB_T, n) : fill_f64(s, cb, n, 0.0);
-    // sparse adjoint: the reach of the initial burning mass, left in the
-    // workspace by the forward, and zeroed output buffers (skipped tiles keep
-    // them).  A forward that wrote its states sparsely makes every adjoint on
-    // this workspace sparse: the gradient is the same bits.
+    // sparse adjoint, after a forward that wrote its states sparsely: the reach of
+    // the initial burning mass, left in the workspace, and zeroed output buffers
+    // (skipped tiles keep them)
     const int32_t* reach = nullptr;
     if (R.sparse_lds > 0 && T > 0 && e == hipSuccess) {
         reach = reinterpret_cast<const int32_t*>(ws + L.reach);
-        e = fill_f64(s, nu, 2 * n, 0.0);
+        e = fill_f64(s, nu, 2 * n, 0.0, reach);
     }
     const int32_t n_seg = T > 0 ? (T + k - 1) / k : 0;
     for (int32_t sg = n_seg - 1; sg >= 0 && e == hipSuccess; --sg) {
