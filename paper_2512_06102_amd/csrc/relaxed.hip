@@ -1408,9 +1408,16 @@ RelaxedInputs at_step(const RelaxedInputs& in, int32_t t)
 
 // Row bands per tile: where the tiles alone (or those in reach of the fire)
 // leave the chip idle, a step lasts as long as one wave's walk, so more waves
-// walk fewer rows each (both sides measured at the kernels).
+// walk fewer rows each.  Measured, many / few, ms of 100 steps, product form,
+// envs of 128 x 128 (8 tiles each):
+//   tiles   256          512          768          896          1024         2048
+//   forward 0.94 / 0.77  1.41 / 1.26  1.70 / 1.59  2.00 / 1.78  2.06 / 1.92  3.64 / 3.26
+//   adjoint 5.1  / 2.2   5.6  / 4.1   6.0  / 5.8   6.3  / 7.2   6.5  / 7.5   10.0 / 14.6
+// where the fire decides which tiles run (envs of 64 tiles and more, 4 bands
+// instead of 1): 512 tiles 3.3 / 3.3, 896 4.0 / 4.6; in one env, which has fewer
+// of them in reach, 968 tiles 2.7 / 2.3, 2048 3.2 / 3.7
 constexpr int kFwdBands = 4, kFwdBandsFew = 16, kAdjBandsFew = 8, kAdjBandsPart = 4;
-constexpr int kFewTiles = 1024;
+constexpr int kFewFwdTiles = 1024, kFewAdjTiles = 800, kFewAdjTilesOneEnv = 1024;
 
 // Do only some of the tiles run in most steps: large envs under a sparse plan?
 bool partly_active(const RelaxedInputs& in, const RelaxedState& R)
@@ -1430,7 +1437,7 @@ void launch_fwd(hipStream_t s, const RelaxedInputs& in, const RelaxedState& R, c
                 const double* U, const double* B, double* Uo, double* Bo, const int32_t* reach, const double* U_0,
                 int32_t step)
 {
-    const bool few = in.n_tiles < kFewTiles;
+    const bool few = in.n_tiles < kFewFwdTiles;
     auto kernel = few ? relaxed_fwd_kernel<WC, FORM, SL, kFwdBandsFew> : relaxed_fwd_kernel<WC, FORM, SL, kFwdBands>;
     const int32_t groups = (in.n_tiles * (few ? kFwdBandsFew : kFwdBands) + 3) / 4;
     const int32_t per_xcd = blocks_per_xcd(in, R, groups);
@@ -1469,7 +1476,9 @@ void launch_adj(hipStream_t s, const RelaxedInputs& in, const RelaxedState& R, c
                 double* gU0, double* gB0, const double* Xin, double* Xout, double* gsum, const int32_t* reach,
                 int32_t step)
 {
-    const int bands = R.n_btiles < kFewTiles ? kAdjBandsFew : (partly_active(in, R) ? kAdjBandsPart : 1);
+    const bool part = partly_active(in, R);
+    const bool few = R.n_btiles < (part && in.n_env == 1 ? kFewAdjTilesOneEnv : kFewAdjTiles);
+    const int bands = few ? kAdjBandsFew : (part ? kAdjBandsPart : 1);
     auto kernel = bands == kAdjBandsFew    ? relaxed_adj_kernel<WC, FORM, SL, kAdjBandsFew>
                   : bands == kAdjBandsPart ? relaxed_adj_kernel<WC, FORM, SL, kAdjBandsPart>
                                            : relaxed_adj_kernel<WC, FORM, SL, 1>;

@@ -72,3 +72,34 @@ def test_states_of_the_callers(T, k):
     for key, (U1, B1, g1) in got.items():
         assert np.array_equal(U1, U) and np.array_equal(B1, B), key
         assert np.max(np.abs(g1 - g)) <= 1e-11 * np.max(np.abs(g)), key
+
+
+@pytest.mark.parametrize("n", [99, 100, 127, 128])
+def test_gradient_on_both_sides_of_the_band_lines(n):
+    """n envs of 8 tiles, around the numbers of tiles at which the adjoint and
+    the forward change their row bands: the sum of the envs' own gradients,
+    whose sums only run in another order."""
+    batch = firegen.landscape_batch(105, [(128, 128)] * n)
+    params = _params(105)
+    rng = np.random.default_rng(10)
+    seed_u = rng.normal(size=batch.n_cells)
+    T, k = 6, 3
+
+    def gradient(sub, cells):
+        sim = fs.FireSim.from_batch(sub, params, seed=0)
+        p = fs.make_params(params)
+        p.unburnable_mask = sub.unburnable_mask
+        U, B = sim.relaxed_init()
+        ws = sim.relaxed_workspace(T, k)
+        sim.relaxed_fwd(p, U, B, T, k, ws, "product")
+        return U.cpu().numpy(), sim.relaxed_bwd(p, torch.from_numpy(seed_u[cells]).cuda(), None, T, k, ws,
+                                                "product").cpu().numpy()
+
+    U, g = gradient(batch, slice(0, batch.n_cells))
+    whole = np.zeros(17)
+    for a in range(0, n, 50):
+        cells = slice(a * 128 * 128, min(n, a + 50) * 128 * 128)
+        part, gp = gradient(batch.subset(range(a, min(n, a + 50))), cells)
+        assert np.array_equal(part, U[cells])
+        whole += gp
+    assert np.max(np.abs(whole - g)) <= 1e-11 * np.max(np.abs(g))
