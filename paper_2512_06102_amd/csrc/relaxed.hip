@@ -84,6 +84,14 @@ RelaxedArgs relaxed_args(const sim_params& p)
     return a;
 }
 
+bool finite_params(const sim_params& p)
+{
+    bool ok = true;
+    for (float v : {p.p_base, p.alpha_gamma, p.alpha_w1, p.alpha_w2, p.alpha_s, p.p_continue}) ok = ok && std::isfinite(v);
+    for (float v : p.veg) ok = ok && std::isfinite(v);
+    return ok;
+}
+
 struct Veg11 {
     float v[11];
 };
@@ -1599,10 +1607,11 @@ hipError_t relaxed_forward(hipStream_t s, const RelaxedInputs& in, const sim_par
     hipError_t e = fuel(s, in, p, g);
     // sparse: tiles with initial burning mass and their integral images, kept in
     // the workspace for the backward; a dense forward notes that it is one
-    // (B' = N + p_continue B is not 0 out of reach if p_continue is not finite)
+    // (as it is under parameters that are not finite: what is 0 out of reach of the
+    // fire, the terms of edges without burning mass and p_continue B, then is not)
     int32_t* const r = R.sparse_lds > 0 ? reinterpret_cast<int32_t*>(ws + L.reach) : nullptr;
     const int32_t* reach = nullptr;
-    if (r && in.sparse && std::isfinite(p.p_continue)) {
+    if (r && in.sparse && finite_params(p)) {
         int32_t* mass = r + kReachHead + 4 * (size_t)R.n_btiles;
         if (e == hipSuccess) {
             hipLaunchKernelGGL(first_state_kernel, dim3(R.n_btiles), dim3(256), 0, s, R.d_btiles, in.envs, U, B, ckpt,

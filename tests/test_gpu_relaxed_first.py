@@ -103,3 +103,28 @@ def test_gradient_on_both_sides_of_the_band_lines(n):
         assert np.array_equal(part, U[cells])
         whole += gp
     assert np.max(np.abs(whole - g)) <= 1e-11 * np.max(np.abs(g))
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("name", ["p_base", "alpha_gamma", "alpha_w1", "alpha_w2", "alpha_s", "veg"])
+def test_parameters_that_are_not_finite(name, value):
+    """Under such a parameter (a calibration that has diverged) edges without
+    burning mass are no longer 0: the states are those of the dense forward,
+    far from the fire too."""
+    batch = firegen.landscape_batch(106, [(200, 300), (40, 70)], ign_range=(1, 1))
+    params = _params(106)
+    got = []
+    for sparse in (0, 1):
+        sim = fs.FireSim.from_batch(batch, params, seed=0)
+        sim.set_plan(sparse=sparse)
+        p = fs.make_params(params)
+        p.unburnable_mask = batch.unburnable_mask
+        if name == "veg":
+            p.veg[1] = value
+        else:
+            setattr(p, name, value)
+        U, B = sim.relaxed_init()
+        sim.relaxed_fwd(p, U, B, 6, 3, sim.relaxed_workspace(6, 3), "product")
+        got.append((U.cpu().numpy(), B.cpu().numpy()))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b, equal_nan=True)
