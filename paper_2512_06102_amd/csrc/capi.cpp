@@ -381,6 +381,8 @@ int plane_threads_for(int64_t cells, int64_t per_cu)
     return cells < 1536 ? 64 : (per_cu > 3 ? 256 : 512);
 }
 
+EnvDev env_dev(const sim_env& v) { return EnvDev{v.offset, v.H, v.W, v.env_id, v.V, v.Vx, v.Vy, 0}; }
+
 // Envs of more cells than this weigh on one workgroup: see thick_fires and
 // set_plane_min_steps.
 constexpr int64_t kLargeEnvCells = 160 * 160;
@@ -464,6 +466,7 @@ int build_planes(sim_handle* h, PlanGroup& g)
         const int32_t e = g.envs.empty() ? q : g.envs[q];
         const int H = h->envs[e].H, W = h->envs[e].W;
         const int64_t cells = (int64_t)H * W;
+        const EnvDev dev = env_dev(h->envs[e]);
         const int threads = g.plan.resident ? g.plan.resident : plane_threads_for(cells, n_members / cus);
         const size_t lds =
             plane_lds_bytes(plane_frame_words(H, W), 3, threads, plane_list_cap(H, W));
@@ -478,7 +481,7 @@ int build_planes(sim_handle* h, PlanGroup& g)
         for (int i = 0; i < nr; ++i)
             for (int j = 0; j < nc; ++j) {
                 parts.push_back(PlaneTile{e, i * kPartRows, j * kPartCols, std::min(kPartRows, H - i * kPartRows),
-                                          std::min(kPartCols, W - j * kPartCols)});
+                                          std::min(kPartCols, W - j * kPartCols), dev});
                 for (int di = -1; di <= 1; ++di)
                     for (int dj = -1; dj <= 1; ++dj) {
                         if (di == 0 && dj == 0) continue;
@@ -517,7 +520,7 @@ int build_planes(sim_handle* h, PlanGroup& g)
         L.n_tiles += 1;
         L.frame_words = std::max(L.frame_words, frame_words);
         L.list_cap = std::max(L.list_cap, list_cap);
-        tiles.push_back(PlaneTile{w.env, 0, 0, H, W});
+        tiles.push_back(PlaneTile{w.env, 0, 0, H, W, env_dev(h->envs[w.env])});
     }
     const size_t n_whole = tiles.size(), n_parts = parts.size();
     tiles.insert(tiles.end(), parts.begin(), parts.end());
@@ -717,7 +720,6 @@ hipError_t enqueue_planes(sim_handle* h, PlanGroup& g, hipStream_t s, const Step
 {
     hipError_t e;
     auto with_inputs = [&](PlaneLaunch P) {
-        P.envs = h->d_envs;
         P.n_env = h->n_env;
         P.fields = L.fields;
         P.args = L.args;

@@ -45,6 +45,7 @@
 
 #include "bitplane.hpp"
 #include "devmath.hpp"
+#include "framed.hpp"
 #include "internal.hpp"
 #include "plane.hpp"
 #include "stepcell.hpp"
@@ -84,7 +85,6 @@ __device__ __forceinline__ uint32_t lds_add(uint32_t* p, uint32_t x)
 struct PlaneArgs {
     const PlaneTile* tiles;
     int32_t n_tiles, frame_words, list_cap, has_u;
-    const EnvDev* envs;
     int32_t n_env;
     StaticFields F;
     StepArgs A;
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
         }
     }
     const PlaneTile td = K.tiles[tix];
-    const EnvDev ed = K.envs[td.env];
+    const EnvDev ed = td.dev;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int H = ed.H, W = ed.W;
@@ -191,14 +191,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     uint32_t* const pU = nxt + K.frame_words;
     uint16_t* const list = reinterpret_cast<uint16_t*>(pF + (3 + (HALO ? K.has_u : 0)) * K.frame_words);
 
-    // -- planes cleared (frames included), then filled from the source bytes
-    for (int i = tid; i < (3 + (HALO ? K.has_u : 0)) * K.frame_words; i += NT) pF[i] = 0u;
-    if (tid < 2) s_n[tid] = 0u;
-    if (tid < 3) s_all[tid] = 0u;
-    if (tid < kPlaneChunk) s_tile[tid] = 0u;
-    __syncthreads();
-    const int g_step = G <= NT ? G : NT, g_rows = G <= NT ? NT / G : 1;
-    const int my_g = G <= NT ? tid % G : tid, my_gr = G <= NT ? tid / G : 0;
+    // how the lanes share the cells (small_div: run-time divisions are long, and
+    // a call of few steps on a small env is little more than its start)
+    const float inv_g = 1.0f / (float)G;
+    const int g_step = G <= NT ? G : NT, g_rows = G <= NT ? small_div(NT, G, inv_g) : 1;
+    const int my_gr = G <= NT ? small_div(tid, G, inv_g) : 0, my_g = tid - my_gr * G;
     auto load4 = [&](const uint8_t* p, int col) -> uint32_t {
         if constexpr (ALIGNED) {
             return *reinterpret_cast<const uint32_t*>(p);
@@ -210,13 +207,44 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
             return v;
         }
     };
+    // on its way while the planes are cleared: this lane's first group
+    uint32_t w_first = 0;
+    if (my_gr < g_rows && my_g < G && my_gr < RH)
+        w_first = load4(K.src + base + (uint32_t)((q0 + my_gr) * W + p0 + 4 * my_g), p0 + 4 * my_g);
+
+    const uint32_t t0 = *K.t_base + K.step0;
+    const bool ew_series = RATES == kRatesEnvWind && K.F.env_wind != nullptr;
+    // the drops and wind of the steps from s0 on
+    auto stage = [&](int32_t s0) {
+        const int nk = min(kPlaneChunk, K.steps - s0);
+        if (K.actions)
+            for (int j = tid; j < nk; j += NT) s_act[j] = K.actions[(int64_t)(s0 + j) * K.n_env + td.env];
+        if (ew_series)
+            for (int q = tid; q < nk * 8; q += NT) {
+                const int j = q >> 3, d = q & 7;
+                const float* w = K.F.env_wind + ((int64_t)(t0 + (uint32_t)s0 + j) * K.F.n_env + td.env) * 3;
+                s_ew[j][d] = wind_exponent(d, K.A.alpha_w1, K.A.alpha_w2, w[0], w[1], w[2]);
+            }
+    };
+    stage(0);
+    if (RATES == kRatesEnvWind && !ew_series && tid < 8)
+        s_ew[0][tid] = wind_exponent(tid, K.A.alpha_w1, K.A.alpha_w2, ed.V, ed.Vx, ed.Vy);
+
+    // -- planes cleared (frames included), then filled from the source bytes
+    for (int i = tid; i < (3 + (HALO ? K.has_u : 0)) * K.frame_words; i += NT) pF[i] = 0u;
+    if (tid < 2) s_n[tid] = 0u;
+    if (tid < 3) s_all[tid] = 0u;
+    if (tid < kPlaneChunk) s_tile[tid] = 0u;
+    __syncthreads();
     {
         uint32_t any = 0;
         if (my_gr < g_rows)
             for (int g = my_g; g < G; g += g_step)
                 for (int r = my_gr; r < RH; r += g_rows) {
                     const int col = p0 + 4 * g;
-                    const uint32_t w = load4(K.src + base + (uint32_t)((q0 + r) * W + col), col);
+                    const uint32_t w = g == my_g && r == my_gr
+                                           ? w_first
+                                           : load4(K.src + base + (uint32_t)((q0 + r) * W + col), col);
                     const uint32_t f = pack4(flammable_flags(w)), bu = pack4(burning_flags(w));
                     const int at = (r + 1) * S + 1 + (g >> 3), sh = 4 * (g & 7);
                     if (f) atomicOr(&pF[at], f << sh);
@@ -248,8 +276,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     // the tile's cells to an array of whole envs
     auto store_tile = [&](uint8_t* out) {
         const int ga = tc0 >> 2, gn = (tc1 - tc0 + 3) >> 2;
-        const int st = gn <= NT ? gn : NT, rows = gn <= NT ? NT / gn : 1;
-        const int g0 = gn <= NT ? tid % gn : tid, r0 = gn <= NT ? tid / gn : 0;
+        const float inv = 1.0f / (float)gn;
+        const int st = gn <= NT ? gn : NT, rows = gn <= NT ? small_div(NT, gn, inv) : 1;
+        const int r0 = gn <= NT ? small_div(tid, gn, inv) : 0, g0 = tid - r0 * gn;
         if (r0 >= rows) return;
         for (int g = g0; g < gn; g += st)
             for (int r = tr0 + r0; r < tr1; r += rows) {
@@ -267,13 +296,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     };
 
     const uint2 key = make_uint2(K.A.key0, K.A.key1);
-    const uint32_t t0 = *K.t_base + K.step0;
-    const bool ew_series = RATES == kRatesEnvWind && K.F.env_wind != nullptr;
     // scan: lane (word column, strip of rows)
-    const int w_step = WW <= NT ? WW : NT, n_strips = WW <= NT ? NT / WW : 1;
-    const int my_w = WW <= NT ? tid % WW : tid, my_strip = WW <= NT ? tid / WW : 0;
-    if (RATES == kRatesEnvWind && !ew_series && tid < 8)
-        s_ew[0][tid] = wind_exponent(tid, K.A.alpha_w1, K.A.alpha_w2, ed.V, ed.Vx, ed.Vy);
+    const float inv_ww = 1.0f / (float)WW;
+    const int w_step = WW <= NT ? WW : NT, n_strips = WW <= NT ? small_div(NT, WW, inv_ww) : 1;
+    const int my_strip = WW <= NT ? small_div(tid, WW, inv_ww) : 0, my_w = tid - my_strip * WW;
 
     // the counts of `n` steps from step `first` on, and their slots cleared
     auto flush_counts = [&](int32_t first, int32_t n) {
@@ -288,9 +314,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
             atomicAdd(row, (int32_t)c);
     };
 
-    const int per = (RH + n_strips - 1) / n_strips;  // rows of a strip
+    const int per = small_div(RH + n_strips - 1, n_strips, 1.0f / (float)n_strips);  // rows of a strip
     // groups per row padded to whole words; this lane's first in a dense pass
-    const int GW = 8 * WW, dense_r = tid / GW, dense_g = tid - dense_r * GW;
+    const int GW = 8 * WW, dense_r = small_div(tid, GW, 0.125f * inv_ww), dense_g = tid - dense_r * GW;
+    const int dense_step = small_div(NT, GW, 0.125f * inv_ww), dense_rest = NT - dense_step * GW;
     const bool small = !HALO && RH * GW <= kSmallRounds * NT;
     bool quiet = false, stopped = false;
     int32_t s = 0;
@@ -298,20 +325,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     for (; s < K.steps; ++s, s3 = s3 == 2 ? 0 : s3 + 1) {
         const uint32_t t = t0 + (uint32_t)s;
         const int kc = s % kPlaneChunk;
-        if (kc == 0) {
-            if (s > 0) {
-                lds_barrier();  // the last chunk's drops and wind are read, its counts summed
-                flush_counts(s - kPlaneChunk, kPlaneChunk);
-            }
-            const int nk = min(kPlaneChunk, K.steps - s);
-            if (K.actions)
-                for (int j = tid; j < nk; j += NT) s_act[j] = K.actions[(int64_t)(s + j) * K.n_env + td.env];
-            if (ew_series)
-                for (int q = tid; q < nk * 8; q += NT) {
-                    const int j = q >> 3, d = q & 7;
-                    const float* w = K.F.env_wind + ((int64_t)(t + j) * K.F.n_env + td.env) * 3;
-                    s_ew[j][d] = wind_exponent(d, K.A.alpha_w1, K.A.alpha_w2, w[0], w[1], w[2]);
-                }
+        if (kc == 0 && s > 0) {
+            lds_barrier();  // the last chunk's drops and wind are read, its counts summed
+            flush_counts(s - kPlaneChunk, kPlaneChunk);
+            stage(s);
         }
         lds_barrier();  // F_t complete, the chunk staged, the last step's cells counted
         const uint32_t prev = s_all[s3 == 0 ? 2 : s3 - 1];
@@ -479,8 +496,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
                 on = rd < hi;
                 r = on ? rd : lo;
                 g = gd;
-                rd += NT / GW;
-                gd += NT % GW;
+                rd += dense_step;
+                gd += dense_rest;
                 if (gd >= GW) {
                     gd -= GW;
                     ++rd;
@@ -715,7 +732,6 @@ hipError_t launch_stoch_plane(hipStream_t s, const PlaneLaunch& L, const uint8_t
     K.frame_words = L.frame_words;
     K.list_cap = L.list_cap;
     K.has_u = L.halo && actions && L.args.drop_mode == 0 ? 1 : 0;
-    K.envs = L.envs;
     K.n_env = L.n_env;
     K.F = L.fields;
     K.A = L.args;

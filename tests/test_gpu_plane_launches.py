@@ -31,3 +31,21 @@ def test_strip_and_square(sizes, series):
     got = sim.step(T, counts=True)
     assert np.array_equal(got.cpu().numpy(), want)
     assert np.array_equal(sim.states.cpu().numpy(), ref.states)
+
+
+@pytest.mark.parametrize("mode", [None, 0])
+@pytest.mark.parametrize("size", [(1, 32767), (1, 4100), (2, 9000), (3, 2500), (8000, 1), (4100, 2), (700, 33)])
+def test_one_env_wide_or_tall(size, mode):
+    """More groups or words per row than lanes, and more rows than lanes: the
+    ends of the divisions that deal cells out to them."""
+    T = 40
+    batch = firegen.landscape_batch(93, [size], ign_range=(30, 30))
+    params = firegen.Params(p_base=0.9, veg=tuple(float(v) for v in firegen.veg_table(np.random.default_rng(93))))
+    act = None if mode is None else firegen.random_actions(47, batch, T, p_none=0.3)
+    ref = oracle.Sim(batch, params, seed=14)
+    want = ref.step(T, actions=act, counts=True, threads=8, drop_mode=mode or 0, drop_radius=2)
+    sim = fs.FireSim.from_batch(batch, params, seed=14)
+    sim.set_drop(mode or 0, 2)
+    got = sim.step(T, actions=None if act is None else torch.from_numpy(act), counts=True)
+    assert np.array_equal(got.cpu().numpy(), want)
+    assert np.array_equal(sim.states.cpu().numpy(), ref.states)
