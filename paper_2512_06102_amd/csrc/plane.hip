@@ -55,6 +55,7 @@ namespace {
 
 constexpr int kScanRows = 4;     // rows scanned between two listings
 constexpr int kSmallRounds = 1;  // a region of up to so many groups per lane is not scanned
+constexpr int kDeal = 16;        // listed groups a wave takes at a time, without the table
 
 constexpr int32_t kPartRun = 1, kPartRan = 2;  // marks of a part for the next launch
 
@@ -487,7 +488,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
             wave_sync();
         };
         int rd = lo + dense_r, gd = dense_g;
-        // a list is dealt out entry by entry: a short one keeps every wave busy
+        // a list is dealt out entry by entry: a short one keeps every wave busy.
+        // Without the table a wave evaluates its front cells 64 at a time, at one
+        // price for few and many: kDeal entries at a time fill fewer waves (226
+        // envs of 136 x 36, 60 steps of a wind series: 315 us one by one, 270 by
+        // 8, 252 by 16, 235 by 32; 8 of 100 x 200 328, 325, 332 and 354 us)
         const int n_rounds = (n_work + NT - 1) / NT;
         for (int k = 0; k < n_rounds; ++k) {
             bool on;
@@ -503,7 +508,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
                     ++rd;
                 }
             } else {
-                const int i = NW * (64 * k + lane) + wv;
+                const int i = RATES == kRatesTable ? NW * (64 * k + lane) + wv
+                                                   : kDeal * (NW * (64 / kDeal * k + lane / kDeal) + wv) + lane % kDeal;
                 on = i < n_work;
                 const uint32_t id = on ? list[i] : 0u;
                 r = (int)(id >> gshift);

@@ -62,3 +62,22 @@ def test_history_of_every_step(size, threads, mode, series):
     assert np.array_equal(hist.cpu().numpy(), rows)
     assert np.array_equal(got.cpu().numpy(), want)
     assert np.array_equal(sim.states.cpu().numpy(), rows[-1])
+
+
+@pytest.mark.parametrize("size,threads", [((136, 36), 1024), ((132, 52), 512), ((100, 200), 256), ((65, 33), 64)])
+def test_lists_dealt_out_without_the_table(size, threads):
+    """Envs just too large for that, under a series: the listed groups go to the
+    waves several at a time, with fewer waves than lists and more."""
+    batch = firegen.landscape_batch(94, [size] * 6, ign_range=(1, 6))
+    params = firegen.Params(p_base=0.8, p_continue=0.7,
+                            veg=tuple(float(v) for v in firegen.veg_table(np.random.default_rng(94))))
+    wind = firegen.wind_series(12, batch, T, speed_step=1.0, turn_step=0.3)
+    ref = oracle.Sim(batch, params, seed=15)
+    want = ref.step(T, counts=True, threads=8, wind_env_series=wind)
+    sim = fs.FireSim.from_batch(batch, params, seed=15)
+    if sim.n_cells // 6 <= 92 * 92 and size[1] % 4 == 0:
+        sim.set_plan(resident=threads, sparse=1)
+    sim.set_wind_series(env_series=torch.from_numpy(wind).cuda())
+    got = sim.step(T, counts=True)
+    assert np.array_equal(got.cpu().numpy(), want)
+    assert np.array_equal(sim.states.cpu().numpy(), ref.states)
