@@ -328,6 +328,9 @@ int sim_set_rate_table(sim_handle* h, int32_t on, void* stream);
  * and, if allow_skip and every env has W % 4 == 0, temporal 2/4/8 x
  * tile_width 64/128; and, if allow_skip and the batch fits it, resident
  * 64/256/512/1024)
+ * (the plans that run on the bit-plane kernel with its own workgroup sizes,
+ * whatever their tiles, are one launch: timed once, tile_rows 4 and tile_width
+ * 64 listed first)
  * for T_probe steps of this batch starting from `states` (device, read only)
  * at the handle's step counter, and makes the fastest the handle's plan
  * (graph flag kept).  Plans are ranked on those steps alone, and which plan
@@ -394,7 +397,9 @@ int sim_get_class_plans(const sim_handle* h, sim_class_plan* out, int32_t max_ou
  *              count, cells and largest H and W, whether all its envs have
  *              W % 4 == 0 and 4-aligned offsets, the wind kind (per env,
  *              per cell, per-env series, per-cell series), T_probe,
- *              allow_skip and allow_sparse -- and a plan.  A class whose key
+ *              allow_skip, allow_sparse, the version of the library's step
+ *              kernels and whether the table of ignition rates is there --
+ *              and a plan.  A class whose key
  *              is in the file (the last such line wins) takes its plan
  *              without timing; each class timed is appended as one line.
  *              SIM_EINVAL if the file exists but cannot be read, or cannot
