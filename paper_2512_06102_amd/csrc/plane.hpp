@@ -32,11 +32,11 @@ constexpr int kPlaneHaloThreads = 256;
 constexpr size_t kPlaneStaticLds = 1536;
 
 // Words of one bit plane of a region: rows of ceil(cols / 32) words and one
-// zero word between rows, a zero row above and four below (the scan reads
-// four rows at a time).
+// zero word between rows, a zero row above and below and one word more (the
+// right neighbour of the last one).
 inline int64_t plane_frame_words(int64_t rows, int64_t cols)
 {
-    return (rows + 5) * ((cols + 31) / 32 + 1) + 1;
+    return (rows + 2) * ((cols + 31) / 32 + 1) + 1;
 }
 // A listed group is rows << shift | group column in 16 bits.
 inline bool plane_indexable(int64_t rows, int64_t cols)
