@@ -192,11 +192,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     uint32_t* const pU = nxt + K.frame_words;
     uint16_t* const list = reinterpret_cast<uint16_t*>(pF + (3 + (HALO ? K.has_u : 0)) * K.frame_words);
 
-    // how the lanes share the cells (small_div: run-time divisions are long, and
-    // a call of few steps on a small env is little more than its start)
+    // how the lanes share the cells.  (Run-time divisions are long, and a call of
+    // few steps on a small env is little more than its start; the variants that
+    // have no registers to spare take the short form badly: 8 envs of 2048 x
+    // 2048 in parts ran 5% slower.)
+    auto share = [&](int q, int d, float inv_d) { return ALIGNED && !HALO ? small_div(q, d, inv_d) : q / d; };
     const float inv_g = 1.0f / (float)G;
-    const int g_step = G <= NT ? G : NT, g_rows = G <= NT ? small_div(NT, G, inv_g) : 1;
-    const int my_gr = G <= NT ? small_div(tid, G, inv_g) : 0, my_g = tid - my_gr * G;
+    const int g_step = G <= NT ? G : NT, g_rows = G <= NT ? share(NT, G, inv_g) : 1;
+    const int my_gr = G <= NT ? share(tid, G, inv_g) : 0, my_g = tid - my_gr * G;
     auto load4 = [&](const uint8_t* p, int col) -> uint32_t {
         if constexpr (ALIGNED) {
             return *reinterpret_cast<const uint32_t*>(p);
@@ -278,8 +281,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     auto store_tile = [&](uint8_t* out) {
         const int ga = tc0 >> 2, gn = (tc1 - tc0 + 3) >> 2;
         const float inv = 1.0f / (float)gn;
-        const int st = gn <= NT ? gn : NT, rows = gn <= NT ? small_div(NT, gn, inv) : 1;
-        const int r0 = gn <= NT ? small_div(tid, gn, inv) : 0, g0 = tid - r0 * gn;
+        const int st = gn <= NT ? gn : NT, rows = gn <= NT ? share(NT, gn, inv) : 1;
+        const int r0 = gn <= NT ? share(tid, gn, inv) : 0, g0 = tid - r0 * gn;
         if (r0 >= rows) return;
         for (int g = g0; g < gn; g += st)
             for (int r = tr0 + r0; r < tr1; r += rows) {
@@ -299,8 +302,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     const uint2 key = make_uint2(K.A.key0, K.A.key1);
     // scan: lane (word column, strip of rows)
     const float inv_ww = 1.0f / (float)WW;
-    const int w_step = WW <= NT ? WW : NT, n_strips = WW <= NT ? small_div(NT, WW, inv_ww) : 1;
-    const int my_strip = WW <= NT ? small_div(tid, WW, inv_ww) : 0, my_w = tid - my_strip * WW;
+    const int w_step = WW <= NT ? WW : NT, n_strips = WW <= NT ? share(NT, WW, inv_ww) : 1;
+    const int my_strip = WW <= NT ? share(tid, WW, inv_ww) : 0, my_w = tid - my_strip * WW;
 
     // the counts of `n` steps from step `first` on, and their slots cleared
     auto flush_counts = [&](int32_t first, int32_t n) {
@@ -315,10 +318,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
             atomicAdd(row, (int32_t)c);
     };
 
-    const int per = small_div(RH + n_strips - 1, n_strips, 1.0f / (float)n_strips);  // rows of a strip
+    const int per = share(RH + n_strips - 1, n_strips, 1.0f / (float)n_strips);  // rows of a strip
     // groups per row padded to whole words; this lane's first in a dense pass
-    const int GW = 8 * WW, dense_r = small_div(tid, GW, 0.125f * inv_ww), dense_g = tid - dense_r * GW;
-    const int dense_step = small_div(NT, GW, 0.125f * inv_ww), dense_rest = NT - dense_step * GW;
+    const int GW = 8 * WW, dense_r = share(tid, GW, 0.125f * inv_ww), dense_g = tid - dense_r * GW;
     const bool small = !HALO && RH * GW <= kSmallRounds * NT;
     bool quiet = false, stopped = false;
     int32_t s = 0;
@@ -501,8 +503,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
                 on = rd < hi;
                 r = on ? rd : lo;
                 g = gd;
-                rd += dense_step;
-                gd += dense_rest;
+                rd += NT / GW;
+                gd += NT % GW;
                 if (gd >= GW) {
                     gd -= GW;
                     ++rd;
