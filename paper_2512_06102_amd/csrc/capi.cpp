@@ -404,7 +404,7 @@ bool thick_fires(const sim_handle* h, int64_t cells)
 // where its planes fit LDS and its fires stay thin, else in parts of kPartRows x
 // kPartCols.
 constexpr int kPartRows = 64, kPartCols = 128, kPartSteps = 24;
-constexpr int kSideSteps = 4;  // fewest steps for which launches run beside each other
+constexpr int32_t kSideSteps = 4;  // fewest steps for which launches run beside each other
 
 // The fewest steps of a call for which the bit-plane kernel, which first takes
 // an env's states into LDS and at last writes them back, beats one launch per
@@ -415,6 +415,8 @@ constexpr int kSideSteps = 4;  // fewest steps for which launches run beside eac
 //   1 of 512 x 512          43  18 |  58  38 |  65  46 |  79  66 | 100  94
 //   128 of 512 x 512        63  44 |  79  85 |  86  94
 //   1024 of 256 x 256       74  84 | 100 187 | 113 212
+//   256 of 512 x 512        71  67 |  90 137 |  99 150
+//   256 each of 64, 128, 256 and 512 squared 173 99 | 221 210 | (6 steps) 214 322
 //   1 of 640 x 640 in parts 45  18 |  40  38 |  44  45 |  52  67
 //   16 of 1024 x 1024       118  32 |  88  65 |  94  70 | 103 103 | 114 137
 //   8 of 2048 x 2048        339  41 | 129  79 | 135  86 | 143 122 | 151 162
@@ -427,6 +429,9 @@ void set_plane_min_steps(PlanGroup& g, int64_t n_large, int64_t largest, int cus
     const bool fills = n_large >= cus;  // a large env for every compute unit
     int32_t steps = 1;
     if (n_large > 0 && !fills) steps = 4 * n_large >= cus || largest <= 256 * 256 ? 3 : 10;
+    if (fills && largest > 256 * 256) steps = 2;
+    // envs of several kinds run beside each other from kSideSteps steps on
+    if (n_large > 0 && g.plane_whole.size() > 1) steps = std::max(steps, kSideSteps);
     if (g.plane_parts.n_tiles) steps = std::max(steps, 4 + std::min(g.plane_parts.n_tiles / 1024, 4));
     g.min_steps = steps;
     // (a history of envs in parts needs each state in memory between the steps)
