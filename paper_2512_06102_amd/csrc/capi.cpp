@@ -1185,7 +1185,7 @@ int sim_rl_reset(sim_handle* h, const sim_rl_config* cfg, uint8_t* states, sim_r
     RlAgent* ag = reinterpret_cast<RlAgent*>(agents);
     HIP_OR_FAIL(h, launch_rl_reset(s, h->d_envs, h->n_env, h->d_cls, h->params.unburnable_mask, states, ag,
                                    reset_mask, (uint32_t)h->seed, (uint32_t)(h->seed >> 32), episode,
-                                   cfg->water_capacity));
+                                   cfg->water_capacity, h->n_cells));
     HIP_OR_FAIL(h, launch_rl_obs(s, h->d_envs, h->n_env, states, ag, nullptr, rl_dev(cfg), obs, nullptr,
                                  done_out));
     return SIM_OK;

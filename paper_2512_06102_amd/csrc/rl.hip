@@ -25,7 +25,16 @@
 namespace firesim {
 namespace {
 
-constexpr int kRlWaves = 4;       // envs (waves) per workgroup
+constexpr int kRlWaves = 4;       // waves per workgroup
+// An env of more cells (on average) is reset by 4 waves, not 1.  Measured, us per
+// reset with 1 and 4: 4096 envs of 64 x 64 12.9 13.9; 1024 of 76 x 76 11.7 11.0;
+// 64 of 128 x 128 17.5 11.3; 1 of 1000 x 1000 626 186.
+constexpr int64_t kRlLargeCells = 4096;
+// A window of more cells is written by 4 waves in batches of no more envs.
+// Measured, us per step in separate launches: 64 envs of 92 x 92, windows of 121
+// cells 20.1 19.8, 289 20.8 20.4, 3969 36.3 21.1; 65536 envs of 20 x 20, 289 86 103,
+// 3969 190 204; 4096 of 64 x 64, 289 35.0 34.1, 3969 57.8 45.0.
+constexpr int kRlLargeWindow = 256, kRlLargeWindowEnvs = 8192;
 constexpr int kRlWaveList = 128;  // front cells listed per wave
 constexpr uint8_t kOutside = 4;  // observation code of cells beyond the grid
 
@@ -34,9 +43,10 @@ __device__ __forceinline__ int32_t scale_draw(uint32_t w, int32_t n)
     return (int32_t)(((uint64_t)w * (uint64_t)n) >> 32);  // uniform in 0..n-1
 }
 
-// One wave per env, kRlWaves envs per workgroup: lanes 0 to 7 draw the eight
-// ignition attempts at once, then the wave writes the cells, the ignited one
-// among them.
+// kWaves waves per env, kRlWaves waves per workgroup: lanes 0 to 7 of each draw
+// the eight ignition attempts at once, then the env's waves write the cells, the
+// ignited one among them.
+template <int kWaves>
 __global__ __launch_bounds__(64 * kRlWaves) void rl_reset_kernel(const EnvDev* __restrict__ envs, int32_t n_env,
                                                        const uint8_t* __restrict__ cls,
                                                        uint32_t unburnable_mask,
@@ -44,8 +54,9 @@ __global__ __launch_bounds__(64 * kRlWaves) void rl_reset_kernel(const EnvDev* _
                                                        const int32_t* __restrict__ reset_mask, uint2 key,
                                                        uint64_t episode, int32_t water)
 {
-    const int lane = threadIdx.x & 63;
-    const int e = blockIdx.x * kRlWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int e = blockIdx.x * (kRlWaves / kWaves) + wv / kWaves;
+    const int me = 64 * (wv % kWaves) + lane;  // of the env's 64 kWaves lanes
     if (e >= n_env || (reset_mask && reset_mask[e] == 0)) return;
     const EnvDev ed = envs[e];
     const int64_t n = (int64_t)ed.H * ed.W;
@@ -68,7 +79,7 @@ __global__ __launch_bounds__(64 * kRlWaves) void rl_reset_kernel(const EnvDev* _
     if (((ed.offset | n | (int64_t)(uintptr_t)states) & 3) == 0) {
         const uint32_t* c4 = reinterpret_cast<const uint32_t*>(cls + ed.offset);
         uint32_t* s4 = reinterpret_cast<uint32_t*>(states + ed.offset);
-        for (int64_t i = lane; i < (n >> 2); i += 64) {
+        for (int64_t i = me; i < (n >> 2); i += 64 * kWaves) {
             const uint32_t c = c4[i];
             uint32_t v = 0;
 #pragma unroll
@@ -76,9 +87,9 @@ __global__ __launch_bounds__(64 * kRlWaves) void rl_reset_kernel(const EnvDev* _
             s4[i] = v;
         }
     } else {
-        for (int64_t i = lane; i < n; i += 64) states[ed.offset + i] = (uint8_t)fresh(cls[ed.offset + i], i);
+        for (int64_t i = me; i < n; i += 64 * kWaves) states[ed.offset + i] = (uint8_t)fresh(cls[ed.offset + i], i);
     }
-    if (lane != 0) return;
+    if (me != 0) return;
     RlAgent a{};
     a.row = scale_draw(w.z, ed.H);
     a.col = scale_draw(w.w, ed.W);
@@ -113,7 +124,8 @@ __global__ __launch_bounds__(256) void rl_act_kernel(const EnvDev* __restrict__ 
 }
 
 // counts == nullptr: observation only (after a reset), reward 0.
-// One wave per env, kRlWaves envs per workgroup.
+// kWaves waves per env, kRlWaves waves per workgroup.
+template <int kWaves>
 __global__ __launch_bounds__(64 * kRlWaves) void rl_obs_kernel(const EnvDev* __restrict__ envs, int32_t n_env,
                                                      const uint8_t* __restrict__ states,
                                                      RlAgent* __restrict__ agents,
@@ -121,11 +133,14 @@ __global__ __launch_bounds__(64 * kRlWaves) void rl_obs_kernel(const EnvDev* __r
                                                      uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                      int32_t* __restrict__ done)
 {
-    const int lane = threadIdx.x & 63;
-    const int e = blockIdx.x * kRlWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int e = blockIdx.x * (kRlWaves / kWaves) + wv / kWaves;
+    const int me = 64 * (wv % kWaves) + lane;  // of the env's 64 kWaves lanes
+    static_assert(kWaves == 1 || kWaves == kRlWaves, "a barrier of the env's waves is one of the workgroup");
     if (e >= n_env) return;
     const EnvDev ed = envs[e];
     RlAgent a = agents[e];
+    if (kWaves > 1) __syncthreads();  // every wave has the agent as it was
     float r = 0.0f;
     if (counts && !a.done) {
         const int32_t c = counts[e];
@@ -134,16 +149,16 @@ __global__ __launch_bounds__(64 * kRlWaves) void rl_obs_kernel(const EnvDev* __r
         a.steps += 1;
         a.last_count = c;
         a.done = (c == 0 || a.steps >= cfg.max_steps) ? 1 : 0;
-        if (lane == 0) agents[e] = a;
+        if (me == 0) agents[e] = a;
     }
-    if (lane == 0) {
+    if (me == 0) {
         if (reward) reward[e] = r;
         if (done) done[e] = a.done;
     }
     const int R = cfg.obs_radius, side = 2 * R + 1, n = side * side;
     const float inv_side = 1.0f / (float)side;
     uint8_t* o = obs + (int64_t)e * n;
-    for (int i = lane; i < n; i += 64) {
+    for (int i = me; i < n; i += 64 * kWaves) {
         const int di = small_div(i, side, inv_side);
         const int gi = a.row - R + di, gj = a.col - R + (i - di * side);
         o[i] = (gi >= 0 && gi < ed.H && gj >= 0 && gj < ed.W) ? states[ed.offset + (int64_t)gi * ed.W + gj]
@@ -417,11 +432,14 @@ hipError_t launch_rl_step_fused(hipStream_t s, const EnvDev* envs, int32_t n_env
 hipError_t launch_rl_reset(hipStream_t s, const EnvDev* envs, int32_t n_env, const uint8_t* cls,
                            uint32_t unburnable_mask, uint8_t* states, RlAgent* agents,
                            const int32_t* reset_mask, uint32_t key0, uint32_t key1, uint64_t episode,
-                           int32_t water)
+                           int32_t water, int64_t n_cells)
 {
     if (n_env <= 0) return hipSuccess;
-    hipLaunchKernelGGL(rl_reset_kernel, dim3((n_env + kRlWaves - 1) / kRlWaves), dim3(64 * kRlWaves), 0, s, envs,
-                       n_env, cls, unburnable_mask, states, agents, reset_mask, make_uint2(key0, key1), episode, water);
+    const bool large = n_cells > kRlLargeCells * n_env;
+    auto kernel = large ? rl_reset_kernel<kRlWaves> : rl_reset_kernel<1>;
+    const int grid = large ? n_env : (n_env + kRlWaves - 1) / kRlWaves;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * kRlWaves), 0, s, envs, n_env, cls, unburnable_mask, states,
+                       agents, reset_mask, make_uint2(key0, key1), episode, water);
     return hipGetLastError();
 }
 
@@ -439,8 +457,12 @@ hipError_t launch_rl_obs(hipStream_t s, const EnvDev* envs, int32_t n_env, const
                          float* reward, int32_t* done)
 {
     if (n_env <= 0) return hipSuccess;
-    hipLaunchKernelGGL(rl_obs_kernel, dim3((n_env + kRlWaves - 1) / kRlWaves), dim3(64 * kRlWaves), 0, s, envs, n_env,
-                       states, agents, counts, cfg, obs, reward, done);
+    const int side = 2 * cfg.obs_radius + 1;
+    const bool large = side * side > kRlLargeWindow && n_env <= kRlLargeWindowEnvs;
+    auto kernel = large ? rl_obs_kernel<kRlWaves> : rl_obs_kernel<1>;
+    const int grid = large ? n_env : (n_env + kRlWaves - 1) / kRlWaves;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * kRlWaves), 0, s, envs, n_env, states, agents, counts, cfg, obs,
+                       reward, done);
     return hipGetLastError();
 }
 

@@ -53,7 +53,7 @@ inline size_t rl_fused_lds_bytes(const RlFusedShape& s)
 hipError_t launch_rl_reset(hipStream_t s, const EnvDev* envs, int32_t n_env, const uint8_t* cls,
                            uint32_t unburnable_mask, uint8_t* states, RlAgent* agents,
                            const int32_t* reset_mask, uint32_t key0, uint32_t key1, uint64_t episode,
-                           int32_t water);
+                           int32_t water, int64_t n_cells);
 hipError_t launch_rl_act(hipStream_t s, const EnvDev* envs, int32_t n_env, RlAgent* agents,
                          const int32_t* actions, int32_t* drop_row);
 // One launch per RL step for envs that fit; the fire step is bit-identical to

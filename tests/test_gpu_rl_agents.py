@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import firegen
+from oracle import rl
 
 pytestmark = pytest.mark.gpu
 
@@ -62,3 +63,40 @@ def test_reset_of_states_at_any_address(shift):
         got.append([x.cpu().numpy() for x in out])
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("obs_radius", [7, 8, 31])
+@pytest.mark.parametrize("sizes", [[(64, 64)] * 5, [(64, 65)] * 5, [(70, 60), (130, 129), (33, 20)], [(300, 200)]])
+def test_large_envs_and_windows(sizes, obs_radius):
+    """Resets and observations by one wave and by several, around the lines
+    between them, against the oracle."""
+    batch = firegen.landscape_batch(95, sizes)
+    params = firegen.Params(p_base=0.6, veg=tuple(float(v) for v in firegen.veg_table(np.random.default_rng(95))))
+    cfg = rl.Config(obs_radius=obs_radius, drop_radius=1, water_capacity=6, max_steps=6, burn_penalty=0.1,
+                    extinguish_bonus=10.0)
+    ref = rl.RLEnvs(batch, params, 78, cfg)
+    sim = fs.FireSim.from_batch(batch, params, seed=78)
+    env = fs.RLEnv(sim, obs_radius=obs_radius, drop_radius=1, water_capacity=6, max_steps=6, burn_penalty=0.1,
+                   extinguish_bonus=10.0, single_launch=False)
+
+    def agents():
+        return np.array([[a.row, a.col, a.water, a.steps, a.done, a.last_count] for a in ref.agents], np.int32)
+
+    rng = np.random.default_rng(11)
+    obs, done = env.reset(episode=5)
+    want_obs, want_done = ref.reset(5)
+    for step in range(8):
+        assert np.array_equal(obs.cpu().numpy(), want_obs.reshape(obs.shape)), step
+        assert np.array_equal(done.cpu().numpy(), want_done), step
+        assert np.array_equal(sim.states.cpu().numpy(), ref.sim.states), step
+        assert np.array_equal(env.agents.cpu().numpy()[:, :6], agents()), step
+        act = (rng.integers(0, 9, len(sizes)) | (rng.integers(0, 2, len(sizes)) << 4)).astype(np.int32)
+        obs, reward, done = env.step(torch.from_numpy(act).cuda())
+        want_obs, want_reward, want_done = ref.step(act)
+        assert np.array_equal(reward.cpu().numpy(), want_reward), step
+    mask = (np.arange(len(sizes)) % 2).astype(np.int32)
+    want_obs, _ = ref.reset(6, mask=mask.copy())
+    obs, _ = env.reset(episode=6, mask=torch.from_numpy(mask))
+    assert np.array_equal(obs.cpu().numpy(), want_obs)
+    assert np.array_equal(sim.states.cpu().numpy(), ref.sim.states)
+    assert np.array_equal(env.agents.cpu().numpy()[:, :6], agents())
