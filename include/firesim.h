@@ -281,7 +281,8 @@ int sim_set_step(sim_handle* h, uint64_t t);
  *  sparse       1: after the first step of a call, a tile with no burning
  *               cell in it or in its 8 neighbouring tiles, and no drop on it,
  *               is not computed (its cells cannot change); 0: every tile runs.
- *               In sim_step_relaxed_fwd, 1 computes step s only on tiles within
+ *               In sim_step_relaxed_fwd, 1 computes step s (where the envs have
+ *               8 tiles of 64 x 32 on average, or more) only on tiles within
  *               s + 1 cells of a cell with initial burning mass (B_0 != 0),
  *               the others keep their state, and sim_step_relaxed_bwd on its
  *               workspace skips adjoint step s on tiles farther than that:

@@ -1427,6 +1427,14 @@ RelaxedInputs at_step(const RelaxedInputs& in, int32_t t)
 constexpr int kFwdBands = 4, kFwdBandsFew = 16, kAdjBandsFew = 8, kAdjBandsPart = 4;
 constexpr int kFewFwdTiles = 1024, kFewAdjTiles = 800, kFewAdjTilesOneEnv = 1024;
 
+// Tiles per env from which the sparse plan skips any.  In smaller envs the fire is
+// in reach of every tile soon, and each wave looks it up in every step: dense and
+// sparse, 40 steps forward, 4096 envs of 24 x 24 (1 tile) 1.86 and 1.89 ms, 512 of
+// 64 x 64 (2) 0.80 and 0.83, 1000 of 50 x 70 (4) 2.09 and 2.15, 300 of 96 x 128 (6)
+// 1.28 and 1.29, 256 of 128 x 128 (8) 1.49 and 1.44, 64 of 160 x 320 (25) 1.16 and
+// 1.04; one step forward and back is 2 to 17% longer in the first four.
+constexpr int64_t kSparseTiles = 8;
+
 // Do only some of the tiles run in most steps: large envs under a sparse plan?
 bool partly_active(const RelaxedInputs& in, const RelaxedState& R)
 {
@@ -1611,7 +1619,7 @@ hipError_t relaxed_forward(hipStream_t s, const RelaxedInputs& in, const sim_par
     // fire, the terms of edges without burning mass and p_continue B, then is not)
     int32_t* const r = R.sparse_lds > 0 ? reinterpret_cast<int32_t*>(ws + L.reach) : nullptr;
     const int32_t* reach = nullptr;
-    if (r && in.sparse && finite_params(p)) {
+    if (r && in.sparse && in.n_tiles >= kSparseTiles * (int64_t)in.n_env && finite_params(p)) {
         int32_t* mass = r + kReachHead + 4 * (size_t)R.n_btiles;
         if (e == hipSuccess) {
             hipLaunchKernelGGL(first_state_kernel, dim3(R.n_btiles), dim3(256), 0, s, R.d_btiles, in.envs, U, B, ckpt,
