@@ -303,8 +303,12 @@ int sim_set_step(sim_handle* h, uint64_t t);
  *               step (sparse still applies to the relaxed step).
  * With resident 0, skip_static 1, sparse 1 and temporal 1 the same kernel runs
  * with workgroup sizes of its own choice, for envs of any size: those whose
- * state does not fit LDS as bits are cut into parts that take up to 24 steps
- * per launch (their sim_step_history runs one step per launch).  Envs of
+ * state does not fit LDS as bits, and under a p_continue above 0.75 those of
+ * more than 160 x 160 cells, are cut into parts that take up to 24 steps per
+ * launch.  Calls of few steps on envs of more than 160 x 160 cells (up to 10
+ * steps, twice as many without the table below), and histories of such envs
+ * where they are fewer than the compute units or cut into parts, run one step
+ * per launch over tiles.  Envs of
  * different sizes are launches of their own, which outside captures run
  * beside each other on a stream of the handle's; the caller's stream waits
  * for it.  Under static wind it reads the table of sim_set_rate_table. */

@@ -370,11 +370,13 @@ bool wants_planes(const sim_plan& p) { return p.resident != 0 || (p.skip_static 
 
 // Lanes of the workgroup that takes an env of `cells` cells, in a batch of
 // `per_cu` envs per compute unit.  More lanes shorten a step while workgroups
-// are few, fewer lanes waste less once they share the units.  Measured, 200
-// steps of 256 x 256: 64 envs 1.04 ms with 512 lanes, 1.33 ms with 256; 1024
-// envs 2.33 ms and 2.21 ms (4.2 ms with 1024 lanes); 256 envs of 128 x 128
-// 0.76 ms with 512 and 1.00 ms with 256; 192 envs of up to 331 x 331 1.26 ms
-// with 1024 lanes for the large ones and 1.35 ms with 512.
+// are few, fewer lanes waste less once they share the units.  Measured, ms of
+// 200 steps with 256, 512 and 1024 lanes (and 64 where below 1536 cells):
+//   256 x 256  64 envs 1.27 0.98 1.07 | 512 1.60 1.48 2.30 | 768 1.94 1.89 3.37 |
+//              1024 2.38 2.83 4.46
+//   128 x 128  64 envs 0.62 0.55 0.66 | 768 1.02 0.96 2.01 | 1024 1.09 1.34 2.65
+//   300 x 300  256 envs 1.79 1.40 1.40 | 330 x 332 2.08 1.55 1.49
+//   37 x 41    64, 256, 512: 256 envs 0.26 0.25 0.25 | 1024 0.40 0.41 0.50
 int plane_threads_for(int64_t cells, int64_t per_cu)
 {
     if (cells >= 96 * 1024) return 1024;
@@ -591,11 +593,14 @@ int ensure_tiles(sim_handle* h)
     return SIM_OK;
 }
 
-// The resident workgroup size a new handle starts with, 0 for the tiled
-// plans.  Measured on 64 x 64 envs: 1024 lanes for up to 256 envs (0.43 ms
-// per 200 steps for 64 envs, against 1.2 ms for the tiled plan), 512 for
-// 1024 envs (1.26 against 2.1 ms); 64 lanes for 20 x 20 envs.  Beyond two
-// rounds of workgroups (4096 envs of 64 x 64) the tiled plan wins.
+// The resident workgroup size a new handle starts with; 0 leaves the lanes to
+// plane_threads_for, on the same kernel.  The rule dates from a kernel that held
+// bytes, and stays as it was published.  Measured now, us per 200 steps with the
+// lanes of plane_threads_for, 64, 256, 512 and 1024 (its choice in brackets):
+//   64 x 64   64 envs 308 340 274 308 [255] | 256 385 403 373 379 [327] |
+//             512 484 508 491 [483] 498 | 1024 546 509 540 [692] 852
+//   20 x 20   64 envs 84 [82] 70 69 68 | 1024 99 [99] 100 123 181
+//   92 x 92   64 envs 483 781 519 478 [613] | 512 685 1064 671 [682] 1127
 int default_resident(sim_handle* h, const PlanGroup& g)
 {
     if (!g.res.fits) return 0;
@@ -621,7 +626,7 @@ int size_class_of(int H, int W)
     return c;
 }
 
-// Alignment, sizes and the resident kernel's fit over a group's envs.
+// Alignment, sizes and the resident plan's fit over a group's envs.
 void describe_group(sim_handle* h, PlanGroup& g)
 {
     const int32_t n_members = g.envs.empty() ? h->n_env : (int32_t)g.envs.size();
@@ -735,9 +740,9 @@ hipError_t enqueue_planes(sim_handle* h, PlanGroup& g, hipStream_t s, const Step
     // Envs of different sizes, and envs in parts, do not wait for each other:
     // all but the first launch, or but the parts, go to the side stream, which
     // s then waits for.  A launch lasts as long as its longest fire, and most
-    // compute units are done long before.  256 envs each of 64, 128, 256 and
-    // 512 squared with drops: 300 steps 6.18 -> 4.24 ms, 4 steps 246 -> 198 us;
-    // fewer steps, and captures, stay in order on s.
+    // compute units are done long before.  1024 envs of 64, 128, 256 and 512
+    // squared with drops, the whole call: 300 steps 7.6 -> 5.9 ms, 4 steps 246 ->
+    // 198 us; fewer steps, and captures, stay in order on s.
     const bool parts_too = g.plane_parts.n_tiles > 0;
     hipStream_t beside = s;
     if (g.side && T >= kSideSteps) {
@@ -1375,7 +1380,7 @@ int tune_group(sim_handle* h, PlanGroup& g, hipStream_t s, const uint8_t* states
     if (allow_skip && g.aligned)  // temporal blocking reads fuel and elevation only at fronts, like skip
         for (int width : {64, 128})
             for (int k : {2, 4, 8}) cands.push_back(sim_plan{4, width, k, 1, 0, 0, 0});
-    if (allow_skip && g.res.fits)  // so does the resident kernel
+    if (allow_skip && g.res.fits)  // so does the resident plan
         for (int nt : {64, 256, 512, 1024}) cands.push_back(sim_plan{4, 64, 1, 1, allow_sparse ? 1 : 0, 0, nt});
     tried.clear();
     int rc = SIM_OK;

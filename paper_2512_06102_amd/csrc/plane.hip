@@ -22,8 +22,9 @@
 //     masked adds and one exponential.  Under a wind series, or without the
 //     table, the front cells go to the wave's own short list, 64 of which are
 //     evaluated at a time.
-// Two barriers per step (three with a drop).  No state goes to memory between
-// the steps of a launch.
+// Two barriers per step (three with a drop; one less where a region is small
+// enough for one group per lane, and is not scanned).  No state goes to memory
+// between the steps of a launch.
 //
 // What bounds it: the chain of a step (LDS round trips, one Philox block, one
 // table load, one exponential, the barriers; 4000 to 10000 cycles at one
@@ -31,13 +32,13 @@
 // to do while the fires burn, and the longest fire of a launch (at 1024 envs of
 // 256 x 256 the compute units are busy 57% of it; one env alone takes half its
 // time), not memory.  Measured against one launch per step over 64-lane tiles
-// (the other step kernel): 1024 envs of 256 x 256, 200 steps, 11.6 -> 2.3 ms;
-// 1024 envs of 64 to 512 squared with a drop per step, 300 steps, 18.5 -> 6.0
+// (the other step kernel): 1024 envs of 256 x 256, 200 steps, 11.4 -> 2.4 ms;
+// 1024 envs of 64 to 512 squared with a drop per step, 300 steps, 18.6 -> 6.1
 // ms (its two launches beside each other; 7.6 in order); 8 envs of 2048 x 2048
-// with per-cell wind, 1000 steps, 28.1 -> 5.9 ms (parts of 64 x 128 with 24
+// with per-cell wind, 1000 steps, 27.9 -> 6.0 ms (parts of 64 x 128 with 24
 // steps of halo; 0.6 ms more with 12 steps, 1.7 ms more with 128 x 128).
 // Against one workgroup per env with byte states and the exponentials worked
-// out per step: 64 envs of 64 x 64, 200 steps, 491 -> 255 us.
+// out per step: 64 envs of 64 x 64, 200 steps, 463 -> 268 us.
 //
 // With a halo the region is the tile and `steps` rows and 32 columns around
 // it; a step works out the cells that the tile's last step still depends on.
