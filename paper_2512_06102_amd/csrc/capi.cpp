@@ -730,6 +730,7 @@ hipError_t enqueue_planes(sim_handle* h, PlanGroup& g, hipStream_t s, const Step
 {
     hipError_t e;
     auto with_inputs = [&](PlaneLaunch P) {
+        P.envs = h->d_envs;
         P.n_env = h->n_env;
         P.fields = L.fields;
         P.args = L.args;

@@ -87,6 +87,7 @@ __device__ __forceinline__ uint32_t lds_add(uint32_t* p, uint32_t x)
 struct PlaneArgs {
     const PlaneTile* tiles;
     int32_t n_tiles, frame_words, list_cap, has_u;
+    const EnvDev* envs;
     int32_t n_env;
     StaticFields F;
     StepArgs A;
@@ -112,6 +113,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     PlaneArgs K)
 {
     constexpr int NW = NT / 64;
+    // A call of few steps on a small env is little more than its start.  The
+    // aligned whole envs therefore start briskly: the env's entry comes with the
+    // tile, the first cells are on their way while the planes are cleared, and the
+    // lanes' shares take no run-time divisions (64 envs of 64 x 64, 1 step: 10.2 ->
+    // 9.5 us).  The variants that have no registers to spare lose more by it (8
+    // envs of 2048 x 2048 in parts 1 to 5%).
+    constexpr bool kBrisk = ALIGNED && !HALO;
     extern __shared__ uint4 lds_dyn[];
     __shared__ float s_ew[RATES == kRatesEnvWind ? kPlaneChunk : 1][8];
     __shared__ int32_t s_act[kPlaneChunk];
@@ -138,7 +146,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
         }
     }
     const PlaneTile td = K.tiles[tix];
-    const EnvDev ed = td.dev;
+    const EnvDev ed = kBrisk ? td.dev : K.envs[td.env];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int H = ed.H, W = ed.W;
@@ -193,11 +201,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     uint32_t* const pU = nxt + K.frame_words;
     uint16_t* const list = reinterpret_cast<uint16_t*>(pF + (3 + (HALO ? K.has_u : 0)) * K.frame_words);
 
-    // how the lanes share the cells.  (Run-time divisions are long, and a call of
-    // few steps on a small env is little more than its start; the variants that
-    // have no registers to spare take the short form badly: 8 envs of 2048 x
-    // 2048 in parts ran 5% slower.)
-    auto share = [&](int q, int d, float inv_d) { return ALIGNED && !HALO ? small_div(q, d, inv_d) : q / d; };
+    // how the lanes share the cells (the store at the end keeps its divisions, and
+    // the first drops and wind wait for the planes: 200 steps of 64 envs of 64 x
+    // 64 took 274 and 278 us otherwise, now 270)
+    auto share = [&](int q, int d, float inv_d) { return kBrisk ? small_div(q, d, inv_d) : q / d; };
     const float inv_g = 1.0f / (float)G;
     const int g_step = G <= NT ? G : NT, g_rows = G <= NT ? share(NT, G, inv_g) : 1;
     const int my_gr = G <= NT ? share(tid, G, inv_g) : 0, my_g = tid - my_gr * G;
@@ -212,26 +219,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
             return v;
         }
     };
-    // on its way while the planes are cleared: this lane's first group
+    // this lane's first group
     uint32_t w_first = 0;
-    if (my_gr < g_rows && my_g < G && my_gr < RH)
+    if (kBrisk && my_gr < g_rows && my_g < G && my_gr < RH)
         w_first = load4(K.src + base + (uint32_t)((q0 + my_gr) * W + p0 + 4 * my_g), p0 + 4 * my_g);
 
     const uint32_t t0 = *K.t_base + K.step0;
     const bool ew_series = RATES == kRatesEnvWind && K.F.env_wind != nullptr;
-    // the drops and wind of the steps from s0 on
-    auto stage = [&](int32_t s0) {
-        const int nk = min(kPlaneChunk, K.steps - s0);
-        if (K.actions)
-            for (int j = tid; j < nk; j += NT) s_act[j] = K.actions[(int64_t)(s0 + j) * K.n_env + td.env];
-        if (ew_series)
-            for (int q = tid; q < nk * 8; q += NT) {
-                const int j = q >> 3, d = q & 7;
-                const float* w = K.F.env_wind + ((int64_t)(t0 + (uint32_t)s0 + j) * K.F.n_env + td.env) * 3;
-                s_ew[j][d] = wind_exponent(d, K.A.alpha_w1, K.A.alpha_w2, w[0], w[1], w[2]);
-            }
-    };
-    stage(0);
     if (RATES == kRatesEnvWind && !ew_series && tid < 8)
         s_ew[0][tid] = wind_exponent(tid, K.A.alpha_w1, K.A.alpha_w2, ed.V, ed.Vx, ed.Vy);
 
@@ -247,7 +241,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
             for (int g = my_g; g < G; g += g_step)
                 for (int r = my_gr; r < RH; r += g_rows) {
                     const int col = p0 + 4 * g;
-                    const uint32_t w = g == my_g && r == my_gr
+                    const uint32_t w = kBrisk && g == my_g && r == my_gr
                                            ? w_first
                                            : load4(K.src + base + (uint32_t)((q0 + r) * W + col), col);
                     const uint32_t f = pack4(flammable_flags(w)), bu = pack4(burning_flags(w));
@@ -281,9 +275,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     // the tile's cells to an array of whole envs
     auto store_tile = [&](uint8_t* out) {
         const int ga = tc0 >> 2, gn = (tc1 - tc0 + 3) >> 2;
-        const float inv = 1.0f / (float)gn;
-        const int st = gn <= NT ? gn : NT, rows = gn <= NT ? share(NT, gn, inv) : 1;
-        const int r0 = gn <= NT ? share(tid, gn, inv) : 0, g0 = tid - r0 * gn;
+        const int st = gn <= NT ? gn : NT, rows = gn <= NT ? NT / gn : 1;
+        const int r0 = gn <= NT ? tid / gn : 0, g0 = tid - r0 * gn;
         if (r0 >= rows) return;
         for (int g = g0; g < gn; g += st)
             for (int r = tr0 + r0; r < tr1; r += rows) {
@@ -329,10 +322,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_
     for (; s < K.steps; ++s, s3 = s3 == 2 ? 0 : s3 + 1) {
         const uint32_t t = t0 + (uint32_t)s;
         const int kc = s % kPlaneChunk;
-        if (kc == 0 && s > 0) {
-            lds_barrier();  // the last chunk's drops and wind are read, its counts summed
-            flush_counts(s - kPlaneChunk, kPlaneChunk);
-            stage(s);
+        if (kc == 0) {
+            if (s > 0) {
+                lds_barrier();  // the last chunk's drops and wind are read, its counts summed
+                flush_counts(s - kPlaneChunk, kPlaneChunk);
+            }
+            const int nk = min(kPlaneChunk, K.steps - s);
+            if (K.actions)
+                for (int j = tid; j < nk; j += NT) s_act[j] = K.actions[(int64_t)(s + j) * K.n_env + td.env];
+            if (ew_series)
+                for (int q = tid; q < nk * 8; q += NT) {
+                    const int j = q >> 3, d = q & 7;
+                    const float* w = K.F.env_wind + ((int64_t)(t + j) * K.F.n_env + td.env) * 3;
+                    s_ew[j][d] = wind_exponent(d, K.A.alpha_w1, K.A.alpha_w2, w[0], w[1], w[2]);
+                }
         }
         lds_barrier();  // F_t complete, the chunk staged, the last step's cells counted
         const uint32_t prev = s_all[s3 == 0 ? 2 : s3 - 1];
@@ -741,6 +744,7 @@ hipError_t launch_stoch_plane(hipStream_t s, const PlaneLaunch& L, const uint8_t
     K.frame_words = L.frame_words;
     K.list_cap = L.list_cap;
     K.has_u = L.halo && actions && L.args.drop_mode == 0 ? 1 : 0;
+    K.envs = L.envs;
     K.n_env = L.n_env;
     K.F = L.fields;
     K.A = L.args;

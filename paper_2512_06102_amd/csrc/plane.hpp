@@ -13,8 +13,8 @@ namespace firesim {
 
 // One workgroup's cells: `rows` x `cols` of env `env` from (r0, c0).  A tile
 // is a whole env, or (in a launch with a halo) a part of one with c0 a
-// multiple of 32.  It holds the env's own entry, so that a workgroup starts with
-// one load and not two in turn.
+// multiple of 32.  It holds the env's own entry, so that a workgroup can start
+// with one load and not two in turn.
 struct PlaneTile {
     int32_t env, r0, c0, rows, cols;
     EnvDev dev;
@@ -66,6 +66,7 @@ struct PlaneLaunch {
     int32_t threads;      // 64, 256, 512 or 1024
     int32_t frame_words;  // largest plane of the launch's regions
     int32_t list_cap;
+    const EnvDev* envs;
     int32_t n_env;
     StaticFields fields;
     StepArgs args;
