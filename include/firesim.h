@@ -323,8 +323,9 @@ int sim_get_plan(const sim_handle* h, sim_plan* plan);
  * result depends on it).  sim_init builds it when it takes at most a quarter
  * of the free device memory; without it the rates are worked out in every
  * step, which then takes longer.  on 0 frees it, for instance on a handle
- * that only calibrates (waits for the device; not during a capture); on 1
- * builds it again (synchronises `stream`; SIM_ENOMEM if it would take more
+ * that only calibrates (waits for the device; not during a capture, and
+ * SIM_ESTATE once a step was captured into a caller's graph, which may still
+ * read it); on 1 builds it again (synchronises `stream`; SIM_ENOMEM if it would take more
  * than a quarter of the free memory). */
 int sim_set_rate_table(sim_handle* h, int32_t on, void* stream);
 

@@ -335,7 +335,8 @@ class FireSim:
     def set_rate_table(self, on: bool = True):
         """Free (or build again) the table of ignition rates under static wind,
         32 bytes per cell.  Steps give the same results without it, and take
-        longer; the relaxed path does not use it."""
+        longer; the relaxed path does not use it.  Refused once a step has been
+        captured into a graph, which may still read it."""
         _check(lib().sim_set_rate_table(self.handle, int(bool(on)), self._s()), self.handle)
 
     @property
@@ -423,7 +424,10 @@ class FireSim:
         try:
             return torch.empty(n, dtype=torch.uint8, device=self.device)
         except torch.OutOfMemoryError:  # the relaxed path does not read the table
-            self.set_rate_table(False)
+            try:
+                self.set_rate_table(False)
+            except SimError:  # a captured step does
+                pass
         return torch.empty(n, dtype=torch.uint8, device=self.device)
 
     def relaxed_fwd(self, params: SimParams, U, B, T, ckpt_every, ws, form: str = "product"):

@@ -176,6 +176,7 @@ struct sim_handle {
     float* d_den = nullptr;
     float* d_wind = nullptr;
     float* d_phi = nullptr;            // [n_cells][8] ignition rate of every edge (nullptr: worked out in the step)
+    bool phi_captured = false;         // a caller's graph may read d_phi
     uint8_t* d_init_states = nullptr;  // initial fire state (for the relaxed initial state)
     uint8_t* d_tmp = nullptr;          // ping-pong state buffer
     uint32_t* d_t = nullptr;           // step counter base read by the step kernels
@@ -879,6 +880,15 @@ hipError_t build_rate_table(sim_handle* h, hipStream_t s)
     return launch_phi_table(s, h->d_envs, h->d_chunk_env, h->n_chunks, F, step_args(h), h->d_phi);
 }
 
+// Notes a step under a caller's capture: its graph keeps the table's address.
+void note_capture(sim_handle* h, hipStream_t s)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (s && h->d_phi && !h->phi_captured && hipStreamIsCapturing(s, &capture) == hipSuccess &&
+        capture != hipStreamCaptureStatusNone)
+        h->phi_captured = true;
+}
+
 bool same_plan(const sim_plan& a, const sim_plan& b)
 {
     return a.tile_rows == b.tile_rows && a.tile_width == b.tile_width && a.temporal == b.temporal &&
@@ -1101,6 +1111,7 @@ int step_common(sim_handle* h, uint8_t* states, const int32_t* actions, int32_t 
         const int rc = ensure_tiles(h);
         if (rc != SIM_OK) return rc;
     }
+    note_capture(h, s);
     HIP_OR_FAIL(h, launch_set_u32(s, h->d_t, (uint32_t)h->t));
     if (h->plan.graph) {
         GraphCache& G = h->graph;
@@ -1209,6 +1220,7 @@ int sim_rl_step(sim_handle* h, const sim_rl_config* cfg, uint8_t* states, sim_rl
         return fail(h, SIM_EINVAL, "the wind series does not cover step %llu", (unsigned long long)h->t);
     hipStream_t s = (hipStream_t)stream;
     if ((rc = ensure_tiles(h)) != SIM_OK) return rc;
+    note_capture(h, s);
     RlAgent* ag = reinterpret_cast<RlAgent*>(agents);
     if (cfg->single_launch && h->rl_shape.fits) {
         StepLaunch L = step_launch(h, h->all);
@@ -1263,6 +1275,8 @@ int sim_set_rate_table(sim_handle* h, int32_t on, void* stream)
     CallScope scope("sim_set_rate_table", h);
     if (!h) return fail(nullptr, SIM_EINVAL, "handle is NULL");
     if (on != 0 && on != 1) return fail(h, SIM_EINVAL, "on must be 0 or 1");
+    if (!on && h->d_phi && h->phi_captured)
+        return fail(h, SIM_ESTATE, "a captured step may still read the table of ignition rates");
     h->graph.valid = false;  // the table is a kernel argument
     if (!on) {
         if (h->d_phi) HIP_OR_FAIL(h, hipFree(h->d_phi));

@@ -106,3 +106,43 @@ def test_the_table_is_given_back(monkeypatch):
     del ws
     torch.cuda.empty_cache()
     assert free() >= held + table // 2
+
+
+@pytest.mark.parametrize("rl_step", [False, True])
+def test_a_captured_step_keeps_the_table(rl_step, monkeypatch):
+    """Its graph holds the table's address: it is not given back, neither on
+    request nor for a workspace, and the replays stay right."""
+    batch = firegen.landscape_batch(108, [(64, 64)] * 4)
+    params = _params(108)
+    sim = fs.FireSim.from_batch(batch, params, seed=25)
+    env = fs.RLEnv(sim)
+    acts = torch.zeros(4, dtype=torch.int32, device="cuda")
+    if rl_step:
+        env.reset(episode=1)
+        env.step(acts)
+    init = sim.states.clone()
+    sim.t = 0
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        env.step(acts) if rl_step else sim.step(20)
+    with pytest.raises(fs.SimError):
+        sim.set_rate_table(False)
+    empty = torch.empty
+
+    def refused(*args, **kw):
+        raise torch.OutOfMemoryError("refused")
+
+    monkeypatch.setattr(torch, "empty", refused)
+    with pytest.raises(torch.OutOfMemoryError):
+        sim.relaxed_workspace(1, 1)
+    monkeypatch.undo()
+    assert torch.empty is empty
+    if not rl_step:
+        ref = oracle.Sim(batch, params, seed=25)
+        ref.step(20, threads=4)
+        for _ in range(3):
+            sim.states.copy_(init)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(sim.states.cpu().numpy(), ref.states)
